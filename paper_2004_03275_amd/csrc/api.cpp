@@ -78,7 +78,7 @@ Layout plan(const amrv_config& c, const Tables& t) {
   L.off_plist = take(sizeof(int32_t) * std::max<size_t>(1, t.plist.size()));
   L.off_pp = take(sizeof(double) * PP_COUNT);
   L.off_lp = take(sizeof(double) * LP_COUNT);
-  L.off_red = take(sizeof(unsigned long long) * 4);
+  L.off_red = take(sizeof(unsigned long long) * RED_WORDS);
   L.off_cnt = take(sizeof(unsigned) * CNT_COUNT);
   L.off_emax = take(sizeof(double) * t.n);
   L.off_flags = take(sizeof(int8_t) * t.n);
@@ -552,10 +552,12 @@ int amrv_get_state(amrv_forest* f, double* U, int64_t nd, int32_t on_device) {
 
 int amrv_max_dt(amrv_forest* f, double* dt_out) {
   if (!f || !dt_out) return fail(AMRV_EINVAL, "null argument");
-  HIPCHK(launch_reset_u32((unsigned*)f->red, 8, f->st));
+  HIPCHK(launch_reset_u32((unsigned*)f->red, 2 * RED_SLOTS * RED_STRIDE, f->st));
   HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->st));
-  unsigned long long h[4] = {0, 0, 0, 0};
-  HIPCHK(hipMemcpyAsync(h, f->red, sizeof h, hipMemcpyDeviceToHost, f->st));
+  unsigned long long* res = f->red + RED_SLOTS * RED_STRIDE;
+  HIPCHK(launch_red_result(f->red, res, f->st));
+  unsigned long long h[3] = {0, 0, 0};
+  HIPCHK(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, f->st));
   HIPCHK(hipStreamSynchronize(f->st));
   f->fold_valid = true;
   if (h[2]) return fail(AMRV_ENONPHYSICAL, "non-physical state (rho <= 0, p <= 0 or NaN)");
@@ -605,7 +607,7 @@ int amrv_advance_cfl(amrv_forest* f, int32_t nsteps, double t_end, double* t, in
   int rc = set_scalars(f, PP_T, {*t});
   if (rc) return rc;
   if (!f->fold_valid) {
-    HIPCHK(launch_reset_u32((unsigned*)f->red, 8, f->st));
+    HIPCHK(launch_reset_u32((unsigned*)f->red, 2 * RED_SLOTS * RED_STRIDE, f->st));
     HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->st));
   }
   f->fold_valid = false;

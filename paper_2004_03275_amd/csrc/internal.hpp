@@ -58,7 +58,7 @@ struct StageArgs {
   const double* dtp;   // device-resident dt
   int stage;           // 1..rk
   int rk;              // 2 or 3
-  unsigned long long* cflred;  // last stage: fold the Courant reduction of the new state here (or null)
+  unsigned long long* cflred;  // last stage: fold the Courant reduction of the new state into these slots (or null)
   double* Gw;          // 3D combined variant: restrict the stage output onto the coarse neighbours'
                        // ghost slabs of this buffer (the G layout), or null
   uint16_t* Xout;      // 3D combined variant, last stage: the learned flagger's features of the
@@ -103,6 +103,12 @@ hipError_t launch_transfer(const Geo& from, const double* Uf, const Geo& to, dou
 hipError_t launch_set_scalars(double* dst, const double* src_host_vals, int n, hipStream_t st);
 hipError_t launch_reset_u32(unsigned* p, int n, hipStream_t st);
 hipError_t launch_scale_var(double* U, const double* facp, long long count, hipStream_t st);
+// Courant reduction: RED_SLOTS slots of RED_STRIDE 64-bit words (a cache line
+// each), words 0..2 of each in use; RED_WORDS with the three result words that
+// follow the slots
+constexpr int RED_SLOTS = 256, RED_STRIDE = 8, RED_WORDS = RED_SLOTS * RED_STRIDE + 4;
+// the slots' maxima into three words
+hipError_t launch_red_result(const unsigned long long* red, unsigned long long* out, hipStream_t st);
 // device-side time step from a Courant reduction: dt = min(cfl / smax, t_end - t),
 // t += dt, c_h and the GLM damping factor into the parameter block, then the
 // reduction words are cleared for the next fold

@@ -1123,9 +1123,10 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
 // ---------------------------------------------------------------------------
 
 
-// red[0] = bits of max_cells sum_d (|v_d|+c_d)/dx_d, red[1] = bits of the max
-// signal speed (GLM c_h), red[2] = non-physical flag.  Non-negative doubles
-// order like their bit patterns, so integer atomics give the exact maximum.
+// Words of a reduction slot: [0] bits of max_cells sum_d (|v_d|+c_d)/dx_d, [1]
+// bits of the max signal speed (GLM c_h), [2] non-physical flag; the result is
+// the maximum over the slots.  Non-negative doubles order like their bit
+// patterns, so integer atomics give the exact maximum.
 template <int ND, int PH>
 __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U, const double* __restrict__ pp,
                                              unsigned long long* red) {
@@ -1134,8 +1135,9 @@ __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U
   const long long total = (long long)g.n * g.ncell;
   unsigned long long smax = 0, cmax = 0;
   int bad = 0;
+  constexpr int NC = ND == 3 ? NB * NB * NB : NB * NB;  // cells of a 2D / 3D leaf
   for (long long i = (long long)blockIdx.x * WGS + threadIdx.x; i < total; i += (long long)gridDim.x * WGS) {
-    const int leaf = (int)(i / g.ncell), cell = (int)(i % g.ncell);
+    const int leaf = (int)(ND == 1 ? i / g.ncell : i / NC), cell = (int)(ND == 1 ? i % g.ncell : i % NC);
     double u[NV], v[NV];
 #pragma unroll
     for (int k = 0; k < NV; k++) u[k] = U[uidx(g, k, leaf, cell)];
@@ -1158,14 +1160,7 @@ __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U
     smax = sb > smax ? sb : smax;
     cmax = cb > cmax ? cb : cmax;
   }
-  smax = wave_max_u64(smax);
-  cmax = wave_max_u64(cmax);
-  bad = __any(bad);
-  if ((threadIdx.x & 63) == 0) {
-    if (smax) atomicMax(&red[0], smax);
-    if (cmax) atomicMax(&red[1], cmax);
-    if (bad) atomicOr(&red[2], 1ull);
-  }
+  cfl_fold(red, smax, cmax, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -1487,7 +1482,7 @@ hipError_t launch_cfl(const Geo& g, const LaunchCfg& c, const double* U, const d
                       unsigned long long* red, hipStream_t st) {
   const long long total = (long long)g.n * g.ncell;
   long long nb = (total + WGS - 1) / WGS;
-  if (nb > 4096) nb = 4096;
+  if (nb > 2048) nb = 2048;  // 8 workgroups per CU; the rest by the grid stride
 #define BODY_C(ND)                                                                                                    \
   if (c.phys == PH_MHD)                                                                                               \
     hipLaunchKernelGGL((k_cfl<ND, PH_MHD>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red);                  \
@@ -1529,16 +1524,20 @@ hipError_t launch_lohner(const Geo& g, const LaunchCfg& c, const double* U, cons
   return hipGetLastError();
 }
 
-__global__ void k_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err, double cfl, double t_end,
-                            double glm_cr, int mhd) {
+__global__ void __launch_bounds__(WGS) k_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err,
+                                                   double cfl, double t_end, double glm_cr, int mhd) {
+  unsigned long long sb, cb;
+  int bad;
+  red_all(red, sb, cb, bad);
+#pragma unroll
+  for (int w = 0; w < 3; w++) red[threadIdx.x * RED_STRIDE + w] = 0ull;
   if (threadIdx.x != 0) return;
-  const unsigned long long sb = red[0], cb = red[1];
-  if (red[2]) *err = 1u;
+  if (bad) *err = 1u;
   const double smax = __longlong_as_double((long long)sb);
   const double ch = __longlong_as_double((long long)cb);
   const double tn = *t;
   double dt = 0.0;
-  if (tn < t_end && smax > 0.0 && !red[2]) {
+  if (tn < t_end && smax > 0.0 && !bad) {
     dt = cfl / smax;
     const double rem = t_end - tn;
     if (rem < dt) dt = rem;
@@ -1550,14 +1549,28 @@ __global__ void k_dt_update(unsigned long long* red, double* pp, double* t, unsi
     pp[PP_CH] = ch;
     pp[PP_DAMP] = exp(-(dt * ch) / glm_cr);
   }
-  red[0] = 0ull;
-  red[1] = 0ull;
-  red[2] = 0ull;
 }
 
 hipError_t launch_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err, double cfl, double t_end,
                             double glm_cr, int mhd, hipStream_t st) {
-  hipLaunchKernelGGL(k_dt_update, dim3(1), dim3(64), 0, st, red, pp, t, err, cfl, t_end, glm_cr, mhd);
+  hipLaunchKernelGGL(k_dt_update, dim3(1), dim3(WGS), 0, st, red, pp, t, err, cfl, t_end, glm_cr, mhd);
+  return hipGetLastError();
+}
+
+// the slots' result into out[0..2] (the slots keep their values)
+__global__ void __launch_bounds__(WGS) k_red_result(const unsigned long long* red, unsigned long long* out) {
+  unsigned long long sb, cb;
+  int bad;
+  red_all(red, sb, cb, bad);
+  if (threadIdx.x == 0) {
+    out[0] = sb;
+    out[1] = cb;
+    out[2] = (unsigned long long)bad;
+  }
+}
+
+hipError_t launch_red_result(const unsigned long long* red, unsigned long long* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_red_result, dim3(1), dim3(WGS), 0, st, red, out);
   return hipGetLastError();
 }
 

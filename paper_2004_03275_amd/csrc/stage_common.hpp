@@ -165,16 +165,55 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
   return x;
 }
 
-// fold per-thread Courant maxima into the reduction words (one atomic per wave)
+// fold per-thread Courant maxima into the reduction slots (one atomic per
+// wave and word).  Atomics on one address are served one after another, about
+// 12 ns each across the XCDs: with a single set of words the waves of one
+// launch queued for 23 us on 256 2D leaves (stage 30 us instead of 7) and
+// 383 us in k_cfl over 2.1M cells, so consecutive waves take different slots,
+// each a cache line of its own.  A wave's slot comes from the compute unit and
+// XCD it runs on (HW_ID bits 8..15, XCC_ID): taken from blockIdx.x, which then
+// stays live through the whole kernel, it cost the register-bound 3D stage
+// kernel 10% (511 -> 560 us per launch in exact arithmetic).
 __device__ __forceinline__ void cfl_fold(unsigned long long* red, unsigned long long smax, unsigned long long cmax,
                                          int bad) {
   smax = wave_max_u64(smax);
   cmax = wave_max_u64(cmax);
   bad = __any(bad);
   if ((threadIdx.x & 63) == 0) {
-    if (smax) atomicMax(&red[0], smax);
-    if (cmax) atomicMax(&red[1], cmax);
-    if (bad) atomicOr(&red[2], 1ull);
+    const unsigned cu = __builtin_amdgcn_s_getreg((7 << 11) | (8 << 6) | 4);
+    const unsigned xcc = __builtin_amdgcn_s_getreg((3 << 11) | 20);
+    unsigned long long* r = red + ((cu + 64 * xcc) & (RED_SLOTS - 1)) * RED_STRIDE;
+    if (smax) atomicMax(&r[0], smax);
+    if (cmax) atomicMax(&r[1], cmax);
+    if (bad) atomicOr(&r[2], 1ull);
+  }
+}
+
+// the maxima (and the non-physical flag) of all reduction slots, in every
+// thread of a WGS-thread workgroup (WGS == RED_SLOTS: one slot per thread)
+__device__ __forceinline__ void red_all(const unsigned long long* red, unsigned long long& smax,
+                                        unsigned long long& cmax, int& bad) {
+  static_assert(WGS == RED_SLOTS, "one slot per thread");
+  __shared__ unsigned long long sr[2][WGS / 64];
+  __shared__ int sb[WGS / 64];
+  const unsigned long long* r = red + threadIdx.x * RED_STRIDE;
+  const unsigned long long s0 = r[0], c0 = r[1], b0 = r[2];
+  const unsigned long long s = wave_max_u64(s0), c = wave_max_u64(c0);
+  const int b = __any(b0 != 0);
+  if ((threadIdx.x & 63) == 0) {
+    sr[0][threadIdx.x >> 6] = s;
+    sr[1][threadIdx.x >> 6] = c;
+    sb[threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  smax = 0;
+  cmax = 0;
+  bad = 0;
+#pragma unroll
+  for (int w = 0; w < WGS / 64; w++) {
+    smax = sr[0][w] > smax ? sr[0][w] : smax;
+    cmax = sr[1][w] > cmax ? sr[1][w] : cmax;
+    bad |= sb[w];
   }
 }
 
