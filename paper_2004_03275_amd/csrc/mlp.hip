@@ -10,9 +10,10 @@
 //   k_mlp_infer     refine and coarsen logits of all leaves: bfloat16 MFMA
 //                   products (v_mfma_f32_16x16x32_bf16), binary32 accumulation,
 //                   and each leaf's three-way flag from its two logits
-//   k_mlp_train     one optimisation step on a batch: forward, class-weighted
-//                   binary cross-entropy, backward (weight gradients again as
-//                   bfloat16 MFMA products with binary32 accumulation), Adam
+//   k_mlp_grad      a batch's forward pass, class-weighted binary cross-entropy
+//                   and backward pass (weight gradients again as bfloat16 MFMA
+//                   products with binary32 accumulation), partial gradients
+//   k_mlp_step      their sum in a fixed order, Adam
 // Reductions run in a fixed order, so results are deterministic.
 #include <type_traits>
 
@@ -41,16 +42,6 @@ __device__ __forceinline__ bf16x8 zero8() {
   bf16x8 r;
   const uint4 z = make_uint4(0, 0, 0, 0);
   __builtin_memcpy(&r, &z, 16);
-  return r;
-}
-
-// gather 8 bfloat16 values with a stride (in elements)
-__device__ __forceinline__ bf16x8 gather8(const uint16_t* p, int stride) {
-  uint16_t t[8];
-#pragma unroll
-  for (int j = 0; j < 8; j++) t[j] = p[j * stride];
-  bf16x8 r;
-  __builtin_memcpy(&r, t, 16);
   return r;
 }
 
@@ -242,209 +233,251 @@ __global__ void __launch_bounds__(256) k_mlp_infer(const uint16_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// training step: one workgroup, one batch
+// training step: the batch's rows over many workgroups, then one update launch
 // ---------------------------------------------------------------------------
 
-// scratch layout (bytes offsets computed by mlp_train_layout)
-struct TrainScratch {
-  uint16_t* xg;    // [B][128] gathered batch features
-  uint16_t* xgT;   // [128][B]
-  uint16_t* h1;    // [B][64]
-  uint16_t* h1T;   // [64][B]
-  uint16_t* h2;    // [B][64]
-  uint16_t* dh2;   // [B][64] bfloat16
-  uint16_t* dh2T;  // [64][B]
-  uint16_t* dh1T;  // [64][B]
-  float* dh1;      // [B][64] binary32 (bias gradient)
-  float* z;        // [B][2]
-  float* dz;       // [B][2]
-  float* grad;     // [NPARAM]
-  float* loss;     // [B] per-row loss
-  uint16_t* wb;    // bfloat16 operand copies
-  int* tstep;      // Adam step counter
-};
+// A step is two launches.  k_mlp_grad: each workgroup takes `rows` rows of the
+// batch through the forward and backward pass with every activation in LDS
+// and writes its own partial gradient (part[workgroup][NPARAM + 1], the last
+// value its loss sum); k_mlp_step adds the partials in workgroup order and
+// applies Adam, so the sums have a fixed order and the result is
+// deterministic.  Bound by latency (0.03 GFLOP a batch of 1,024).  One
+// workgroup per batch, its activations in global scratch, left 255 CUs idle:
+// 1,060 us a batch of 1,024; 32 rows per workgroup (one K step of the
+// 16x16x32 products, 32 workgroups) 13.2 us + 4.0 us.
+constexpr int TR = 32;           // rows of a K step
+constexpr int TS = TR + 8;       // LDS row stride of the [feature][row] arrays (16-byte multiples, spread over banks)
+constexpr int HS = MLP_NH + 8;   // and of the [row][unit] arrays
 
-__global__ void __launch_bounds__(256) k_mlp_train(const uint16_t* __restrict__ X, const float* __restrict__ Y,
-                                                   const int32_t* __restrict__ order, int n, int B, int batch,
-                                                   float* __restrict__ w, float* __restrict__ am, float* __restrict__ av,
-                                                   TrainHyper hp, TrainScratch s, float* __restrict__ loss_out) {
-  __shared__ __attribute__((aligned(16))) uint16_t h1t[4][16 * MLP_NH];
-  __shared__ __attribute__((aligned(16))) uint16_t h2t[4][16 * MLP_NH];
-  __shared__ float red[256];
+// rows per workgroup: 32, or 64 where 32 would give more than 64 partials (the
+// scratch then stays below that of a whole batch's activations)
+constexpr int mlp_train_rows(int B) { return B <= 64 * TR ? TR : 2 * TR; }
+
+__global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X, const float* __restrict__ Y,
+                                                  const int32_t* __restrict__ order, int n, int B, int batch, int rows,
+                                                  const float* __restrict__ w, const uint16_t* __restrict__ wb,
+                                                  TrainHyper hp, float* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint16_t xT[MLP_NIN * TS];
+  __shared__ __attribute__((aligned(16))) uint16_t h1[TR * HS], h1T[MLP_NH * TS], h2[TR * HS];
+  __shared__ __attribute__((aligned(16))) uint16_t dh2[TR * HS], dh2T[MLP_NH * TS], dh1T[MLP_NH * TS];
+  __shared__ float dh1[TR * (MLP_NH + 1)];
+  __shared__ float zs[TR][MLP_NOUT], dz[TR][MLP_NOUT], ls[TR];
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63;
-  const int lm = l & 15, lk = 8 * (l >> 4);
+  const int lm = l & 15, lk = 8 * (l >> 4), lq = 4 * (l >> 4);
   const int b0 = batch * B;
   int nvalid = n - b0;
   if (nvalid > B) nvalid = B;
-
-  // P0: gather the batch (padding rows are zero with zero weight)
-  for (int i = tid; i < B * MLP_NIN; i += 256) {
-    const int r = i / MLP_NIN, c = i % MLP_NIN;
-    const uint16_t v = r < nvalid ? X[(size_t)order[b0 + r] * MLP_NIN + c] : (uint16_t)0;
-    s.xg[i] = v;
-    s.xgT[(size_t)c * B + r] = v;
-  }
-  __threadfence_block();
-  __syncthreads();
-
-  // P1: forward, 16-row tiles round-robin over the waves
-  for (int rt = wave; rt < B / 16; rt += 4) {
-    const int r0 = rt * 16;
-    auto xrow = [&](int m) -> const uint16_t* { return s.xg + (size_t)(r0 + m) * MLP_NIN; };
-    const float z = tile_forward(xrow, s.wb, w, h1t[wave], h2t[wave]);
-    // activations for the backward pass
-    for (int i = l; i < 16 * MLP_NH; i += 64) {
-      const int m = i / MLP_NH, c = i % MLP_NH;
-      s.h1[(size_t)(r0 + m) * MLP_NH + c] = h1t[wave][i];
-      s.h1T[(size_t)c * B + r0 + m] = h1t[wave][i];
-      s.h2[(size_t)(r0 + m) * MLP_NH + c] = h2t[wave][i];
-    }
-    if (l < 32) s.z[(size_t)(r0 + (l & 15)) * MLP_NOUT + (l >> 4)] = z;
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-  }
-  __threadfence_block();
-  __syncthreads();
-
-  // P2: logit gradients and loss per row.  The label is Loehner's class
-  // (+1 refine, -1 coarsen, 0 keep): target 1 of the refine output for +1,
-  // of the coarsen output for -1; each output's class-weighted binary
-  // cross-entropy, summed
   const float Bv = (float)nvalid;
-  for (int r = tid; r < B; r += 256) {
-    float dzr = 0.f, dzc = 0.f, lr = 0.f;
-    if (r < nvalid) {
-      const float lab = Y[order[b0 + r]];
+  const int rt = wave & 1, np = wave >> 1;  // forward: a 16-row tile and half of the output units per wave
+
+  f32x4 g1[8], g2[4];  // dW1, dW2 tiles of this wave
 #pragma unroll
-      for (int o = 0; o < MLP_NOUT; o++) {
-        const float z = s.z[(size_t)r * MLP_NOUT + o];
-        const float y = o == 0 ? (lab > 0.5f ? 1.f : 0.f) : (lab < -0.5f ? 1.f : 0.f);
-        const float pw = o == 0 ? hp.pos_weight : hp.pos_weight_c;
-        const float sg = 1.f / (1.f + expf(-z));
-        const float dz = ((1.f - y) * sg - pw * y * (1.f - sg)) / Bv;
-        // -(pw y log s + (1-y) log(1-s)) with log s = -softplus(-z)
-        const float sp_neg = fmaxf(-z, 0.f) + log1pf(expf(-fabsf(z)));
-        const float sp_pos = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));
-        lr = lr + (pw * y * sp_neg + (1.f - y) * sp_pos);
-        if (o == 0)
-          dzr = dz;
-        else
-          dzc = dz;
+  for (int i = 0; i < 8; i++) g1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 4; i++) g2[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gs = 0.f, gb1 = 0.f;  // W3 (threads 0..127), b3 (128, 129), loss (130), b2 (192..255); b1 (192..255)
+
+  const int rend = min(B, (int)(blockIdx.x + 1) * rows);
+  for (int r0 = blockIdx.x * rows; r0 < rend; r0 += TR) {
+    // layer 1; the rows (zeros past the batch's last sample) also to xT
+    {
+      const int r = r0 + rt * 16 + lm;
+      const uint16_t* xr = r < nvalid ? X + (size_t)order[b0 + r] * MLP_NIN : nullptr;
+      bf16x8 xa[4];
+#pragma unroll
+      for (int kt = 0; kt < 4; kt++) xa[kt] = xr ? load8(xr + kt * 32 + lk) : zero8();
+#pragma unroll
+      for (int k2 = 0; k2 < 2; k2++) {
+        uint16_t t[8];
+        const bf16x8 v = np ? xa[2 + k2] : xa[k2];
+        __builtin_memcpy(t, &v, 16);
+#pragma unroll
+        for (int j = 0; j < 8; j++) xT[((2 * np + k2) * 32 + lk + j) * TS + rt * 16 + lm] = t[j];
+      }
+#pragma unroll
+      for (int q = 0; q < 2; q++) {
+        const int u = (2 * np + q) * 16 + lm;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < 4; kt++) acc = mfma(xa[kt], load8(wb + MLP_WB_W1 + u * MLP_NIN + kt * 32 + lk), acc);
+        const float bias = w[MLP_B1 + u];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const float a = acc[i] + bias;
+          const uint16_t hb = to_bf16(a > 0.f ? a : 0.f);
+          h1[(rt * 16 + lq + i) * HS + u] = hb;
+          h1T[u * TS + rt * 16 + lq + i] = hb;
+        }
       }
     }
-    s.dz[(size_t)r * MLP_NOUT] = dzr;
-    s.dz[(size_t)r * MLP_NOUT + 1] = dzc;
-    s.loss[r] = lr;
-  }
-  __threadfence_block();
-  __syncthreads();
-
-  // P3: W3, b3, b2 gradients; dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0]
-  // (binary32, then bfloat16)
-  if (tid < MLP_NOUT * MLP_NH) {
-    const int o = tid / MLP_NH, c = tid % MLP_NH;
-    float g3 = 0.f;
-    for (int r = 0; r < B; r++) g3 = g3 + s.dz[(size_t)r * MLP_NOUT + o] * from_bf16(s.h2[(size_t)r * MLP_NH + c]);
-    s.grad[MLP_W3 + tid] = g3;
-  } else if (tid < MLP_NOUT * MLP_NH + MLP_NOUT) {
-    const int o = tid - MLP_NOUT * MLP_NH;
-    float g = 0.f, L = 0.f;
-    for (int r = 0; r < B; r++) {
-      g = g + s.dz[(size_t)r * MLP_NOUT + o];
-      L = L + s.loss[r];
+    __syncthreads();
+    // layer 2
+#pragma unroll
+    for (int q = 0; q < 2; q++) {
+      const int u = (2 * np + q) * 16 + lm;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kt = 0; kt < 2; kt++)
+        acc = mfma(load8(h1 + (rt * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2 + u * MLP_NH + kt * 32 + lk), acc);
+      const float bias = w[MLP_B2 + u];
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const float a = acc[i] + bias;
+        h2[(rt * 16 + lq + i) * HS + u] = to_bf16(a > 0.f ? a : 0.f);
+      }
     }
-    s.grad[MLP_B3 + o] = g;
-    if (loss_out && o == 0) loss_out[batch] = L / Bv;
-  }
-  auto dh2_of = [&](int r, int c) -> float {
-    return from_bf16(s.h2[(size_t)r * MLP_NH + c]) > 0.f
-               ? s.dz[(size_t)r * MLP_NOUT] * from_bf16(s.wb[MLP_WB_W3 + c]) +
-                     s.dz[(size_t)r * MLP_NOUT + 1] * from_bf16(s.wb[MLP_WB_W3 + MLP_NH + c])
-               : 0.f;
-  };
-  for (int i = tid; i < B * MLP_NH; i += 256) {
-    const int r = i / MLP_NH, c = i % MLP_NH;
-    const uint16_t db = to_bf16(dh2_of(r, c));
-    s.dh2[i] = db;
-    s.dh2T[(size_t)c * B + r] = db;
-  }
-  __threadfence_block();
-  __syncthreads();
-  if (tid < MLP_NH) {
-    float g = 0.f;
-    for (int r = 0; r < B; r++) g = g + dh2_of(r, tid);
-    s.grad[MLP_B2 + tid] = g;
-  }
-
-  // P4a: dW2 = dh2^T h1  (64 x 64, K = B): 16 output tiles, 4 per wave
-  for (int tt = wave; tt < 16; tt += 4) {
-    const int mt = tt >> 2, nt = tt & 3;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < B / 32; kt++)
-      acc = mfma(load8(s.dh2T + (size_t)(mt * 16 + lm) * B + kt * 32 + lk),
-                 load8(s.h1T + (size_t)(nt * 16 + lm) * B + kt * 32 + lk), acc);
-#pragma unroll
-    for (int i = 0; i < 4; i++) s.grad[MLP_W2 + (mt * 16 + 4 * (l >> 4) + i) * MLP_NH + nt * 16 + lm] = acc[i];
-  }
-  // P4b: dh1 = dh2 W2 * [h1 > 0]  (B x 64, K = 64)
-  for (int tt = wave; tt < (B / 16) * 4; tt += 4) {
-    const int rt = tt >> 2, nt = tt & 3;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int kt = 0; kt < 2; kt++)
-      acc = mfma(load8(s.dh2 + (size_t)(rt * 16 + lm) * MLP_NH + kt * 32 + lk),
-                 load8(s.wb + MLP_WB_W2T + (nt * 16 + lm) * MLP_NH + kt * 32 + lk), acc);
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      const int r = rt * 16 + 4 * (l >> 4) + i, c = nt * 16 + lm;
-      const float d = from_bf16(s.h1[(size_t)r * MLP_NH + c]) > 0.f ? acc[i] : 0.f;
-      s.dh1[(size_t)r * MLP_NH + c] = d;
-      s.dh1T[(size_t)c * B + r] = to_bf16(d);
+    __syncthreads();
+    // logits, in unit order
+    if (tid < TR * MLP_NOUT) {
+      const int o = tid >> 5, r = tid & 31;
+      float z = 0.f;
+      for (int k = 0; k < MLP_NH; k++) z = z + from_bf16(h2[r * HS + k]) * from_bf16(wb[MLP_WB_W3 + o * MLP_NH + k]);
+      zs[r][o] = z + w[MLP_B3 + o];
     }
-  }
-  __threadfence_block();
-  __syncthreads();
-
-  // P5: dW1 = dh1^T X (64 x 128, K = B): 32 tiles; b1 gradient
-  for (int tt = wave; tt < 32; tt += 4) {
-    const int mt = tt >> 3, nt = tt & 7;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int kt = 0; kt < B / 32; kt++)
-      acc = mfma(load8(s.dh1T + (size_t)(mt * 16 + lm) * B + kt * 32 + lk),
-                 load8(s.xgT + (size_t)(nt * 16 + lm) * B + kt * 32 + lk), acc);
+    __syncthreads();
+    // logit gradients and loss per row.  The label is Loehner's class (+1
+    // refine, -1 coarsen, 0 keep): target 1 of the refine output for +1, of
+    // the coarsen output for -1; each output's class-weighted binary
+    // cross-entropy, summed
+    if (tid < TR) {
+      float d[MLP_NOUT] = {0.f, 0.f}, lr = 0.f;
+      if (r0 + tid < nvalid) {
+        const float lab = Y[order[b0 + r0 + tid]];
 #pragma unroll
-    for (int i = 0; i < 4; i++) s.grad[MLP_W1 + (mt * 16 + 4 * (l >> 4) + i) * MLP_NIN + nt * 16 + lm] = acc[i];
+        for (int o = 0; o < MLP_NOUT; o++) {
+          const float z = zs[tid][o];
+          const float y = o == 0 ? (lab > 0.5f ? 1.f : 0.f) : (lab < -0.5f ? 1.f : 0.f);
+          const float pw = o == 0 ? hp.pos_weight : hp.pos_weight_c;
+          const float sg = 1.f / (1.f + expf(-z));
+          d[o] = ((1.f - y) * sg - pw * y * (1.f - sg)) / Bv;
+          // -(pw y log s + (1-y) log(1-s)) with log s = -softplus(-z)
+          const float sp_neg = fmaxf(-z, 0.f) + log1pf(expf(-fabsf(z)));
+          const float sp_pos = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));
+          lr = lr + (pw * y * sp_neg + (1.f - y) * sp_pos);
+        }
+      }
+      dz[tid][0] = d[0];
+      dz[tid][1] = d[1];
+      ls[tid] = lr;
+    }
+    __syncthreads();
+    // dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0] (binary32, then bfloat16); the
+    // W3, b3, b2 gradients and the loss
+    auto dh2_of = [&](int r, int c, float wr, float wc) -> float {
+      return from_bf16(h2[r * HS + c]) > 0.f ? dz[r][0] * wr + dz[r][1] * wc : 0.f;
+    };
+    {
+      const int c = tid & 63, ra = 8 * wave;
+      const float wr = from_bf16(wb[MLP_WB_W3 + c]), wc = from_bf16(wb[MLP_WB_W3 + MLP_NH + c]);
+      uint16_t t[8];
+#pragma unroll
+      for (int j = 0; j < 8; j++) {
+        t[j] = to_bf16(dh2_of(ra + j, c, wr, wc));
+        dh2[(ra + j) * HS + c] = t[j];
+      }
+      __builtin_memcpy(&dh2T[c * TS + ra], t, 16);
+      if (wave == 3) {
+#pragma unroll 8
+        for (int r = 0; r < TR; r++) gs = gs + dh2_of(r, c, wr, wc);
+      }
+    }
+    if (tid < MLP_NOUT * MLP_NH) {
+      const int o = tid / MLP_NH, c = tid % MLP_NH;
+#pragma unroll 8
+      for (int r = 0; r < TR; r++) gs = gs + dz[r][o] * from_bf16(h2[r * HS + c]);
+    } else if (tid < MLP_NOUT * MLP_NH + MLP_NOUT) {
+      for (int r = 0; r < TR; r++) gs = gs + dz[r][tid - MLP_NOUT * MLP_NH];
+    } else if (tid == MLP_NOUT * MLP_NH + MLP_NOUT) {
+      for (int r = 0; r < TR; r++) gs = gs + ls[r];
+    }
+    __syncthreads();
+    // dh1 = dh2 W2 * [h1 > 0]: 8 tiles, two per wave
+#pragma unroll
+    for (int j = 0; j < 2; j++) {
+      const int u = wave * 16 + lm;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kt = 0; kt < 2; kt++)
+        acc = mfma(load8(dh2 + (j * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2T + u * MLP_NH + kt * 32 + lk), acc);
+#pragma unroll
+      for (int i = 0; i < 4; i++) {
+        const int r = j * 16 + lq + i;
+        const float d = from_bf16(h1[r * HS + u]) > 0.f ? acc[i] : 0.f;
+        dh1[r * (MLP_NH + 1) + u] = d;
+        dh1T[u * TS + r] = to_bf16(d);
+      }
+    }
+    __syncthreads();
+    // dW2 += dh2^T h1 (16 tiles), dW1 += dh1^T X (32 tiles), K = 32 rows; b1
+#pragma unroll
+    for (int j = 0; j < 4; j++)
+      g2[j] = mfma(load8(dh2T + (j * 16 + lm) * TS + lk), load8(h1T + (wave * 16 + lm) * TS + lk), g2[j]);
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+      g1[j] = mfma(load8(dh1T + ((j >> 1) * 16 + lm) * TS + lk), load8(xT + ((2 * wave + (j & 1)) * 16 + lm) * TS + lk), g1[j]);
+    if (wave == 3) {
+#pragma unroll 8
+      for (int r = 0; r < TR; r++) gb1 = gb1 + dh1[r * (MLP_NH + 1) + l];
+    }
+    __syncthreads();
   }
-  if (tid < MLP_NH) {
-    float g = 0.f;
-    for (int r = 0; r < B; r++) g = g + s.dh1[(size_t)r * MLP_NH + tid];
-    s.grad[MLP_B1 + tid] = g;
+  float* p = part + (size_t)blockIdx.x * MLP_PART;
+#pragma unroll
+  for (int j = 0; j < 4; j++)
+#pragma unroll
+    for (int i = 0; i < 4; i++) p[MLP_W2 + (j * 16 + lq + i) * MLP_NH + wave * 16 + lm] = g2[j][i];
+#pragma unroll
+  for (int j = 0; j < 8; j++)
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      p[MLP_W1 + ((j >> 1) * 16 + lq + i) * MLP_NIN + (2 * wave + (j & 1)) * 16 + lm] = g1[j][i];
+  if (tid < MLP_NOUT * MLP_NH + MLP_NOUT + 1) p[MLP_W3 + tid] = gs;  // W3, b3, then the loss sum at NPARAM
+  if (wave == 3) {
+    p[MLP_B2 + l] = gs;
+    p[MLP_B1 + l] = gb1;
   }
-  __threadfence_block();
-  __syncthreads();
+}
 
-  // P6: Adam (binary32 master weights), then fresh bfloat16 copies
-  const int t = *s.tstep + 1;
-  const float c1 = (float)(1.0 - pow((double)hp.beta1, (double)t));
-  const float c2 = (float)(1.0 - pow((double)hp.beta2, (double)t));
-  for (int i = tid; i < MLP_NPARAM; i += 256) {
-    const float gr = s.grad[i];
-    const float m = hp.beta1 * am[i] + (1.f - hp.beta1) * gr;
-    const float v = hp.beta2 * av[i] + (1.f - hp.beta2) * gr * gr;
-    am[i] = m;
-    av[i] = v;
-    w[i] = w[i] - hp.lr * (m / c1) / (sqrtf(v / c2) + hp.eps);
+// one parameter per thread: the partial gradients added in workgroup order,
+// Adam on the binary32 master weight, and its bfloat16 operand copies; the
+// thread past the last parameter writes the batch's mean loss
+__global__ void __launch_bounds__(256) k_mlp_step(const float* __restrict__ part, int nparts, int nvalid,
+                                                  float* __restrict__ w, float* __restrict__ am, float* __restrict__ av,
+                                                  uint16_t* __restrict__ wb, TrainHyper hp, float c1, float c2,
+                                                  float* __restrict__ loss_out, float* __restrict__ grad_out) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i > MLP_NPARAM) return;
+  float gr = 0.f;
+  int k = 0;
+  for (; k + 8 <= nparts; k += 8) {
+    float t[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) t[j] = part[(size_t)(k + j) * MLP_PART + i];
+#pragma unroll
+    for (int j = 0; j < 8; j++) gr = gr + t[j];
   }
-  __threadfence_block();
-  __syncthreads();
-  for (int i = tid; i < MLP_NH * MLP_NIN; i += 256) s.wb[MLP_WB_W1 + i] = to_bf16(w[MLP_W1 + i]);
-  for (int i = tid; i < MLP_NH * MLP_NH; i += 256) {
-    const uint16_t b = to_bf16(w[MLP_W2 + i]);
-    s.wb[MLP_WB_W2 + i] = b;
-    s.wb[MLP_WB_W2T + (i % MLP_NH) * MLP_NH + i / MLP_NH] = b;
+  for (; k < nparts; k++) gr = gr + part[(size_t)k * MLP_PART + i];
+  if (i == MLP_NPARAM) {
+    if (loss_out) *loss_out = gr / (float)nvalid;
+    return;
   }
-  if (tid < MLP_NOUT * MLP_NH) s.wb[MLP_WB_W3 + tid] = to_bf16(w[MLP_W3 + tid]);
-  if (tid == 0) *s.tstep = t;
+  if (grad_out) grad_out[i] = gr;
+  const float m = hp.beta1 * am[i] + (1.f - hp.beta1) * gr;
+  const float v = hp.beta2 * av[i] + (1.f - hp.beta2) * gr * gr;
+  am[i] = m;
+  av[i] = v;
+  const float wn = w[i] - hp.lr * (m / c1) / (sqrtf(v / c2) + hp.eps);
+  w[i] = wn;
+  const uint16_t b = to_bf16(wn);
+  if (i < MLP_B1) {
+    wb[MLP_WB_W1 + i] = b;
+  } else if (i >= MLP_W2 && i < MLP_B2) {
+    const int q = i - MLP_W2;
+    wb[MLP_WB_W2 + q] = b;
+    wb[MLP_WB_W2T + (q % MLP_NH) * MLP_NH + q / MLP_NH] = b;
+  } else if (i >= MLP_W3 && i < MLP_B3) {
+    wb[MLP_WB_W3 + i - MLP_W3] = b;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -488,48 +521,21 @@ hipError_t launch_mlp_infer(const uint16_t* X, int n, const uint16_t* wb, const 
 
 size_t mlp_train_scratch_bytes(int B) { return mlp_train_scratch_bytes_c(B); }
 
-static TrainScratch carve(char* ws, int B) {
-  TrainScratch s;
-  size_t o = 0;
-  auto take = [&](size_t b) {
-    char* p = ws + o;
-    o += (b + 255) / 256 * 256;
-    return p;
-  };
-  s.xg = (uint16_t*)take(2 * (size_t)B * MLP_NIN);
-  s.xgT = (uint16_t*)take(2 * (size_t)B * MLP_NIN);
-  s.h1 = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.h1T = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.h2 = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.dh2 = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.dh2T = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.dh1T = (uint16_t*)take(2 * (size_t)B * MLP_NH);
-  s.dh1 = (float*)take(4 * (size_t)B * MLP_NH);
-  s.z = (float*)take(4 * (size_t)MLP_NOUT * B);
-  s.dz = (float*)take(4 * (size_t)MLP_NOUT * B);
-  s.grad = (float*)take(4 * (size_t)MLP_NPARAM);
-  s.loss = (float*)take(4 * (size_t)B);
-  s.wb = (uint16_t*)take(2 * (size_t)MLP_WB_COUNT);
-  s.tstep = (int*)take(16);
-  return s;
-}
-
-__global__ void k_set_int(int* p, int v) {
-  if (threadIdx.x == 0) *p = v;
-}
-
 hipError_t launch_mlp_train(const uint16_t* X, const float* Y, const int32_t* order, int n, int B, int first_batch,
                             int nbatch, float* w, float* am, float* av, const TrainHyper& hp, int t0, void* ws,
                             float* loss_out, float* grad_out, hipStream_t st) {
-  TrainScratch s = carve((char*)ws, B);
-  hipLaunchKernelGGL(k_set_int, dim3(1), dim3(64), 0, st, s.tstep, t0);
-  hipLaunchKernelGGL(k_mlp_prep, dim3(16), dim3(256), 0, st, w, s.wb);
-  for (int b = 0; b < nbatch; b++)
-    hipLaunchKernelGGL(k_mlp_train, dim3(1), dim3(256), 0, st, X, Y, order, n, B, first_batch + b, w, am, av, hp, s,
-                       loss_out);
-  if (grad_out) {
-    hipError_t e = hipMemcpyAsync(grad_out, s.grad, sizeof(float) * MLP_NPARAM, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return e;
+  const int rows = mlp_train_rows(B), nparts = (B + rows - 1) / rows;
+  uint16_t* wb = (uint16_t*)ws;
+  float* part = (float*)((char*)ws + mlp_align256(2 * (size_t)MLP_WB_COUNT));
+  hipLaunchKernelGGL(k_mlp_prep, dim3(16), dim3(256), 0, st, w, wb);
+  for (int b = first_batch; b < first_batch + nbatch; b++) {
+    const int t = t0 + (b - first_batch) + 1;
+    const float c1 = (float)(1.0 - pow((double)hp.beta1, (double)t));
+    const float c2 = (float)(1.0 - pow((double)hp.beta2, (double)t));
+    const int nvalid = n - b * B < B ? n - b * B : B;
+    hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(256), 0, st, X, Y, order, n, B, b, rows, w, wb, hp, part);
+    hipLaunchKernelGGL(k_mlp_step, dim3(MLP_NPARAM / 256 + 1), dim3(256), 0, st, part, nparts, nvalid, w, am, av, wb, hp,
+                       c1, c2, loss_out ? loss_out + b : nullptr, b + 1 == first_batch + nbatch ? grad_out : nullptr);
   }
   return hipGetLastError();
 }

@@ -38,15 +38,12 @@ hipError_t launch_mlp_infer(const uint16_t* X, int n, const uint16_t* wb, const 
                             hipStream_t st);
 // device scratch of one training call with batch B (256-byte aligned pieces)
 constexpr size_t mlp_align256(size_t b) { return (b + 255) / 256 * 256; }
+// floats of one workgroup's partial gradient and loss sum (a 256-byte multiple)
+constexpr int MLP_PART = (int)(mlp_align256(4 * (size_t)(MLP_NPARAM + 1)) / 4);
+constexpr int mlp_train_parts_c(int B) { return B <= 2048 ? (B + 31) / 32 : (B + 63) / 64; }
 constexpr size_t mlp_train_scratch_bytes_c(int B) {
-  return 2 * mlp_align256(2 * (size_t)B * MLP_NIN)       // xg, xgT
-         + 6 * mlp_align256(2 * (size_t)B * MLP_NH)      // h1 h1T h2 dh2 dh2T dh1T
-         + mlp_align256(4 * (size_t)B * MLP_NH)          // dh1
-         + 2 * mlp_align256(4 * (size_t)MLP_NOUT * B)    // z, dz [B][2]
-         + mlp_align256(4 * (size_t)B)                   // loss
-         + mlp_align256(4 * (size_t)MLP_NPARAM)          // grad
-         + mlp_align256(2 * (size_t)MLP_WB_COUNT)        // wb
-         + mlp_align256(16);                             // step counter
+  return mlp_align256(2 * (size_t)MLP_WB_COUNT)                  // bfloat16 operand copies
+         + 4 * (size_t)MLP_PART * (size_t)mlp_train_parts_c(B);  // partial gradients
 }
 size_t mlp_train_scratch_bytes(int B);
 // the library-held scratch of amrv_mlp_train_noalloc: the largest batch
