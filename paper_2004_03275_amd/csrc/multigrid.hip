@@ -33,6 +33,7 @@
 #include <cmath>
 #include <cstring>
 #include <string>
+#include <type_traits>
 
 #include "../../include/amrv_mg.h"
 #include "errors.hpp"
@@ -43,8 +44,14 @@ namespace {
 constexpr int MG_MAXL = 14;   // n <= 8192: 13 levels down to 2 cells per side
 constexpr int NFMAX = 2;
 constexpr int TAIL_CELLS = 4096;
-constexpr int TAIL_THREADS = 1024;
-constexpr int TK = TAIL_CELLS / 2 / TAIL_THREADS;  // colour cells per tail thread on its top level
+constexpr int TAIL_THREADS = 1024;  // the variable-coefficient tail
+// threads of the tail: in 3D 512, whose 256 registers hold a restriction's reads
+// (1,024 threads spilled, and the first touch of scratch memory cost 3 us)
+template <int ND>
+constexpr int tail_threads() {
+  return ND == 3 ? 512 : 1024;
+}
+constexpr int COARSE_CELLS = 64;  // the tail's levels of at most this many cells: one matrix product
 constexpr int PAR_LAM = 0;
 constexpr int PAR_IDIAG = NFMAX;                       // + field * MG_MAXL + level
 constexpr int PAR_IH2 = NFMAX + NFMAX * MG_MAXL;       // + level
@@ -55,14 +62,14 @@ struct MgDev {
   int n[MG_MAXL];
   int lg[MG_MAXL];              // log2(n[l])
   int cells[MG_MAXL];
-  int loff[MG_MAXL];            // LDS offset (doubles) of the tail's phi_l; f_l follows it
-  int loffv[MG_MAXL];           // the same with a coefficient: phi_l, f_l, eps_l
+  int loffv[MG_MAXL];           // LDS offset (doubles) of the variable-coefficient tail's phi_l, f_l, eps_l
   const double* eps[MG_MAXL];   // cell coefficient per level (variable-coefficient solves)
   double* phi[NFMAX][MG_MAXL];
   double* f[NFMAX][MG_MAXL];
   double* phi2[NFMAX][MG_MAXL]; // 2D levels above the tail: the tiled launches'
                                 // second buffer (down writes it, up reads it)
   const double* par;
+  double* cmat;               // [field][64 columns][64 cells]: the coarse matrix
   unsigned long long* hpart;  // pinned host slots of per-block maxima: [2][NFMAX][maxb]
   int maxb;
 };
@@ -604,71 +611,297 @@ __global__ void __launch_bounds__(256) k_mg_up2d(MgDev g, int l, int post, int n
 // ---- the coarse tail: every level from `top` down, one workgroup per field,
 // all levels in LDS -------------------------------------------------------
 
-template <int ND>
-__device__ void tail_sweeps(const MgDev& g, double* P, const double* F, int l, int sweeps, double ih2, double idg) {
-  const int n = g.n[l], lg = g.lg[l], half = g.cells[l] >> 1;
-  for (int s = 0; s < sweeps; s++)
-    for (int c = 0; c < 2; c++) {
-      // TK cells per thread per pass: every new value before any store
-      for (int t0 = threadIdx.x; t0 < half; t0 += TK * blockDim.x) {
-        double nv[TK];
-        int idx[TK];
-#pragma unroll
-        for (int k = 0; k < TK; k++) {
-          const int t = t0 + k * blockDim.x;
-          idx[k] = -1;
-          if (t < half) {
-            int x, y, z;
-            colour_cell<ND>(t, n, lg, c, x, y, z);
-            const int row = (z * n + y) * n;
-            double sum = (P[row + im(x, n, g.bc)] + P[row + ip(x, n, g.bc)]) +
-                         (P[(z * n + im(y, n, g.bc)) * n + x] + P[(z * n + ip(y, n, g.bc)) * n + x]);
-            if constexpr (ND == 3)
-              sum = sum + (P[(im(z, n, g.bc) * n + y) * n + x] + P[(ip(z, n, g.bc) * n + y) * n + x]);
-            idx[k] = row + x;
-            nv[k] = (sum * ih2 - F[row + x]) * idg;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < TK; k++)
-          if (idx[k] >= 0) P[idx[k]] = nv[k];
-      }
-      __syncthreads();
-    }
-}
-
 // exact solve on the coarsest grid (2 cells per side): per direction the
 // operator couples the two cells as c [[-1, 1], [1, -1]] (c = 1/h^2 with the
 // mirrored Neumann ghost, 2/h^2 with the periodic wrap), so the 2^d Walsh
 // patterns (-1)^popcount(k & cell) are its eigenvectors, with eigenvalue
 // -2c per set bit of k, minus lambda.  For lambda = 0 the constant pattern
 // has eigenvalue 0 and the correction gets no constant part.
+// One wave: lane k forms the coefficient of pattern k, then cell k's sum.
 template <int ND>
-__device__ void coarse_exact(const MgDev& g, double* P, const double* F, double ih2, double lam) {
+__device__ __forceinline__ void coarse_exact(double* P, const double* F, int bc, double ih2, double lam) {
   constexpr int C = 1 << ND;
-  if (threadIdx.x == 0) {
-    const double c2 = 2.0 * (g.bc == AMRV_MG_PERIODIC ? 2.0 : 1.0) * ih2;
-    double hat[C];
+  const int k = threadIdx.x & (C - 1);
+  const double c2 = 2.0 * (bc == AMRV_MG_PERIODIC ? 2.0 : 1.0) * ih2;
+  double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < C; k++) {
-      double s = 0.0;
+  for (int c = 0; c < C; c++) s += (__popc(k & c) & 1) ? -F[c] : F[c];
+  double mu = -lam;
 #pragma unroll
-      for (int c = 0; c < C; c++) s += (__popc(k & c) & 1) ? -F[c] : F[c];
-      double mu = -lam;
+  for (int d = 0; d < ND; d++)
+    if ((k >> d) & 1) mu -= c2;
+  const double hat = mu == 0.0 ? 0.0 : s / (mu * C);
+  double v = 0.0;
 #pragma unroll
-      for (int d = 0; d < ND; d++)
-        if ((k >> d) & 1) mu -= c2;
-      hat[k] = mu == 0.0 ? 0.0 : s / (mu * C);
-    }
+  for (int q = 0; q < C; q++) {
+    const double h = __shfl(hat, q, 64);
+    v += (__popc(q & k) & 1) ? -h : h;
+  }
+  if (threadIdx.x < C) P[k] = v;
+}
+
+// A tail level in LDS holds its two colours in two halves (the cells of one
+// colour are then consecutive: two doubles apart, as in the natural order, they
+// meet two-way bank conflicts).  The cells 2 xh, 2 xh + 1 of a row are a pair,
+// p = row * n / 2 + xh; each half holds one cell of the pair at p, so both
+// colours of a pair share their addresses up to the half.
+template <int ND>
+__device__ __forceinline__ int tail_idx(int x, int y, int z, int lg) {
+  const int i = ND == 3 ? (((z << lg) + y) << lg) + x : (y << lg) + x;
+  return (i >> 1) + (((x + y + z) & 1) << (ND * lg - 1));
+}
+
+// LDS indices of a thread's pairs and right-hand sides, formed once per level
+// and kept in registers over its sweeps, so that a cell update is its
+// neighbour reads, six operations and a store
+template <int ND, int K>
+struct TailPairs {
+  bool ok[K];
+  int p[K];
+  int nb[2][K][2 * ND - 1];  // per colour: the outer x neighbour, then -y, +y, -z, +z (the inner x neighbour is p)
+  double f[2][K];
+};
+
+template <int ND, int K>
+__device__ __forceinline__ TailPairs<ND, K> tail_pairs(const double* F, int lg, int bc, int t0) {
+  constexpr int NT = tail_threads<ND>();
+  const int n = 1 << lg, nh = n >> 1, half = 1 << (ND * lg - 1);
+  const bool per = bc == AMRV_MG_PERIODIC;
+  TailPairs<ND, K> T;
 #pragma unroll
-    for (int c = 0; c < C; c++) {
-      double s = 0.0;
-#pragma unroll
-      for (int k = 0; k < C; k++) s += (__popc(k & c) & 1) ? -hat[k] : hat[k];
-      P[c] = s;
+  for (int k = 0; k < K; k++) {
+    T.ok[k] = t0 + k * NT < half;
+    const int p = T.ok[k] ? t0 + k * NT : 0;
+    const int xh = p & (nh - 1), r = p >> (lg - 1), y = ND == 3 ? r & (n - 1) : r, z = ND == 3 ? r >> lg : 0;
+    T.p[k] = p;
+    T.f[0][k] = F[p];
+    T.f[1][k] = F[half + p];
+    // index of a neighbour for colour 0 and colour 1: in the other half, or (a
+    // Neumann wall) the cell itself
+    auto both = [&](bool edge, int in, int wrap, int& a0, int& a1) {
+      const bool wall = edge && !per;
+      const int q = wall ? p : (edge ? wrap : in);
+      a0 = wall ? q : q + half;
+      a1 = wall ? q + half : q;
+    };
+    int l0, l1, r0, r1;
+    both(xh == 0, p - 1, p + nh - 1, l0, l1);
+    both(xh == nh - 1, p + 1, p - nh + 1, r0, r1);
+    const bool right = (y + z) & 1;  // the cell of colour 0 is the pair's right one
+    T.nb[0][k][0] = right ? r0 : l0;
+    T.nb[1][k][0] = right ? l1 : r1;
+    both(y == 0, p - nh, p + ((n - 1) << (lg - 1)), T.nb[0][k][1], T.nb[1][k][1]);
+    both(y == n - 1, p + nh, p - ((n - 1) << (lg - 1)), T.nb[0][k][2], T.nb[1][k][2]);
+    if constexpr (ND == 3) {
+      const int zs = 1 << (2 * lg - 1);
+      both(z == 0, p - zs, p + half - zs, T.nb[0][k][3], T.nb[1][k][3]);
+      both(z == n - 1, p + zs, p - half + zs, T.nb[0][k][4], T.nb[1][k][4]);
     }
   }
-  __syncthreads();
+  return T;
+}
+
+// `sweeps` red-black sweeps on a level, without the first half-sweep when the
+// level's values already include it
+template <int ND, int K>
+__device__ __forceinline__ void tail_sweeps(const TailPairs<ND, K>& T, double* P, int half, int sweeps,
+                                            bool first_done, double ih2, double idg) {
+  auto half_sweep = [&](auto colour) {
+    constexpr int c = decltype(colour)::value;
+    double* own = P + (c ? half : 0);
+    const double* other = P + (c ? 0 : half);
+    double nv[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      const int* b = T.nb[c][k];
+      double sum = (other[T.p[k]] + P[b[0]]) + (P[b[1]] + P[b[2]]);
+      if constexpr (ND == 3) sum = sum + (P[b[3]] + P[b[4]]);
+      nv[k] = (sum * ih2 - T.f[c][k]) * idg;
+    }
+    // a half-sweep reads the other colour (and a wall cell its own value): no
+    // barrier before the stores
+#pragma unroll
+    for (int k = 0; k < K; k++)
+      if (T.ok[k]) own[T.p[k]] = nv[k];
+    __syncthreads();
+  };
+  for (int s = 0; s < sweeps; s++) {
+    if (s || !first_done) half_sweep(std::integral_constant<int, 0>{});
+    half_sweep(std::integral_constant<int, 1>{});
+  }
+}
+
+// the coarse right-hand side (the children's mean residual, restrict_cell's
+// arithmetic with each value read once) and, for the zero initial guess, the
+// coarse level after its first half-sweep: colour 0 at -f / diag, colour 1 at
+// 0; the matrix level (SPLIT false, natural order) takes the right-hand side only
+template <int ND, bool SPLIT>
+__device__ __forceinline__ void tail_restrict(const double* P, const double* F, double* Pc, double* Fc, int t, int lg,
+                                              int bc, double ih2, double lam, double idgc) {
+  int xc, yc, zc;
+  const int n = 1 << lg, nc = n >> 1, half = 1 << (ND * lg - 1), lgc = lg - 1;
+  const bool per = bc == AMRV_MG_PERIODIC;
+  decode<ND>(t, nc, lgc, xc, yc, zc);
+  constexpr int NZ = ND == 3 ? 2 : 1;
+  const int zs = 1 << (2 * lg - 1);  // pairs of a plane
+  const int p00 = ND == 3 ? (((2 * zc << lg) + 2 * yc) << lgc) + xc : (2 * yc << lgc) + xc;
+  double w[NZ][2][2];
+#pragma unroll
+  for (int dz = 0; dz < NZ; dz++)
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++)
+#pragma unroll
+      for (int dx = 0; dx < 2; dx++) w[dz][dy][dx] = P[p00 + dy * nc + dz * zs + (((dx + dy + dz) & 1) ? half : 0)];
+  double s = 0.0;
+#pragma unroll
+  for (int dz = 0; dz < NZ; dz++) {
+    // the neighbours outside the 2^d children: the other colour, or (a Neumann
+    // wall) the cell itself
+    double fv[2][2], ex[2][2], ey[2][2], ez[2][2];
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++)
+#pragma unroll
+      for (int dx = 0; dx < 2; dx++) {
+        const int p = p00 + dy * nc + dz * zs, oo = ((dx + dy + dz) & 1) ? 0 : half;  // other half
+        const int os = half - oo;                                                     // own half
+        auto out = [&](bool edge, int in, int wrap) { return P[!edge ? oo + in : (per ? oo + wrap : os + p)]; };
+        fv[dy][dx] = F[os + p];
+        ex[dy][dx] = dx ? out(xc == nc - 1, p + 1, p - nc + 1) : out(xc == 0, p - 1, p + nc - 1);
+        ey[dy][dx] = dy ? out(yc == nc - 1, p + nc, p - ((n - 1) << lgc)) : out(yc == 0, p - nc, p + ((n - 1) << lgc));
+        if constexpr (ND == 3)
+          ez[dy][dx] = dz ? out(zc == nc - 1, p + zs, p - half + zs) : out(zc == 0, p - zs, p + half - zs);
+      }
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++)
+#pragma unroll
+      for (int dx = 0; dx < 2; dx++) {
+        const double v = w[dz][dy][dx];
+        double lap = ((ex[dy][dx] + w[dz][dy][1 - dx]) - 2.0 * v) * ih2;
+        lap = lap + ((ey[dy][dx] + w[dz][1 - dy][dx]) - 2.0 * v) * ih2;
+        if constexpr (ND == 3) lap = lap + ((ez[dy][dx] + w[NZ - 1 - dz][dy][dx]) - 2.0 * v) * ih2;
+        s += fv[dy][dx] - (lap - lam * v);
+      }
+    }
+  const double fc = s * (ND == 3 ? 0.125 : 0.25);
+  if constexpr (SPLIT) {
+    const int i = tail_idx<ND>(xc, yc, zc, lgc);
+    Fc[i] = fc;
+    Pc[i] = ((xc + yc + zc) & 1) ? 0.0 : (0.0 - fc) * idgc;
+  } else {
+    Fc[t] = fc;
+  }
+}
+
+// the interpolated correction (prolong_cell's weights and order) where the
+// half-sweep of colour 0 that follows reads it: every cell of colour 1 and, with
+// Neumann walls (a cell at one sums its own old value), both cells of every
+// pair, which share their coarse rows; the others of colour 0 are recomputed
+// without their old values
+template <int ND, int K, bool SPLIT>
+__device__ __forceinline__ void tail_prolong(double* P, const double* Pc, int t0, int lg, int bc) {
+  constexpr int NT = tail_threads<ND>();
+  const int n = 1 << lg, half = 1 << (ND * lg - 1), lgc = lg - 1, nc = n >> 1;
+  const bool both = bc != AMRV_MG_PERIODIC;
+#pragma unroll
+  for (int k = 0; k < K; k++) {
+    const int p = t0 + k * NT;
+    if (p >= half) continue;
+    const int xc = p & (nc - 1), r = p >> lgc, y = ND == 3 ? r & (n - 1) : r, z = ND == 3 ? r >> lg : 0;
+    const bool odd = (y + z) & 1;  // the cell of colour 1 is the pair's left one
+    const int xl = im(xc, nc, bc), xr = ip(xc, nc, bc);
+    const int xa = odd ? xl : xr, xb = odd ? xr : xl;  // toward the cell of colour 1, of colour 0
+    auto row = [&](int yy, int zz, double& a, double& b) {
+      const int base = ND == 3 ? ((zz << lgc) + yy) << lgc : yy << lgc;
+      const int s = (yy + zz) & 1;
+      auto e = [&](int x) {
+        if constexpr (SPLIT) return Pc[((base + x) >> 1) + (((x + s) & 1) << (ND * lgc - 1))];
+        return Pc[base + x];
+      };
+      const double c = 0.75 * e(xc);
+      a = c + 0.25 * e(xa);
+      b = both ? c + 0.25 * e(xb) : 0.0;
+    };
+    const int yc = y >> 1, yn = (y & 1) ? ip(yc, nc, bc) : im(yc, nc, bc);
+    auto plane = [&](int zz, double& a, double& b) {
+      double a0, b0, a1, b1;
+      row(yc, zz, a0, b0);
+      row(yn, zz, a1, b1);
+      a = 0.75 * a0 + 0.25 * a1;
+      b = 0.75 * b0 + 0.25 * b1;
+    };
+    double d1, d0;
+    if constexpr (ND == 2) {
+      plane(0, d1, d0);
+    } else {
+      const int zc = z >> 1, zn = (z & 1) ? ip(zc, nc, bc) : im(zc, nc, bc);
+      double a0, b0, a1, b1;
+      plane(zc, a0, b0);
+      plane(zn, a1, b1);
+      d1 = 0.75 * a0 + 0.25 * a1;
+      d0 = 0.75 * b0 + 0.25 * b1;
+    }
+    P[half + p] += d1;
+    if (both) P[p] += d0;
+  }
+}
+
+// a V-cycle on a grid of at most 64 cells by one wave (phi at P, f after it, the
+// levels below after that, natural order in LDS): the coarse matrix's columns and grids with
+// no larger level
+template <int ND>
+__device__ void wave_cycle(double* P, int lg0, int lev0, const MgDev& g, int f, int bc, int pre, int post,
+                           double lam) {
+  const int l = threadIdx.x;
+  auto sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto level = [&](double* base, int lg) {  // start of level lg: 2 cells doubles per level above it
+    for (int q = lg0; q > lg; q--) base += 2 << (ND * q);
+    return base;
+  };
+  auto sweeps = [&](double* p, const double* r, int lg, int lev, int count) {
+    const int n = 1 << lg, half = 1 << (ND * lg - 1);
+    const double ih2 = par_ih2(g, lev), idg = par_idiag(g, f, lev);
+    for (int s = 0; s < 2 * count; s++) {
+      if (l < half) {
+        int x, y, z;
+        colour_cell<ND>(l, n, lg, s & 1, x, y, z);
+        gs_cell<ND>(p, r, x, y, z, n, bc, ih2, idg);
+      }
+      sync();
+    }
+  };
+  for (int lg = lg0, lev = lev0; lg > 1; lg--, lev++) {
+    double* p = level(P, lg);
+    double* r = p + (1 << (ND * lg));
+    double* pc = level(P, lg - 1);
+    sweeps(p, r, lg, lev, pre);
+    if (l < (1 << (ND * (lg - 1)))) {
+      int x, y, z;
+      decode<ND>(l, 1 << (lg - 1), lg - 1, x, y, z);
+      pc[(1 << (ND * (lg - 1))) + l] = restrict_cell<ND>(p, r, x, y, z, 1 << lg, bc, par_ih2(g, lev), lam);
+      pc[l] = 0.0;
+    }
+    sync();
+  }
+  {
+    double* p = level(P, 1);
+    coarse_exact<ND>(p, p + (1 << ND), bc, par_ih2(g, lev0 + lg0 - 1), lam);
+    sync();
+  }
+  for (int lg = 2, lev = lev0 + lg0 - 2; lg <= lg0; lg++, lev--) {
+    double* p = level(P, lg);
+    double* r = p + (1 << (ND * lg));
+    const double* pc = level(P, lg - 1);
+    if (l < (1 << (ND * lg))) {
+      int x, y, z;
+      decode<ND>(l, 1 << lg, lg, x, y, z);
+      p[l] += prolong_cell<ND>(pc, x, y, z, 1 << (lg - 1), bc);
+    }
+    sync();
+    sweeps(p, r, lg, lev, post);
+  }
 }
 
 template <int ND>
@@ -723,49 +956,199 @@ __device__ void coarse_exact_var(const MgDev& g, double* P, const double* F, con
   __syncthreads();
 }
 
-template <int ND, bool VAR>
-__global__ void __launch_bounds__(TAIL_THREADS) k_mg_tail(MgDev g, int top, int pre, int post) {
+// The coarse matrix: a V-cycle from zero on the level of 64 cells (8^2 or 4^3)
+// and everything below is a fixed linear map of its right-hand side, 64 x 64
+// per field.  Column j (one wave each) is the cycle's answer to a unit
+// right-hand side at cell j; formed whenever the parameters (lambda) are set.
+// As a product it replaces the last two or three levels' ~25 dependent phases,
+// which kept one wave busy for 10 us of each cycle's tail.
+template <int ND>
+__global__ void __launch_bounds__(64) k_mg_coarse_matrix(MgDev g, int lev, int pre, int post) {
+  __shared__ double lds[2 * (64 + 16 + 8)];
+  const int j = blockIdx.x, f = blockIdx.y, l = threadIdx.x;
+  lds[l] = 0.0;
+  lds[64 + l] = l == j ? 1.0 : 0.0;
+  __syncthreads();
+  wave_cycle<ND>(lds, ND == 2 ? 3 : 2, lev, g, f, g.bc, pre, post, par_lam(g, f));
+  __syncthreads();
+  g.cmat[(size_t)f * 4096 + j * 64 + l] = lds[l];
+}
+
+// a grid of at most 64 cells: one V-cycle by one wave
+template <int ND>
+__global__ void __launch_bounds__(64) k_mg_small(MgDev g, int pre, int post) {
+  __shared__ double lds[2 * (64 + 16 + 8)];
+  const int f = blockIdx.x, l = threadIdx.x, C = g.cells[0];
+  if (l < C) {
+    lds[l] = g.phi[f][0][l];
+    lds[C + l] = g.f[f][0][l];
+  }
+  __syncthreads();
+  wave_cycle<ND>(lds, g.lg[0], 0, g, f, g.bc, pre, post, par_lam(g, f));
+  __syncthreads();
+  if (l < C) g.phi[f][0][l] = lds[l];
+}
+
+// Every level from `top` (more than 64 cells) down in one workgroup's LDS, from
+// the zero guess where finer levels exist (zero != 0: phi of `top` is not read).
+// One CU works through a chain of dependent phases, bound by the instructions
+// of each phase and its barrier, so the phases are few and short: pairs of
+// cells with precomputed indices, the half-sweep from zero folded into the
+// restriction, colour 0 not prolonged, and the levels of at most 64 cells one
+// product with the coarse matrix.  Two fields, Neumann: from 64^2 27.1 -> 15.3 us,
+// from 16^3 27.9 -> 17.1 us (one thread per cell and phase before).
+template <int ND>
+__global__ void __launch_bounds__(tail_threads<ND>()) k_mg_tail(MgDev g, int top, int pre, int post, int zero) {
+  constexpr int NT = tail_threads<ND>(), TK = TAIL_CELLS / 2 / NT;  // pairs of the top level per thread
   extern __shared__ double lds[];
   __shared__ double s_ih2[MG_MAXL], s_idg[MG_MAXL];
-  const int f = blockIdx.x;
-  if (threadIdx.x < MG_MAXL) {
-    s_ih2[threadIdx.x] = par_ih2(g, threadIdx.x);
-    s_idg[threadIdx.x] = par_idiag(g, f, threadIdx.x);
+  const int f = blockIdx.x, tid = threadIdx.x, bc = g.bc;
+  const int lg0 = g.lg[top], H0 = g.cells[top] >> 1;
+  constexpr int LGM = ND == 2 ? 3 : 2;  // the matrix level: 8^2 or 4^3
+  const int nl = lg0 - LGM;             // levels above it: 1..3 (2D), 1..2 (3D)
+  const double2* fg = reinterpret_cast<const double2*>(g.f[f][top]);
+  double2* pg = reinterpret_cast<double2*>(g.phi[f][top]);
+  double2 fv[TK], pv[TK];
+  constexpr int CG = NT / 64, CQ = 64 / CG;  // the matrix product: column groups, columns each
+  double cm[CQ];
+#pragma unroll
+  for (int k = 0; k < TK; k++) {
+    const int p = tid + k * NT;
+    fv[k] = p < H0 ? fg[p] : double2{0.0, 0.0};
+    pv[k] = !zero && p < H0 ? pg[p] : double2{0.0, 0.0};
   }
+  if (tid < MG_MAXL) {
+    s_ih2[tid] = par_ih2(g, tid);
+    s_idg[tid] = par_idiag(g, f, tid);
+  }
+  const double lam = par_lam(g, f), idg_top = par_idiag(g, f, top);
+  // this thread's part of the matrix product: cell tid % 64, columns CQ (tid / 64) .. + CQ - 1
+#pragma unroll
+  for (int q = 0; q < CQ; q++) cm[q] = g.cmat[(size_t)f * 4096 + (CQ * (tid >> 6) + q) * 64 + (tid & 63)];
+  // level i (0: top): phi, then f
+  auto P = [&](int i) {
+    double* b = lds;
+    for (int q = 0; q < i; q++) b += 4 * (H0 >> (ND * q));
+    return b;
+  };
+  auto F = [&](int i) { return P(i) + 2 * (H0 >> (ND * i)); };
+  auto colour_x = [&](int p) {  // colour of the pair's left cell
+    const int r = p >> (lg0 - 1);
+    return ND == 3 ? ((r & ((1 << lg0) - 1)) + (r >> lg0)) & 1 : r & 1;
+  };
+#pragma unroll
+  for (int k = 0; k < TK; k++) {
+    const int p = tid + k * NT;
+    if (p < H0) {
+      const bool s = colour_x(p);
+      const double f0 = s ? fv[k].y : fv[k].x, f1 = s ? fv[k].x : fv[k].y;
+      F(0)[p] = f0;
+      F(0)[H0 + p] = f1;
+      P(0)[p] = zero ? (0.0 - f0) * idg_top : (s ? pv[k].y : pv[k].x);
+      P(0)[H0 + p] = s ? pv[k].x : pv[k].y;
+    }
+  }
+  __syncthreads();
+  // the coarse right-hand side of level i into level i + 1 (the matrix level:
+  // natural order, right-hand side only)
+  auto restrict_to = [&](int i) {
+    const int cc = (2 * H0) >> (ND * (i + 1)), lg = lg0 - i;
+    if (i + 1 == nl) {
+      if (tid < 64) tail_restrict<ND, false>(P(i), F(i), nullptr, P(i + 1), tid, lg, bc, s_ih2[top + i], lam, 0.0);
+    } else {
+      for (int t = tid; t < cc; t += NT)
+        tail_restrict<ND, true>(P(i), F(i), P(i + 1), F(i + 1), t, lg, bc, s_ih2[top + i], lam, s_idg[top + i + 1]);
+    }
+    __syncthreads();
+  };
+  {
+    const TailPairs<ND, TK> T = tail_pairs<ND, TK>(F(0), lg0, bc, tid);
+    tail_sweeps<ND, TK>(T, P(0), H0, pre, zero, s_ih2[top], s_idg[top]);
+    restrict_to(0);
+  }
+  for (int i = 1; i < nl; i++) {
+    const TailPairs<ND, 1> T = tail_pairs<ND, 1>(F(i), lg0 - i, bc, tid);
+    tail_sweeps<ND, 1>(T, P(i), H0 >> (ND * i), pre, true, s_ih2[top + i], s_idg[top + i]);
+    restrict_to(i);
+  }
+  // the matrix level: right-hand side at P(nl), partial sums of the
+  // column groups after it, the answer over the right-hand side
+  {
+    double* c = P(nl);
+    double a = cm[0] * c[CQ * (tid >> 6)];
+#pragma unroll
+    for (int q = 1; q < CQ; q++) a = a + cm[q] * c[CQ * (tid >> 6) + q];
+    c[64 + tid] = a;
+    __syncthreads();
+    if (tid < 64) {
+      double v = c[64 + tid];
+#pragma unroll
+      for (int q = 1; q < CG; q++) v = v + c[64 + 64 * q + tid];
+      c[tid] = v;
+    }
+    __syncthreads();
+  }
+  for (int i = nl - 1; i > 0; i--) {
+    const int lg = lg0 - i;
+    if (i + 1 == nl)
+      tail_prolong<ND, 1, false>(P(i), P(i + 1), tid, lg, bc);
+    else
+      tail_prolong<ND, 1, true>(P(i), P(i + 1), tid, lg, bc);
+    __syncthreads();
+    const TailPairs<ND, 1> T = tail_pairs<ND, 1>(F(i), lg, bc, tid);
+    tail_sweeps<ND, 1>(T, P(i), H0 >> (ND * i), post, false, s_ih2[top + i], s_idg[top + i]);
+  }
+  {
+    if (nl == 1)
+      tail_prolong<ND, TK, false>(P(0), P(1), tid, lg0, bc);
+    else
+      tail_prolong<ND, TK, true>(P(0), P(1), tid, lg0, bc);
+    __syncthreads();
+    const TailPairs<ND, TK> T = tail_pairs<ND, TK>(F(0), lg0, bc, tid);
+    tail_sweeps<ND, TK>(T, P(0), H0, post, false, s_ih2[top], s_idg[top]);
+  }
+#pragma unroll
+  for (int k = 0; k < TK; k++) {
+    const int p = tid + k * NT;
+    if (p < H0) {
+      const bool s = colour_x(p);
+      const double a = P(0)[p], b = P(0)[H0 + p];
+      pg[p] = s ? double2{b, a} : double2{a, b};
+    }
+  }
+}
+
+// the same with a cell coefficient, every level on the whole workgroup
+template <int ND>
+__global__ void __launch_bounds__(TAIL_THREADS) k_mg_tail_var(MgDev g, int top, int pre, int post) {
+  extern __shared__ double lds[];
+  __shared__ double s_ih2[MG_MAXL];
+  const int f = blockIdx.x;
+  if (threadIdx.x < MG_MAXL) s_ih2[threadIdx.x] = par_ih2(g, threadIdx.x);
   const double lam = par_lam(g, f);
-  auto P = [&](int l) { return lds + (VAR ? g.loffv[l] : g.loff[l]); };
+  auto P = [&](int l) { return lds + g.loffv[l]; };
   auto F = [&](int l) { return P(l) + g.cells[l]; };
-  auto E = [&](int l) { return P(l) + 2 * g.cells[l]; };  // with a coefficient only
+  auto E = [&](int l) { return P(l) + 2 * g.cells[l]; };
   const int last = g.nlev - 1;
   for (int i = threadIdx.x; i < g.cells[top]; i += blockDim.x) {
     P(top)[i] = g.phi[f][top][i];
     F(top)[i] = g.f[f][top][i];
   }
-  if constexpr (VAR)
-    for (int l = top; l <= last; l++)
-      for (int i = threadIdx.x; i < g.cells[l]; i += blockDim.x) E(l)[i] = g.eps[l][i];
+  for (int l = top; l <= last; l++)
+    for (int i = threadIdx.x; i < g.cells[l]; i += blockDim.x) E(l)[i] = g.eps[l][i];
   __syncthreads();
   for (int l = top; l < last; l++) {
-    if constexpr (VAR)
-      tail_sweeps_var<ND>(g, P(l), F(l), E(l), l, pre, s_ih2[l], lam);
-    else
-      tail_sweeps<ND>(g, P(l), F(l), l, pre, s_ih2[l], s_idg[l]);
+    tail_sweeps_var<ND>(g, P(l), F(l), E(l), l, pre, s_ih2[l], lam);
     const double ih2 = s_ih2[l];
     for (int t = threadIdx.x; t < g.cells[l + 1]; t += blockDim.x) {
       int x, y, z;
       decode<ND>(t, g.n[l + 1], g.lg[l + 1], x, y, z);
-      if constexpr (VAR)
-        F(l + 1)[t] = restrict_cell_var<ND>(P(l), F(l), E(l), x, y, z, g.n[l], g.bc, ih2, lam);
-      else
-        F(l + 1)[t] = restrict_cell<ND>(P(l), F(l), x, y, z, g.n[l], g.bc, ih2, lam);
+      F(l + 1)[t] = restrict_cell_var<ND>(P(l), F(l), E(l), x, y, z, g.n[l], g.bc, ih2, lam);
       P(l + 1)[t] = 0.0;
     }
     __syncthreads();
   }
-  if constexpr (VAR)
-    coarse_exact_var<ND>(g, P(last), F(last), E(last), s_ih2[last], lam);
-  else
-    coarse_exact<ND>(g, P(last), F(last), s_ih2[last], lam);
+  coarse_exact_var<ND>(g, P(last), F(last), E(last), s_ih2[last], lam);
   for (int l = last - 1; l >= top; l--) {
     for (int t = threadIdx.x; t < g.cells[l]; t += blockDim.x) {
       int x, y, z;
@@ -773,10 +1156,7 @@ __global__ void __launch_bounds__(TAIL_THREADS) k_mg_tail(MgDev g, int top, int 
       P(l)[t] += prolong_cell<ND>(P(l + 1), x, y, z, g.n[l + 1], g.bc);
     }
     __syncthreads();
-    if constexpr (VAR)
-      tail_sweeps_var<ND>(g, P(l), F(l), E(l), l, post, s_ih2[l], lam);
-    else
-      tail_sweeps<ND>(g, P(l), F(l), l, post, s_ih2[l], s_idg[l]);
+    tail_sweeps_var<ND>(g, P(l), F(l), E(l), l, post, s_ih2[l], lam);
   }
   for (int i = threadIdx.x; i < g.cells[top]; i += blockDim.x) g.phi[f][top][i] = P(top)[i];
 }
@@ -992,7 +1372,7 @@ int validate(const amrv_mg_config* c) {
 struct MgLayout {
   int nlev = 0;
   size_t off_phi[NFMAX][MG_MAXL]{}, off_f[NFMAX][MG_MAXL]{}, off_phi2[NFMAX][MG_MAXL]{}, off_eps[MG_MAXL]{},
-      off_tmp[4]{}, off_par = 0, total = 0;
+      off_tmp[4]{}, off_par = 0, off_cmat = 0, total = 0;
 };
 
 MgLayout layout(const amrv_mg_config* c) {
@@ -1028,6 +1408,8 @@ MgLayout layout(const amrv_mg_config* c) {
   }
   L.off_par = o;
   o += up(PAR_COUNT * 8);
+  L.off_cmat = o;
+  o += up((size_t)c->nfields * COARSE_CELLS * COARSE_CELLS * 8);
   L.total = o;
   return L;
 }
@@ -1075,11 +1457,13 @@ void enqueue_vcycle_nd(amrv_mg* m) {
     }
   }
   if (m->var)
-    hipLaunchKernelGGL((k_mg_tail<ND, true>), dim3(nf), dim3(TAIL_THREADS), m->tail_lds_var, m->st, g, m->tail, pre,
+    hipLaunchKernelGGL((k_mg_tail_var<ND>), dim3(nf), dim3(TAIL_THREADS), m->tail_lds_var, m->st, g, m->tail, pre,
                        post);
+  else if (g.cells[0] <= COARSE_CELLS)
+    hipLaunchKernelGGL((k_mg_small<ND>), dim3(nf), dim3(64), 0, m->st, g, pre, post);
   else
-    hipLaunchKernelGGL((k_mg_tail<ND, false>), dim3(nf), dim3(TAIL_THREADS), m->tail_lds, m->st, g, m->tail, pre,
-                       post);
+    hipLaunchKernelGGL((k_mg_tail<ND>), dim3(nf), dim3(tail_threads<ND>()), m->tail_lds, m->st, g, m->tail, pre, post,
+                       m->tail > 0 ? 1 : 0);
   if (tiled(m)) {
     for (int l = m->tail - 1; l >= 0; l--)
       hipLaunchKernelGGL(k_mg_up2d, dim3((g.n[l] / TS) * (g.n[l] / TS), nf), dim3(256), 0, m->st, g, l, post,
@@ -1120,6 +1504,12 @@ int set_params(amrv_mg* m, const double* lam) {
       P.v[PAR_IDIAG + f * MG_MAXL + l] = 1.0 / (2.0 * m->g.nd * P.v[PAR_IH2 + l] + lam[f]);
   }
   hipLaunchKernelGGL(k_mg_set, dim3(1), dim3(64), 0, m->st, m->par, P);
+  if (m->g.cells[0] > COARSE_CELLS) {
+    int lev = 0;
+    while (m->g.cells[lev] > COARSE_CELLS) lev++;
+    hipLaunchKernelGGL(m->g.nd == 2 ? k_mg_coarse_matrix<2> : k_mg_coarse_matrix<3>, dim3(COARSE_CELLS, m->g.nf),
+                       dim3(64), 0, m->st, m->g, lev, m->cfg.pre_sweeps, m->cfg.post_sweeps);
+  }
   MGCHK(hipGetLastError());
   m->par_nf = m->g.nf;
   m->par_lam0 = lam[0];
@@ -1295,15 +1685,16 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
   }
   m->par = reinterpret_cast<double*>(base + L.off_par);
   g.par = m->par;
+  g.cmat = reinterpret_cast<double*>(base + L.off_cmat);
   // the tail: the first level of at most TAIL_CELLS cells, and every level below
   int tail = 0;
   while (g.cells[tail] > TAIL_CELLS) tail++;
   m->tail = tail;
   int off = 0;
   for (int l = tail; l < L.nlev; l++) {
-    g.loff[l] = off;
-    off += 2 * g.cells[l];
+    if (g.cells[l] > COARSE_CELLS) off += 2 * g.cells[l];
   }
+  off += COARSE_CELLS + TAIL_THREADS;  // the matrix level's right-hand side and partial sums
   m->tail_lds = (size_t)off * sizeof(double);
   int offv = 0;
   for (int l = tail; l < L.nlev; l++) {
@@ -1312,14 +1703,14 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
   }
   m->tail_lds_var = (size_t)offv * sizeof(double);
   hipError_t e = cfg->ndim == 2
-                     ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<2, false>),
+                     ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<2>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds)
-                     : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<3, false>),
+                     : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<3>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds);
   if (e == hipSuccess)
-    e = cfg->ndim == 2 ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<2, true>),
+    e = cfg->ndim == 2 ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail_var<2>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds_var)
-                       : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<3, true>),
+                       : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail_var<3>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds_var);
   m->nb_init = std::min(blocks_of(g.cells[0]), 256);
   m->nb_cycle = tiled(m) ? (g.n[0] / TS) * (g.n[0] / TS) : m->nb_init;
