@@ -69,7 +69,7 @@ struct MgDev {
   double* phi2[NFMAX][MG_MAXL]; // 2D levels above the tail: the tiled launches'
                                 // second buffer (down writes it, up reads it)
   const double* par;
-  double* cmat;               // [field][64 columns][64 cells]: the coarse matrix
+  double* cmat[NFMAX];        // [64 columns][64 cells]: the coarse matrix (null: grids below TAIL_CELLS)
   unsigned long long* hpart;  // pinned host slots of per-block maxima: [2][NFMAX][maxb]
   int maxb;
 };
@@ -958,7 +958,9 @@ __device__ void coarse_exact_var(const MgDev& g, double* P, const double* F, con
 
 // The coarse matrix: a V-cycle from zero on the level of 64 cells (8^2 or 4^3)
 // and everything below is a fixed linear map of its right-hand side, 64 x 64
-// per field.  Column j (one wave each) is the cycle's answer to a unit
+// per field (32 KiB, in the two temporaries that only the explicit midpoint
+// step uses: grids of fewer than 4,096 cells have no room for it there, and one
+// wave runs the cycle).  Column j (one wave each) is the cycle's answer to a unit
 // right-hand side at cell j; formed whenever the parameters (lambda) are set.
 // As a product it replaces the last two or three levels' ~25 dependent phases,
 // which kept one wave busy for 10 us of each cycle's tail.
@@ -971,7 +973,7 @@ __global__ void __launch_bounds__(64) k_mg_coarse_matrix(MgDev g, int lev, int p
   __syncthreads();
   wave_cycle<ND>(lds, ND == 2 ? 3 : 2, lev, g, f, g.bc, pre, post, par_lam(g, f));
   __syncthreads();
-  g.cmat[(size_t)f * 4096 + j * 64 + l] = lds[l];
+  g.cmat[f][j * 64 + l] = lds[l];
 }
 
 // a grid of at most 64 cells: one V-cycle by one wave
@@ -997,7 +999,7 @@ __global__ void __launch_bounds__(64) k_mg_small(MgDev g, int pre, int post) {
 // restriction, colour 0 not prolonged, and the levels of at most 64 cells one
 // product with the coarse matrix.  Two fields, Neumann: from 64^2 27.1 -> 15.3 us,
 // from 16^3 27.9 -> 17.1 us (one thread per cell and phase before).
-template <int ND>
+template <int ND, bool MAT>
 __global__ void __launch_bounds__(tail_threads<ND>()) k_mg_tail(MgDev g, int top, int pre, int post, int zero) {
   constexpr int NT = tail_threads<ND>(), TK = TAIL_CELLS / 2 / NT;  // pairs of the top level per thread
   extern __shared__ double lds[];
@@ -1024,7 +1026,7 @@ __global__ void __launch_bounds__(tail_threads<ND>()) k_mg_tail(MgDev g, int top
   const double lam = par_lam(g, f), idg_top = par_idiag(g, f, top);
   // this thread's part of the matrix product: cell tid % 64, columns CQ (tid / 64) .. + CQ - 1
 #pragma unroll
-  for (int q = 0; q < CQ; q++) cm[q] = g.cmat[(size_t)f * 4096 + (CQ * (tid >> 6) + q) * 64 + (tid & 63)];
+  for (int q = 0; q < CQ; q++) cm[q] = MAT ? g.cmat[f][(CQ * (tid >> 6) + q) * 64 + (tid & 63)] : 0.0;
   // level i (0: top): phi, then f
   auto P = [&](int i) {
     double* b = lds;
@@ -1050,11 +1052,11 @@ __global__ void __launch_bounds__(tail_threads<ND>()) k_mg_tail(MgDev g, int top
   }
   __syncthreads();
   // the coarse right-hand side of level i into level i + 1 (the matrix level:
-  // natural order, right-hand side only)
+  // natural order, right-hand side only, after phi where one wave cycles on it)
   auto restrict_to = [&](int i) {
     const int cc = (2 * H0) >> (ND * (i + 1)), lg = lg0 - i;
     if (i + 1 == nl) {
-      if (tid < 64) tail_restrict<ND, false>(P(i), F(i), nullptr, P(i + 1), tid, lg, bc, s_ih2[top + i], lam, 0.0);
+      if (tid < 64) tail_restrict<ND, false>(P(i), F(i), nullptr, P(i + 1) + (MAT ? 0 : 64), tid, lg, bc, s_ih2[top + i], lam, 0.0);
     } else {
       for (int t = tid; t < cc; t += NT)
         tail_restrict<ND, true>(P(i), F(i), P(i + 1), F(i + 1), t, lg, bc, s_ih2[top + i], lam, s_idg[top + i + 1]);
@@ -1073,7 +1075,14 @@ __global__ void __launch_bounds__(tail_threads<ND>()) k_mg_tail(MgDev g, int top
   }
   // the matrix level: right-hand side at P(nl), partial sums of the
   // column groups after it, the answer over the right-hand side
-  {
+  if constexpr (!MAT) {
+    double* c = P(nl);
+    if (tid < 64) {
+      c[tid] = 0.0;
+      wave_cycle<ND>(c, LGM, top + nl, g, f, bc, pre, post, lam);
+    }
+    __syncthreads();
+  } else {
     double* c = P(nl);
     double a = cm[0] * c[CQ * (tid >> 6)];
 #pragma unroll
@@ -1372,7 +1381,7 @@ int validate(const amrv_mg_config* c) {
 struct MgLayout {
   int nlev = 0;
   size_t off_phi[NFMAX][MG_MAXL]{}, off_f[NFMAX][MG_MAXL]{}, off_phi2[NFMAX][MG_MAXL]{}, off_eps[MG_MAXL]{},
-      off_tmp[4]{}, off_par = 0, off_cmat = 0, total = 0;
+      off_tmp[4]{}, off_par = 0, total = 0;
 };
 
 MgLayout layout(const amrv_mg_config* c) {
@@ -1408,8 +1417,6 @@ MgLayout layout(const amrv_mg_config* c) {
   }
   L.off_par = o;
   o += up(PAR_COUNT * 8);
-  L.off_cmat = o;
-  o += up((size_t)c->nfields * COARSE_CELLS * COARSE_CELLS * 8);
   L.total = o;
   return L;
 }
@@ -1461,9 +1468,12 @@ void enqueue_vcycle_nd(amrv_mg* m) {
                        post);
   else if (g.cells[0] <= COARSE_CELLS)
     hipLaunchKernelGGL((k_mg_small<ND>), dim3(nf), dim3(64), 0, m->st, g, pre, post);
+  else if (g.cmat[0])
+    hipLaunchKernelGGL((k_mg_tail<ND, true>), dim3(nf), dim3(tail_threads<ND>()), m->tail_lds, m->st, g, m->tail, pre,
+                       post, m->tail > 0 ? 1 : 0);
   else
-    hipLaunchKernelGGL((k_mg_tail<ND>), dim3(nf), dim3(tail_threads<ND>()), m->tail_lds, m->st, g, m->tail, pre, post,
-                       m->tail > 0 ? 1 : 0);
+    hipLaunchKernelGGL((k_mg_tail<ND, false>), dim3(nf), dim3(tail_threads<ND>()), m->tail_lds, m->st, g, m->tail, pre,
+                       post, m->tail > 0 ? 1 : 0);
   if (tiled(m)) {
     for (int l = m->tail - 1; l >= 0; l--)
       hipLaunchKernelGGL(k_mg_up2d, dim3((g.n[l] / TS) * (g.n[l] / TS), nf), dim3(256), 0, m->st, g, l, post,
@@ -1491,7 +1501,8 @@ void enqueue_vcycle(amrv_mg* m) {
     enqueue_vcycle_nd<3>(m);
 }
 
-int set_params(amrv_mg* m, const double* lam) {
+// matrix: a V-cycle follows (else the explicit steps, which use its memory)
+int set_params(amrv_mg* m, const double* lam, bool matrix = true) {
   MgPar P{};
   const double L = m->cfg.length;
   for (int l = 0; l < m->g.nlev; l++) {
@@ -1504,14 +1515,14 @@ int set_params(amrv_mg* m, const double* lam) {
       P.v[PAR_IDIAG + f * MG_MAXL + l] = 1.0 / (2.0 * m->g.nd * P.v[PAR_IH2 + l] + lam[f]);
   }
   hipLaunchKernelGGL(k_mg_set, dim3(1), dim3(64), 0, m->st, m->par, P);
-  if (m->g.cells[0] > COARSE_CELLS) {
+  if (matrix && m->g.cmat[0] && !m->var) {
     int lev = 0;
     while (m->g.cells[lev] > COARSE_CELLS) lev++;
     hipLaunchKernelGGL(m->g.nd == 2 ? k_mg_coarse_matrix<2> : k_mg_coarse_matrix<3>, dim3(COARSE_CELLS, m->g.nf),
                        dim3(64), 0, m->st, m->g, lev, m->cfg.pre_sweeps, m->cfg.post_sweeps);
   }
   MGCHK(hipGetLastError());
-  m->par_nf = m->g.nf;
+  m->par_nf = matrix && !m->var ? m->g.nf : 0;
   m->par_lam0 = lam[0];
   return 0;
 }
@@ -1685,7 +1696,7 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
   }
   m->par = reinterpret_cast<double*>(base + L.off_par);
   g.par = m->par;
-  g.cmat = reinterpret_cast<double*>(base + L.off_cmat);
+  for (int f = 0; f < NFMAX; f++) g.cmat[f] = g.cells[0] >= COARSE_CELLS * COARSE_CELLS ? m->tmp[2 + f] : nullptr;
   // the tail: the first level of at most TAIL_CELLS cells, and every level below
   int tail = 0;
   while (g.cells[tail] > TAIL_CELLS) tail++;
@@ -1702,16 +1713,18 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
     offv += 3 * g.cells[l];
   }
   m->tail_lds_var = (size_t)offv * sizeof(double);
-  hipError_t e = cfg->ndim == 2
-                     ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<2>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds)
-                     : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail<3>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds);
+  auto lds_limit = [](const void* k, size_t bytes) {
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  const bool d2 = cfg->ndim == 2, mat = g.cmat[0] != nullptr;
+  hipError_t e = lds_limit(d2 ? (mat ? reinterpret_cast<const void*>(k_mg_tail<2, true>)
+                                     : reinterpret_cast<const void*>(k_mg_tail<2, false>))
+                              : (mat ? reinterpret_cast<const void*>(k_mg_tail<3, true>)
+                                     : reinterpret_cast<const void*>(k_mg_tail<3, false>)),
+                           m->tail_lds);
   if (e == hipSuccess)
-    e = cfg->ndim == 2 ? hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail_var<2>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds_var)
-                       : hipFuncSetAttribute(reinterpret_cast<const void*>(k_mg_tail_var<3>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)m->tail_lds_var);
+    e = lds_limit(d2 ? reinterpret_cast<const void*>(k_mg_tail_var<2>) : reinterpret_cast<const void*>(k_mg_tail_var<3>),
+                  m->tail_lds_var);
   m->nb_init = std::min(blocks_of(g.cells[0]), 256);
   m->nb_cycle = tiled(m) ? (g.n[0] / TS) * (g.n[0] / TS) : m->nb_init;
   g.maxb = std::max(m->nb_init, m->nb_cycle);
@@ -1828,7 +1841,7 @@ int amrv_rd_step(amrv_mg* m, const amrv_rd_params* p, int32_t scheme, double dt,
     lam[0] = 2.0 / (dt * p->Du);
     lam[1] = 2.0 / (dt * p->Dv);
   }
-  if (int rc = set_params(m, lam)) return rc;
+  if (int rc = set_params(m, lam, implicit)) return rc;
   int total = 0;
   const bool d2 = g.nd == 2;
   double *cu = u, *cv = v, *au = m->tmp[0], *av = m->tmp[1];  // explicit schemes: current and other buffer
