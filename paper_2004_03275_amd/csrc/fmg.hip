@@ -43,9 +43,10 @@
 // Layout in the caller's workspace (256-byte aligned arrays):
 //   tables   lvl, ij[3], nbr[6], chi[8], cnb[6], par per block (2D uses the
 //            first entries); leaf -> block
-//   u, f, fu, r, uo  [block][16^d] doubles (state, relaxation right-hand
-//                 side, the problem's f, residual or restricted residual,
-//                 restricted state)
+//   u, f, fu, r, uo  [block][16^d] doubles, the colours apart (state,
+//                 relaxation right-hand side, the problem's f, restricted
+//                 residual, restricted state; a leaf's r holds its coarse-fine
+//                 ghosts, its uo the block maxima of the residual check)
 //   the uniform solver's own workspace (its finest right-hand side and
 //                 solution arrays are the level-1 grid, fgrid and vgrid)
 //   red, tmp, part  two 64-bit maxima, eight leaf fields (reaction-diffusion
@@ -103,8 +104,23 @@ struct FmgDev {
   double rh[FMG_MAXL + 1];   // 1/h per level
 };
 
-// a cell's index in its block, (x, y, z) with x fastest (z = 0 in 2D)
-__host__ __device__ inline int cidx(const int* c) { return c[0] + NB * (c[1] + NB * c[2]); }
+// a cell's index in its block (z = 0 in 2D): per plane the 128 cells of colour
+// 0 = (x + y + z) & 1, then the 128 of colour 1, each [y][x / 2].  A colour sweep
+// reads one colour of u and the other of f and writes the latter: with the
+// colours apart every line it touches is used whole, where the natural order
+// moved every line of u and f for half its values (finest 3D sweep, 3,040
+// blocks: 66.6 -> 56.7 us, with the ghosts below 34.1 us, 4.4 TB/s).
+__host__ __device__ inline int cidx(const int* c) {
+  return NB * NB * c[2] + NB * NB / 2 * ((c[0] + c[1] + c[2]) & 1) + NB / 2 * c[1] + (c[0] >> 1);
+}
+// and in a leaf field, x fastest
+__host__ __device__ inline int nidx(const int* c) { return c[0] + NB * (c[1] + NB * c[2]); }
+// the cell of natural index t
+__host__ __device__ inline void ncell(int t, int* c) {
+  c[0] = t & (NB - 1);
+  c[1] = (t >> 4) & (NB - 1);
+  c[2] = t >> 8;
+}
 
 // a neighbour value in the form cv + w u(c)
 struct Across {
@@ -163,20 +179,24 @@ __host__ __device__ inline Across across(const FmgDev& g, int b, bool leaf, cons
     K[e] = (gc[e] >> 1) - g.ij[TS * Cb + e] * NB;
   }
   K[d] = lo ? NB - 1 : 0;
-  const double* p = g.u + (size_t)Cb * NCB + cidx(K);
-  double val = p[0];
+  const double* uc = g.u + (size_t)Cb * NCB;
+  const double u0 = uc[cidx(K)];
+  double val = u0;
 #pragma unroll
   for (int e = 0; e < ND; e++) {
     if (e == d) continue;
-    const int st = e == 0 ? 1 : (e == 1 ? NB : NB * NB);
     const int t = K[e];
+    int lo3[3] = {K[0], K[1], K[2]}, hi3[3] = {K[0], K[1], K[2]};
+    lo3[e] = t == 0 ? 0 : t - 1;
+    hi3[e] = t == NB - 1 ? t : t + 1;
+    const double ul = uc[cidx(lo3)], uh = uc[cidx(hi3)];
     double slope;
     if (t == 0)
-      slope = p[st] - p[0];
+      slope = uh - u0;
     else if (t == NB - 1)
-      slope = p[0] - p[-st];
+      slope = u0 - ul;
     else
-      slope = 0.5 * p[st] - 0.5 * p[-st];
+      slope = 0.5 * uh - 0.5 * ul;
     val += ((gc[e] & 1) ? 0.25 : -0.25) * slope;
   }
   return {(2.0 / 3.0) * val, 1.0 / 3.0};
@@ -208,34 +228,76 @@ __host__ __device__ inline void stencil(const FmgDev& g, int b, bool leaf, const
   sw = ws;
 }
 
+// Coarse-fine ghosts.  On the fine side of a coarse-fine face the value across
+// is (u + 2 u_c) / 3 with u_c from a coarser leaf, which no sweep of this level
+// changes: the terms (2/3) u_c of a face's cells are formed once per cycle
+// (when the level is prolonged, after its coarser level is final; they hold
+// until that leaf's level is relaxed on the next way down, after this level's
+// sweeps and restriction) and kept in the residual array of the leaf, which only
+// parents use: [face][cell of the face].  A sweep then reads them like a
+// neighbour's cells; resolved in every sweep, they held all 64 lanes of a wave
+// for two dependent loads and ~100 instructions wherever one lane lay on such a
+// face (finest 3D sweep, 3,040 blocks: 56.7 -> 34.1 us; residual and restriction 94 -> 55).
+template <int ND>
+constexpr int nface() {  // cells of a face
+  return ND == 3 ? NB * NB : NB;
+}
+
+// the cell's number on a face across d
+template <int ND>
+__host__ __device__ inline int face_cell(const int* c, int d) {
+  if constexpr (ND == 2) return c[d ^ 1];
+  return c[d == 0 ? 1 : 0] + NB * c[d == 2 ? 1 : 2];
+}
+
+// cell t of face `face`
+template <int ND>
+__host__ __device__ inline void face_coord(int face, int t, int* c) {
+  const int d = face >> 1;
+  c[2] = 0;
+  c[d == 0 ? 1 : 0] = t & (NB - 1);
+  if constexpr (ND == 3) c[d == 2 ? 1 : 2] = t >> 4;
+  c[d] = (face & 1) ? NB - 1 : 0;
+}
+
 // stencil for K cells of block b at once, the same sums in the same order:
-// every neighbour load that needs no rule (a cell of this block, or of a
-// same-level neighbour block whose own cell stands in: the face type is
-// uniform per block, so a lane on the face only changes the address) is
-// issued before any other face is resolved, so the K cells' loads are in
-// flight together; the lanes on a wall or coarse-fine face then take across()
-template <int ND, int K>
+// every neighbour load that needs no rule is issued before any other face is
+// resolved, so the K cells' loads are in flight together; the face type is
+// uniform per block, so a lane on a face only changes the address: to the
+// same-level neighbour block's cell or (GHOSTS) the coarse-fine ghost, a wall
+// taking no value.  The lanes on a remaining face (a refined neighbour under the
+// problem's rules; without GHOSTS a wall or a coarser leaf too) take across()
+template <int ND, int K, bool GHOSTS = false>
 __host__ __device__ inline void stencil_k(const FmgDev& g, int b, bool leaf, const int (*c)[3], double* sc,
                                           double* sw) {
   constexpr int NCB = ncb<ND>();
-  double v[K][2 * ND];
-  bool rule[2 * ND];  // the face needs across() for the lanes on it
+  constexpr int YS = NB / 2, ZS = NB * NB;
+  const double* ub = g.u + (size_t)b * NCB;
+  double v[K][2 * ND], w[2 * ND];
+  bool rule[2 * ND];
+  int o[K];  // the cell's place in the other colour, from which each neighbour is a fixed step away
+#pragma unroll
+  for (int k = 0; k < K; k++) o[k] = cidx(c[k]) ^ (NB * NB / 2);
 #pragma unroll
   for (int face = 0; face < 2 * ND; face++) {
-    const int d = face >> 1, s1 = (face & 1) ? 1 : -1;
+    const int d = face >> 1;
+    const bool up = face & 1;
     const int nb = g.nbr[FS * b + face];
-    const bool plain = nb >= 0 && (!leaf || g.chi[CS * nb] < 0);
-    rule[face] = !plain;
+    const bool coarse = nb == NBR_NONE, wall = nb == NBR_WALL;
+    rule[face] = (leaf && nb >= 0 && g.chi[CS * nb] >= 0) || (!GHOSTS && nb < 0);
+    w[face] = coarse ? 1.0 / 3.0 : (wall ? 1.0 : 0.0);
+    const bool ghost = GHOSTS && coarse, none = nb < 0 && !ghost;
+    const double* un = none ? ub : (ghost ? g.r + (size_t)b * NCB + face * nface<ND>() : g.u + (size_t)nb * NCB);
+    const int st = d == 1 ? YS : ZS, wrap = d == 0 ? NB / 2 - 1 : (NB - 1) * st;
 #pragma unroll
     for (int k = 0; k < K; k++) {
-      int cn[3] = {c[k][0], c[k][1], c[k][2]};
-      const int x = cn[d] + s1;
-      const bool out = x < 0 || x > NB - 1;
-      // in the block: the neighbour; out with a plain face: the neighbour
-      // block's cell; out otherwise: the cell itself (discarded)
-      cn[d] = out ? (plain ? (s1 > 0 ? 0 : NB - 1) : cn[d]) : x;
-      const int blk = out && plain ? nb : b;
-      v[k][face] = g.u[(size_t)blk * NCB + cidx(cn)];
+      const bool out = c[k][d] == (up ? NB - 1 : 0);
+      // along x the step is 0 or 1: the two cells of a pair share their place
+      const int step = d == 0 ? ((c[k][0] & 1) == (up ? 1 : 0) ? 1 : 0) : st;
+      const int in = up ? o[k] + step : o[k] - step;
+      const int ac = ghost ? face_cell<ND>(c[k], d) : (up ? o[k] - wrap : o[k] + wrap);
+      const double q = (out ? un : ub)[out ? ac : in];
+      v[k][face] = none && out ? 0.0 : q;
     }
   }
 #pragma unroll
@@ -243,9 +305,9 @@ __host__ __device__ inline void stencil_k(const FmgDev& g, int b, bool leaf, con
     double s = 0.0, ws = 0.0;  // as in stencil
 #pragma unroll
     for (int face = 0; face < 2 * ND; face++) {
-      const int x = c[k][face >> 1] + ((face & 1) ? 1 : -1);
-      double av = v[k][face], aw = 0.0;
-      if (!((x >= 0 && x < NB) || !rule[face])) {
+      const bool out = c[k][face >> 1] == ((face & 1) ? NB - 1 : 0);
+      double av = v[k][face], aw = out ? w[face] : 0.0;
+      if (out && rule[face]) {
         const Across a = across<ND>(g, b, leaf, c[k], face);
         av = a.cv;
         aw = a.w;
@@ -258,9 +320,19 @@ __host__ __device__ inline void stencil_k(const FmgDev& g, int b, bool leaf, con
   }
 }
 
-// Every kernel below applies one per-cell function (host-callable too, so a
-// host loop over the same functions checks a cycle on the CPU); a 256-thread
-// workgroup walks a block plane by plane, thread t at (t & 15, t >> 4).
+// the coarse-fine ghosts of leaf block b: `part` of `parts` of its faces
+template <int ND>
+__device__ inline void ghost_faces(const FmgDev& g, int b, int part, int parts) {
+  constexpr int NF = nface<ND>();
+  const int per = blockDim.x / NF;  // faces at a time
+  for (int face = part * per + threadIdx.x / NF; face < 2 * ND; face += parts * per) {
+    if (g.nbr[FS * b + face] != NBR_NONE) continue;
+    const int t = threadIdx.x & (NF - 1);
+    int c[3];
+    face_coord<ND>(face, t, c);
+    g.r[(size_t)b * ncb<ND>() + face * NF + t] = across<ND>(g, b, false, c, face).cv;
+  }
+}
 
 // lap(u) - lambda u at cell c of block b: the problem's rules (leaf), or the
 // plain stencil, the refined neighbours' own (restricted) cells in place of
@@ -273,59 +345,18 @@ __host__ __device__ inline double apply_cell(const FmgDev& g, int b, bool leaf, 
   return g.ih2[g.lvl[b]] * (sc + sw * u - (2.0 * ND) * u) - g.lam * u;
 }
 
-// red-black relaxation of cell c of block b with the plain stencil (the
-// problem's rules on the finest level, which has no refined neighbour): a
-// cell of colour (x + y + z) & 1 reads cells of the other colour only (the
-// block edge is even, so the colour is global) and coarser levels, none of
-// which a sweep of one level writes
-template <int ND>
-__host__ __device__ inline void smooth_cell(const FmgDev& g, int b, const int* c) {
-  const double ih2 = g.ih2[g.lvl[b]];
-  double sc, sw;
-  stencil<ND>(g, b, false, c, sc, sw);
-  const size_t i = (size_t)b * ncb<ND>() + cidx(c);
-  g.u[i] = (g.f[i] - ih2 * sc) / (ih2 * (sw - 2.0 * ND) - g.lam);
-}
-
-// the residual of the relaxation (plain stencil)
-template <int ND>
-__host__ __device__ inline void resid_cell(const FmgDev& g, int b, const int* c) {
-  const size_t i = (size_t)b * ncb<ND>() + cidx(c);
-  g.r[i] = g.f[i] - apply_cell<ND>(g, b, false, c);
-}
-
-// the problem's residual at a leaf cell
-template <int ND>
-__host__ __device__ inline double residual(const FmgDev& g, int b, const int* c) {
-  return g.fu[(size_t)b * ncb<ND>() + cidx(c)] - apply_cell<ND>(g, b, true, c);
-}
-
-// the right-hand side of a level below the finest: L(u) + r with L the plain
+// Red-black relaxation with the plain stencil (the problem's rules on the finest
+// level, which has no refined neighbour): a cell of colour (x + y + z) & 1 reads
+// cells of the other colour only (the block edge is even, so the colour is
+// global) and coarser levels, none of which a sweep of one level writes.
+//
+// The right-hand side of a level below the finest: L(u) + r with L the plain
 // stencil, r the restricted residual (a parent) or the problem's residual (a
 // leaf; where the plain stencil is the problem's, exactly f).  A leaf next to
 // a refined block thereby relaxes with the same stencil as that block's
-// cells, and is left unchanged once the problem's residual vanishes.
-template <int ND>
-__host__ __device__ inline void fas_cell(const FmgDev& g, int b, const int* c) {
-  const size_t i = (size_t)b * ncb<ND>() + cidx(c);
-  if (g.chi[CS * b] >= 0) {
-    g.f[i] = apply_cell<ND>(g, b, false, c) + g.r[i];
-    return;
-  }
-  bool refined = false;  // a refined same-level neighbour (else both stencils agree)
-#pragma unroll
-  for (int face = 0; face < 2 * ND; face++) {
-    const int nb = g.nbr[FS * b + face];
-    refined = refined || (nb >= 0 && g.chi[CS * nb] >= 0);
-  }
-  if (!refined) {
-    g.f[i] = g.fu[i];
-    return;
-  }
-  const double lp = apply_cell<ND>(g, b, false, c);
-  const double lc = apply_cell<ND>(g, b, true, c);
-  g.f[i] = lp == lc ? g.fu[i] : lp + (g.fu[i] - lc);
-}
+// cells, and is left unchanged once the problem's residual vanishes.  A leaf's
+// two stencils differ only in its cells along a refined neighbour, so every
+// other leaf cell keeps the f that loading the problem put there.
 
 // a block of level >= 2 adds the bi/trilinear interpolation of its parent's
 // change e = u - uo: weights 9, 3, 3, 1 (/16) in 2D, 27, 9, 3, 1 (/64) in 3D,
@@ -360,11 +391,6 @@ __host__ __device__ inline double prolong_delta(const FmgDev& g, int b, const in
   return d;
 }
 
-template <int ND>
-__host__ __device__ inline void prolong_cell(const FmgDev& g, int b, const int* c) {
-  g.u[(size_t)b * ncb<ND>() + cidx(c)] += prolong_delta<ND>(g, b, c);
-}
-
 // index of cell c of level-1 block b in the n^ND grid
 template <int ND>
 __host__ __device__ inline size_t grid_index(const FmgDev& g, int b, const int* c, int n) {
@@ -372,16 +398,6 @@ __host__ __device__ inline size_t grid_index(const FmgDev& g, int b, const int* 
 #pragma unroll
   for (int e = ND - 1; e >= 0; e--) i = i * n + (size_t)(g.ij[TS * b + e] * NB + c[e]);
   return i;
-}
-
-// a level-1 cell to the n^ND grid: the correction problem L(e) = r, from e = 0
-template <int ND>
-__host__ __device__ inline void to_grid_cell(const FmgDev& g, int b, const int* c, int n, double* fgrid,
-                                             double* vgrid) {
-  const size_t i = (size_t)b * ncb<ND>() + cidx(c);
-  const size_t gi = grid_index<ND>(g, b, c, n);
-  fgrid[gi] = g.r[i];
-  vgrid[gi] = 0.0;
 }
 
 // the block a workgroup of a 3D launch over n blocks takes: workgroups are
@@ -397,84 +413,89 @@ __device__ inline int xcd_block(int i, int n) {
   const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4; \
   for (int tz = 0; tz < nplanes<ND>(); tz++)
 
-// a colour sweep over the blocks [b0, b0 + gridDim.x); in 3D the 256 threads
-// take the 128 cells of the colour in each of two planes at a time (x = 2 hx
-// + the parity that gives the colour), so no lane idles
+// a colour sweep over the blocks [b0, b0 + gridDim.x): the 128 cells of the
+// colour in a plane are consecutive (x = 2 hx + the parity that gives the
+// colour); 2D 128 threads a block, 3D 256 threads two planes at a time, the
+// cells of four plane pairs batched (stencil_k)
 template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_smooth(FmgDev g, int b0, int colour) {
-  if constexpr (ND == 2) {
-    const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
-    const int c[3] = {tx, ty, 0};
-    if (((tx + ty) & 1) == colour) smooth_cell<2>(g, b0 + blockIdx.x, c);
-  } else {
-    // the cells of four plane pairs at a time (stencil_k): the same update
-    // as smooth_cell, its loads batched
-    constexpr int K = 4;
-    const int hx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & (NB - 1), pz = threadIdx.x >> 7;
-    const int b = b0 + xcd_block(blockIdx.x, gridDim.x);
-    const double ih2 = g.ih2[g.lvl[b]];
-    const int span = NB / gridDim.y;  // the planes of this workgroup's part of the block
-    for (int z0 = blockIdx.y * span; z0 < (int)(blockIdx.y + 1) * span; z0 += 2 * K) {
-      int c[K][3];
-      size_t i[K];
-      double fv[K], sc[K], sw[K];
+__global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_smooth(FmgDev g, int b0, int colour) {
+  constexpr int K = ND == 3 ? 4 : 1;
+  const int hx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & (NB - 1), pz = ND == 3 ? threadIdx.x >> 7 : 0;
+  const int b = b0 + (ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
+  const double ih2 = g.ih2[g.lvl[b]];
+  const int span = ND == 3 ? NB / gridDim.y : 1;  // the planes of this workgroup's part of the block
+  for (int z0 = blockIdx.y * span; z0 < (int)(blockIdx.y + 1) * span; z0 += 2 * K) {
+    int c[K][3];
+    size_t i[K];
+    double fv[K], sc[K], sw[K];
 #pragma unroll
-      for (int k = 0; k < K; k++) {
-        const int tz = z0 + 2 * k + pz;
-        c[k][0] = 2 * hx + ((ty + tz + colour) & 1);
-        c[k][1] = ty;
-        c[k][2] = tz;
-        i[k] = (size_t)b * ncb<3>() + cidx(c[k]);
-        fv[k] = g.f[i[k]];
-      }
-      stencil_k<3, K>(g, b, false, c, sc, sw);
-#pragma unroll
-      for (int k = 0; k < K; k++) g.u[i[k]] = (fv[k] - ih2 * sc[k]) / (ih2 * (sw[k] - 2.0 * 3) - g.lam);
+    for (int k = 0; k < K; k++) {
+      const int tz = ND == 3 ? z0 + 2 * k + pz : 0;
+      c[k][0] = 2 * hx + ((ty + tz + colour) & 1);
+      c[k][1] = ty;
+      c[k][2] = tz;
+      i[k] = (size_t)b * ncb<ND>() + NB * NB * tz + NB * NB / 2 * colour + (threadIdx.x & 127);
+      fv[k] = g.f[i[k]];
     }
+    stencil_k<ND, K, true>(g, b, false, c, sc, sw);
+#pragma unroll
+    for (int k = 0; k < K; k++) g.u[i[k]] = (fv[k] - ih2 * sc[k]) / (ih2 * (sw[k] - 2.0 * ND) - g.lam);
   }
 }
 
 // lap(u) - lambda u at K cells of block b (u their values): apply_cell's
 // arithmetic with the loads batched as in stencil_k
-template <int ND, int K>
+template <int ND, int K, bool GHOSTS = false>
 __host__ __device__ inline void apply_k(const FmgDev& g, int b, bool leaf, const int (*c)[3], const double* u,
                                         double* out) {
   double sc[K], sw[K];
-  stencil_k<ND, K>(g, b, leaf, c, sc, sw);
+  stencil_k<ND, K, GHOSTS>(g, b, leaf, c, sc, sw);
   const double ih2 = g.ih2[g.lvl[b]];
 #pragma unroll
   for (int k = 0; k < K; k++) out[k] = ih2 * (sc[k] + sw[k] * u[k] - (2.0 * ND) * u[k]) - g.lam * u[k];
 }
 
+// every leaf's ghosts (the start of a solve)
 template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_resid(FmgDev g, int b0) {
+__global__ void __launch_bounds__(WG) k_fmg_ghosts(FmgDev g, const int* leafblk) {
+  ghost_faces<ND>(g, leafblk[blockIdx.x], blockIdx.y, gridDim.y);
+}
+
+// the residual of the relaxation on level 1, written to the n^ND grid as the
+// correction problem L(e) = r, from e = 0
+template <int ND>
+__global__ void __launch_bounds__(WG) k_fmg_resid_grid(FmgDev g, int b0, int n, double* fgrid, double* vgrid) {
+  const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
   if constexpr (ND == 2) {
-    FMG_PLANES(ND) {
-      const int c[3] = {tx, ty, tz};
-      resid_cell<ND>(g, b0 + blockIdx.x, c);
-    }
+    const int b = b0 + blockIdx.x;
+    const int c[3] = {tx, ty, 0};
+    const size_t gi = grid_index<2>(g, b, c, n);
+    fgrid[gi] = g.f[(size_t)b * ncb<2>() + cidx(c)] - apply_cell<2>(g, b, false, c);
+    vgrid[gi] = 0.0;
   } else {
     // four planes at a time (apply_k)
     constexpr int K = 4;
-    const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
     const int b = b0 + xcd_block(blockIdx.x, gridDim.x);
     const int span = NB / gridDim.y;
     for (int z0 = blockIdx.y * span; z0 < (int)(blockIdx.y + 1) * span; z0 += K) {
       int c[K][3];
-      size_t i[K];
       double fv[K], uv[K], a[K];
 #pragma unroll
       for (int k = 0; k < K; k++) {
         c[k][0] = tx;
         c[k][1] = ty;
         c[k][2] = z0 + k;
-        i[k] = (size_t)b * ncb<3>() + cidx(c[k]);
-        fv[k] = g.f[i[k]];
-        uv[k] = g.u[i[k]];
+        const size_t i = (size_t)b * ncb<3>() + cidx(c[k]);
+        fv[k] = g.f[i];
+        uv[k] = g.u[i];
       }
-      apply_k<3, K>(g, b, false, c, uv, a);
+      apply_k<3, K, true>(g, b, false, c, uv, a);
 #pragma unroll
-      for (int k = 0; k < K; k++) g.r[i[k]] = fv[k] - a[k];
+      for (int k = 0; k < K; k++) {
+        const size_t gi = grid_index<3>(g, b, c[k], n);
+        fgrid[gi] = fv[k] - a[k];
+        vgrid[gi] = 0.0;
+      }
     }
   }
 }
@@ -482,7 +503,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resid(FmgDev g, int b0) {
 // a child block's residual restricted together with its state, so the fine
 // residual is never stored: parent cell t of the child's quadrant / octant
 // takes the means of u and of f - L(u) (L the plain stencil) over its 2^ND
-// cells (into the parent's u and uo, and r), the residual as resid_cell's; in
+// cells (into the parent's u and uo, and r), the residual f - apply_cell; in
 // 3D 256 threads take the 512 parent cells (on levels of few blocks split
 // over gridDim.y workgroups), in 2D 64 threads the 64
 template <int ND>
@@ -505,7 +526,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resid_restrict(FmgDev g, int b0) {
       uv[k] = g.u[i];
       fv[k] = g.f[i];
     }
-    apply_k<ND, NC>(g, b, false, c, uv, a);
+    apply_k<ND, NC, true>(g, b, false, c, uv, a);
 #pragma unroll
     for (int k = 0; k < NC; k++) r[k] = fv[k] - a[k];
     double um, rm;
@@ -544,178 +565,218 @@ __device__ inline void fas_parent_3d(const FmgDev& g, int b) {
       rv[k] = g.r[i[k]];
       uv[k] = g.u[i[k]];
     }
-    apply_k<3, K>(g, b, false, c, uv, a);
+    apply_k<3, K, true>(g, b, false, c, uv, a);
 #pragma unroll
     for (int k = 0; k < K; k++) g.f[i[k]] = a[k] + rv[k];
   }
 }
 
-// a leaf block below the finest level in 3D (fas_cell's other cases): f
-// copied from the problem's f where no same-level neighbour is refined, else
-// lp + (f - lc) with both stencils, four planes at a time
-__device__ inline void fas_leaf_3d(const FmgDev& g, int b) {
-  const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
-  const size_t base = (size_t)b * ncb<3>() + tx + NB * ty;
-  bool refined = false;  // uniform per workgroup
-#pragma unroll
-  for (int face = 0; face < 6; face++) {
-    const int nb = g.nbr[FS * b + face];
-    refined = refined || (nb >= 0 && g.chi[CS * nb] >= 0);
-  }
-  constexpr int K = 4;
-  const int span = NB / gridDim.y;
-  const int zlo = blockIdx.y * span, zhi = zlo + span;
-  if (!refined) {
-    for (int z0 = zlo; z0 < zhi; z0 += K) {
-      double v[K];
-#pragma unroll
-      for (int k = 0; k < K; k++) v[k] = g.fu[base + (size_t)NB * NB * (z0 + k)];
-#pragma unroll
-      for (int k = 0; k < K; k++) g.f[base + (size_t)NB * NB * (z0 + k)] = v[k];
+// the right-hand side of a level below the finest: L(u) + r on the parents; on
+// a leaf only the cells along a refined neighbour, lp + (f - lc) with both
+// stencils (an edge cell lies along two faces: either gives the same value)
+template <int ND>
+__global__ void __launch_bounds__(WG) k_fmg_fas(FmgDev g, int b0) {
+  const int b = b0 + (ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
+  constexpr int NCB = ncb<ND>(), NF = nface<ND>();
+  if (g.chi[CS * b] >= 0) {
+    if constexpr (ND == 3) {
+      fas_parent_3d(g, b);
+    } else {
+      int c[1][3];
+      ncell(threadIdx.x, c[0]);
+      const size_t i = (size_t)b * NCB + cidx(c[0]);
+      const double uv = g.u[i], rv = g.r[i];
+      double a;
+      apply_k<2, 1, true>(g, b, false, c, &uv, &a);
+      g.f[i] = a + rv;
     }
     return;
   }
-  for (int z0 = zlo; z0 < zhi; z0 += K) {
+  for (int face = ND == 3 ? (int)blockIdx.y : (int)(threadIdx.x >> 4); face < 2 * ND;
+       face += ND == 3 ? (int)gridDim.y : WG / NF) {
+    const int nb = g.nbr[FS * b + face];
+    if (nb < 0 || g.chi[CS * nb] < 0) continue;
+    int c[1][3];
+    face_coord<ND>(face, threadIdx.x & (NF - 1), c[0]);
+    const size_t i = (size_t)b * NCB + cidx(c[0]);
+    const double uv = g.u[i], fv = g.fu[i];
+    double lp, lc;
+    apply_k<ND, 1, true>(g, b, false, c, &uv, &lp);
+    apply_k<ND, 1, true>(g, b, true, c, &uv, &lc);
+    g.f[i] = lp == lc ? fv : lp + (fv - lc);
+  }
+}
+
+// adds the interpolated correction to the cells of colour 1: the colour-0 sweep
+// that follows recomputes every cell of colour 0 from colour 1 and coarser
+// levels, never from its old value.  In 3D the parent's change around the
+// child's octant (8^3 cells and their neighbours inside the parent) is staged in
+// LDS: read per cell it was 16 loads each (finest, 3,040 blocks: 92 -> 31 us).  The second row of
+// workgroups forms the level's coarse-fine ghosts, whose coarser leaves are
+// final by now.
+template <int ND>
+__global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_prolong(FmgDev g, int b0) {
+  const int b = b0 + (ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x);
+  if (blockIdx.y) {
+    if (g.chi[CS * b] < 0) ghost_faces<ND>(g, b, blockIdx.y - 1, gridDim.y - 1);
+    return;
+  }
+  const int hx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & (NB - 1), pz = ND == 3 ? threadIdx.x >> 7 : 0;
+  double* ub = g.u + (size_t)b * ncb<ND>() + NB * NB / 2 + (threadIdx.x & 127);
+  if constexpr (ND == 2) {
+    const int c[3] = {2 * hx + ((ty + 1) & 1), ty, 0};
+    ub[0] += prolong_delta<2>(g, b, c);
+  } else {
+    constexpr int E = 10;  // the octant and one cell around it, clamped to the parent
+    __shared__ double e[E * E * E];
+    const size_t p = (size_t)g.par[b] * ncb<3>();
+    const int o[3] = {(g.ij[TS * b] & 1) * 8 - 1, (g.ij[TS * b + 1] & 1) * 8 - 1, (g.ij[TS * b + 2] & 1) * 8 - 1};
+    double uv[8];
+#pragma unroll
+    for (int k = 0; k < 8; k++) uv[k] = ub[NB * NB * (2 * k + pz)];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int t = threadIdx.x + q * WG;
+      if (t < E * E * E) {
+        const int x = t % E, y = (t / E) % E, z = t / (E * E);
+        const int c[3] = {min(max(o[0] + x, 0), NB - 1), min(max(o[1] + y, 0), NB - 1), min(max(o[2] + z, 0), NB - 1)};
+        e[t] = g.u[p + cidx(c)] - g.uo[p + cidx(c)];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+      // prolong_delta's weights and order
+      const int z = 2 * k + pz, x = 2 * hx + ((ty + z + 1) & 1);
+      const int a = (x >> 1) + 1, bb = (ty >> 1) + 1, cc = (z >> 1) + 1;
+      const int da = (x & 1) ? 1 : -1, db = (ty & 1) ? E : -E, dc = (z & 1) ? E * E : -E * E;
+      const double* q = e + a + E * (bb + E * cc);
+      const double d = (27.0 * q[0] + 9.0 * (q[da] + q[db] + q[dc]) + 3.0 * (q[da + db] + q[da + dc] + q[db + dc]) +
+                        q[da + db + dc]) *
+                       (1.0 / 64.0);
+      ub[NB * NB * z] = uv[k] + d;
+    }
+  }
+}
+
+// the level-1 correction, on colour 1 only (as k_fmg_prolong)
+template <int ND>
+__global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_from_grid(FmgDev g, int b0, int n, const double* vgrid) {
+  const int b = b0 + blockIdx.x;
+  const int hx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & (NB - 1), pz = ND == 3 ? threadIdx.x >> 7 : 0;
+  for (int tz = pz; tz < nplanes<ND>(); tz += 2) {
+    const int c[3] = {2 * hx + ((ty + tz + 1) & 1), ty, tz};
+    g.u[(size_t)b * ncb<ND>() + cidx(c)] += vgrid[grid_index<ND>(g, b, c, n)];
+  }
+}
+
+// workgroup maximum of v >= 0, in thread 0
+__device__ __forceinline__ double wg_max(double v) {
+  __shared__ double sm[16];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int i = 1; i < (int)(blockDim.x >> 6); i++) v = fmax(v, sm[i]);
+  return v;
+}
+
+// and over workgroups into *out (the bits of non-negative doubles order as the
+// values)
+__device__ __forceinline__ void fold_max(double v, unsigned long long* out) {
+  v = wg_max(v);
+  if (threadIdx.x == 0) atomicMax(out, (unsigned long long)__double_as_longlong(v));
+}
+
+// max |r| of the problem over each leaf's part blockIdx.y and, with_f, max |f|
+// (the problem's f as solved), into words y and 2 + y of the leaf's restricted
+// state (which only parents use); k_fmg_resmax_all takes the maximum.  (One
+// atomic per workgroup on one address: 12 ns each, one after another, 106 us of
+// 228 on 4,425 leaves.)  The cells off a refined neighbour take the plain stencil, those along one
+// the problem's rules afterwards: kept out of the main loop, whose registers
+// they had doubled.
+template <int ND>
+__global__ void __launch_bounds__(WG) k_fmg_resmax(FmgDev g, const int* leafblk, int with_f) {
+  const int b = leafblk[ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x];
+  constexpr int NCB = ncb<ND>(), K = ND == 3 ? 4 : 1, NF = nface<ND>();
+  const double ih2 = g.ih2[g.lvl[b]];
+  unsigned refined = 0;  // faces with a refined neighbour
+#pragma unroll
+  for (int face = 0; face < 2 * ND; face++) {
+    const int nb = g.nbr[FS * b + face];
+    if (nb >= 0 && g.chi[CS * nb] >= 0) refined |= 1u << face;
+  }
+  double mr = 0.0, mf = 0.0;
+  const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
+  const int span = ND == 3 ? NB / gridDim.y : 1;
+  for (int z0 = blockIdx.y * span; z0 < (int)(blockIdx.y + 1) * span; z0 += K) {
     int c[K][3];
-    double fv[K], uv[K], lp[K], lc[K];
+    double fv[K], uv[K], sc[K], sw[K];
 #pragma unroll
     for (int k = 0; k < K; k++) {
       c[k][0] = tx;
       c[k][1] = ty;
       c[k][2] = z0 + k;
-      fv[k] = g.fu[base + (size_t)NB * NB * (z0 + k)];
-      uv[k] = g.u[base + (size_t)NB * NB * (z0 + k)];
+      const size_t i = (size_t)b * NCB + cidx(c[k]);
+      fv[k] = g.fu[i];
+      uv[k] = g.u[i];
     }
-    apply_k<3, K>(g, b, false, c, uv, lp);
-    apply_k<3, K>(g, b, true, c, uv, lc);
+    stencil_k<ND, K, true>(g, b, false, c, sc, sw);
 #pragma unroll
-    for (int k = 0; k < K; k++)
-      g.f[base + (size_t)NB * NB * (z0 + k)] = lp[k] == lc[k] ? fv[k] : lp[k] + (fv[k] - lc[k]);
-  }
-}
-
-template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_fas(FmgDev g, int b0) {
-  if constexpr (ND == 3) {
-    const int b = b0 + xcd_block(blockIdx.x, gridDim.x);
-    if (g.chi[CS * b] >= 0)
-      fas_parent_3d(g, b);
-    else
-      fas_leaf_3d(g, b);
-    return;
-  }
-  FMG_PLANES(ND) {
-    const int c[3] = {tx, ty, tz};
-    fas_cell<ND>(g, b0 + blockIdx.x, c);
-  }
-}
-
-template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_prolong(FmgDev g, int b0) {
-  if constexpr (ND == 2) {
-    FMG_PLANES(ND) {
-      const int c[3] = {tx, ty, tz};
-      prolong_cell<ND>(g, b0 + blockIdx.x, c);
-    }
-  } else {
-    // four planes at a time: the parent's values (shared by neighbouring
-    // planes) and the cells' own values loaded before any store
-    constexpr int K = 4;
-    const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
-    const int b = b0 + xcd_block(blockIdx.x, gridDim.x);
-    for (int z0 = 0; z0 < NB; z0 += K) {
-      double d[K], uv[K];
-      size_t i[K];
+    for (int k = 0; k < K; k++) {
+      const double r = fv[k] - (ih2 * (sc[k] + sw[k] * uv[k] - (2.0 * ND) * uv[k]) - g.lam * uv[k]);
+      bool skip = false;
+      if (refined)
 #pragma unroll
-      for (int k = 0; k < K; k++) {
-        const int c[3] = {tx, ty, z0 + k};
-        i[k] = (size_t)b * ncb<3>() + cidx(c);
-        uv[k] = g.u[i[k]];
-        d[k] = prolong_delta<3>(g, b, c);
-      }
-#pragma unroll
-      for (int k = 0; k < K; k++) g.u[i[k]] = uv[k] + d[k];
+        for (int face = 0; face < 2 * ND; face++)
+          skip = skip || ((refined >> face & 1) && c[k][face >> 1] == ((face & 1) ? NB - 1 : 0));
+      mr = fmax(mr, skip ? 0.0 : (isnan(r) ? INFINITY : fabs(r)));
+      mf = fmax(mf, isnan(fv[k]) ? INFINITY : fabs(fv[k]));
     }
   }
-}
-
-template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_to_grid(FmgDev g, int b0, int n, double* fgrid, double* vgrid) {
-  FMG_PLANES(ND) {
-    const int c[3] = {tx, ty, tz};
-    to_grid_cell<ND>(g, b0 + blockIdx.x, c, n, fgrid, vgrid);
-  }
-}
-
-template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_from_grid(FmgDev g, int b0, int n, const double* vgrid) {
-  const int b = b0 + blockIdx.x;
-  FMG_PLANES(ND) {
-    const int c[3] = {tx, ty, tz};
-    g.u[(size_t)b * ncb<ND>() + cidx(c)] += vgrid[grid_index<ND>(g, b, c, n)];
-  }
-}
-
-// block maximum of v >= 0 into *out (the bits of non-negative doubles order
-// as the values)
-__device__ __forceinline__ void fold_max(double v, unsigned long long* out) {
-  __shared__ double sm[WG / 64];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double m = sm[0];
-    for (int i = 1; i < WG / 64; i++) m = fmax(m, sm[i]);
-    atomicMax(out, (unsigned long long)__double_as_longlong(m));
-  }
-}
-
-// max |r| of the problem over the leaves into out[0] and, with fmax, max |f|
-// (the problem's f as solved) into out[1] (every block launched; parents skip)
-template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_resmax(FmgDev g, unsigned long long* out, int with_f) {
-  const int b = ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
-  if (g.chi[CS * b] >= 0) return;  // uniform per workgroup
-  double mr = 0.0, mf = 0.0;
-  if constexpr (ND == 2) {
-    FMG_PLANES(ND) {
-      const int c[3] = {tx, ty, tz};
-      const double r = residual<ND>(g, b, c);
-      const double f = g.fu[(size_t)b * ncb<ND>() + cidx(c)];
+  if (refined) {
+    const int per = WG / NF;  // faces at a time
+    for (int face = blockIdx.y * per + threadIdx.x / NF; face < 2 * ND; face += gridDim.y * per) {
+      if (!(refined >> face & 1)) continue;
+      int c[1][3];
+      face_coord<ND>(face, threadIdx.x & (NF - 1), c[0]);
+      const size_t i = (size_t)b * NCB + cidx(c[0]);
+      const double uv = g.u[i];
+      double a;
+      apply_k<ND, 1, true>(g, b, true, c, &uv, &a);
+      const double r = g.fu[i] - a;
       mr = fmax(mr, isnan(r) ? INFINITY : fabs(r));
-      mf = fmax(mf, isnan(f) ? INFINITY : fabs(f));
-    }
-  } else {
-    // residual() four planes at a time (stencil_k with the problem's rules)
-    constexpr int K = 4;
-    const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
-    const double ih2 = g.ih2[g.lvl[b]];
-    for (int z0 = 0; z0 < NB; z0 += K) {
-      int c[K][3];
-      double fv[K], uv[K], sc[K], sw[K];
-#pragma unroll
-      for (int k = 0; k < K; k++) {
-        c[k][0] = tx;
-        c[k][1] = ty;
-        c[k][2] = z0 + k;
-        const size_t i = (size_t)b * ncb<3>() + cidx(c[k]);
-        fv[k] = g.fu[i];
-        uv[k] = g.u[i];
-      }
-      stencil_k<3, K>(g, b, true, c, sc, sw);
-#pragma unroll
-      for (int k = 0; k < K; k++) {
-        const double r = fv[k] - (ih2 * (sc[k] + sw[k] * uv[k] - (2.0 * 3) * uv[k]) - g.lam * uv[k]);
-        mr = fmax(mr, isnan(r) ? INFINITY : fabs(r));
-        mf = fmax(mf, isnan(fv[k]) ? INFINITY : fabs(fv[k]));
-      }
     }
   }
-  fold_max(mr, out);
+  double* out = g.uo + (size_t)b * NCB;
+  mr = wg_max(mr);
+  if (threadIdx.x == 0) out[blockIdx.y] = mr;
   if (with_f) {
     __syncthreads();
-    fold_max(mf, out + 1);
+    mf = wg_max(mf);
+    if (threadIdx.x == 0) out[2 + blockIdx.y] = mf;
+  }
+}
+
+// the maxima of all leaves into two host words
+template <int ND>
+__global__ void __launch_bounds__(1024) k_fmg_resmax_all(FmgDev g, const int* leafblk, int n, int parts, int with_f,
+                                                         double* host) {
+  double mr = 0.0, mf = 0.0;
+  for (int k = threadIdx.x; k < n; k += 1024) {
+    const double* w = g.uo + (size_t)leafblk[k] * ncb<ND>();
+    for (int p = 0; p < parts; p++) {
+      mr = fmax(mr, w[p]);
+      if (with_f) mf = fmax(mf, w[2 + p]);
+    }
+  }
+  mr = wg_max(mr);
+  __syncthreads();
+  mf = wg_max(mf);
+  if (threadIdx.x == 0) {
+    host[0] = mr;
+    host[1] = mf;
   }
 }
 
@@ -726,7 +787,9 @@ __global__ void __launch_bounds__(WG) k_fmg_leaves(FmgDev g, const int* leafblk,
   constexpr int NCB = ncb<ND>();
   const int k = blockIdx.x;
   for (int t = threadIdx.x; t < NCB; t += WG) {
-    const size_t i = (size_t)leafblk[k] * NCB + t, o = (size_t)k * NCB + t;
+    int c[3];
+    ncell(t, c);
+    const size_t i = (size_t)leafblk[k] * NCB + cidx(c), o = (size_t)k * NCB + t;
     if (dir == 0) {
       g.f[i] = f[o];
       g.fu[i] = f[o];
@@ -820,7 +883,7 @@ __global__ void __launch_bounds__(WG) k_fmg_diff(FmgDev g, const int* leafblk, i
     const int c[3] = {tx, ty, tz};
     const double v =
         (face_value<ND>(g, b, c, 2 * d + 1) - face_value<ND>(g, b, c, 2 * d)) * (0.5 * g.rh[g.lvl[b]]);
-    const size_t o = (size_t)blockIdx.x * NCB + cidx(c);
+    const size_t o = (size_t)blockIdx.x * NCB + nidx(c);
     out[o] = acc ? out[o] + v : v;
   }
 }
@@ -859,8 +922,11 @@ __device__ __forceinline__ void react(const RdF& p, double u, double v, double& 
 template <int ND>
 __global__ void __launch_bounds__(WG) k_fmg_load(FmgDev g, const int* leafblk, const double* w) {
   constexpr int NCB = ncb<ND>();
-  for (int t = threadIdx.x; t < NCB; t += WG)
-    g.u[(size_t)leafblk[blockIdx.x] * NCB + t] = w[(size_t)blockIdx.x * NCB + t];
+  for (int t = threadIdx.x; t < NCB; t += WG) {
+    int c[3];
+    ncell(t, c);
+    g.u[(size_t)leafblk[blockIdx.x] * NCB + cidx(c)] = w[(size_t)blockIdx.x * NCB + t];
+  }
 }
 
 // D lap(w) at the leaf cells of the loaded field (the problem's rules; g.lam = 0)
@@ -868,7 +934,7 @@ template <int ND>
 __global__ void __launch_bounds__(WG) k_fmg_lap(FmgDev g, const int* leafblk, double D, double* out) {
   FMG_PLANES(ND) {
     const int c[3] = {tx, ty, tz};
-    out[(size_t)blockIdx.x * ncb<ND>() + cidx(c)] = D * apply_cell<ND>(g, leafblk[blockIdx.x], true, c);
+    out[(size_t)blockIdx.x * ncb<ND>() + nidx(c)] = D * apply_cell<ND>(g, leafblk[blockIdx.x], true, c);
   }
 }
 
@@ -1080,7 +1146,7 @@ amrv_mg_config base_config(const amrv_fmg_config* c) {
   mc.pre_sweeps = 2;
   mc.post_sweeps = 2;
   mc.use_graph = 0;
-  mc.smoother = AMRV_MG_PER_COLOUR;
+  mc.smoother = AMRV_MG_TILED;  // 2D: three launches a cycle at 128^2 instead of twelve (3D has per-colour launches only)
   mc.length = c->length;
   return mc;
 }
@@ -1186,7 +1252,7 @@ dim3 level_grid(const amrv_fmg* m, int l, int parts) {
 int sweeps(amrv_fmg* m, int l, int count) {
   for (int s = 0; s < count; s++)
     for (int c = 0; c < 2; c++)
-      FMG_LAUNCH(k_fmg_smooth, level_grid(m, l, 2), WG, m->g, m->T.lstart[l], c);
+      FMG_LAUNCH(k_fmg_smooth, level_grid(m, l, 2), m->nd == 3 ? WG : WG / 2, m->g, m->T.lstart[l], c);
   FMGCHK(hipGetLastError());
   return 0;
 }
@@ -1203,19 +1269,18 @@ int vcycle(amrv_fmg* m) {
   }
   if (int rc = sweeps(m, 1, pre)) return rc;
   const int n = m->cfg.base * NB;
-  FMG_LAUNCH(k_fmg_resid, level_grid(m, 1, 4), WG, m->g, m->T.lstart[1]);
-  FMG_LAUNCH(k_fmg_to_grid, nblocks(m, 1), WG, m->g, m->T.lstart[1], n, m->fgrid, m->vgrid);
+  FMG_LAUNCH(k_fmg_resid_grid, level_grid(m, 1, 4), WG, m->g, m->T.lstart[1], n, m->fgrid, m->vgrid);
   FMGCHK(hipGetLastError());
   // the level-1 correction: one of the uniform solver's V-cycles from zero
   // (it cuts the error by 20 or more; solved as a correction, what is left
   // shrinks with the residual from cycle to cycle), enqueued without a host
   // wait
   if (int rc = amrv::mg_enqueue_correction(m->base, m->fgrid, m->vgrid, m->g.lam, 1, true)) return rc;
-  FMG_LAUNCH(k_fmg_from_grid, nblocks(m, 1), WG, m->g, m->T.lstart[1], n, m->vgrid);
+  FMG_LAUNCH(k_fmg_from_grid, nblocks(m, 1), m->nd == 3 ? WG : WG / 2, m->g, m->T.lstart[1], n, m->vgrid);
   FMGCHK(hipGetLastError());
   if (int rc2 = sweeps(m, 1, post)) return rc2;
   for (int l = 2; l <= L; l++) {
-    FMG_LAUNCH(k_fmg_prolong, nblocks(m, l), WG, m->g, m->T.lstart[l]);
+    FMG_LAUNCH(k_fmg_prolong, dim3(nblocks(m, l), m->nd == 3 ? 3 : 2), m->nd == 3 ? WG : WG / 2, m->g, m->T.lstart[l]);
     FMGCHK(hipGetLastError());
     if (int rc2 = sweeps(m, l, post)) return rc2;
   }
@@ -1224,13 +1289,14 @@ int vcycle(amrv_fmg* m) {
 
 // max |r| over the leaves (and, with fmax, max |f| of the problem as solved)
 int norms(amrv_fmg* m, double* res, double* fmax) {
-  hipLaunchKernelGGL(k_fmg_zero2, dim3(1), dim3(64), 0, m->st, m->red);
-  FMG_LAUNCH(k_fmg_resmax, m->T.nblk, WG, m->g, m->red, fmax ? 1 : 0);
+  const int parts = m->nd == 3 ? 2 : 1, n = (int)m->cfg.nleaves;
+  double* host = reinterpret_cast<double*>(m->hred);
+  FMG_LAUNCH(k_fmg_resmax, dim3(n, parts), WG, m->g, m->leafblk, fmax ? 1 : 0);
+  FMG_LAUNCH(k_fmg_resmax_all, 1, 1024, m->g, m->leafblk, n, parts, fmax ? 1 : 0, host);
   FMGCHK(hipGetLastError());
-  FMGCHK(hipMemcpyAsync(m->hred, m->red, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, m->st));
   FMGCHK(hipStreamSynchronize(m->st));
-  *res = bits_to_double(m->hred[0]);
-  if (fmax) *fmax = bits_to_double(m->hred[1]);
+  *res = host[0];
+  if (fmax) *fmax = host[1];
   return 0;
 }
 
@@ -1320,7 +1386,7 @@ int amrv_fmg_create(const amrv_fmg_config* cfg, const int32_t* leaf_level, const
     return rc;
   }
   // the level-1 grid is the uniform solver's own right-hand side and
-  // solution: k_fmg_to_grid fills the one and zeroes the other
+  // solution: k_fmg_resid_grid fills the one and zeroes the other
   amrv::mg_correction_grids(m->base, &m->fgrid, &m->vgrid);
   // parents start from zero (every parent is restricted before it is read)
   e = hipMemsetAsync(g.u, 0, sizeof(double) * m->ncb * (size_t)T.nblk, m->st);
@@ -1356,6 +1422,7 @@ int amrv_fmg_solve(amrv_fmg* m, const double* f, double* phi, double lambda, dou
   if (!(tol > 0.0) || max_cycles < 0) return set_error(AMRV_EINVAL, "tol must be > 0 and max_cycles >= 0");
   m->g.lam = lambda;
   FMG_LAUNCH(k_fmg_leaves, m->cfg.nleaves, WG, m->g, m->leafblk, f, phi, 0);
+  FMG_LAUNCH(k_fmg_ghosts, dim3(m->cfg.nleaves, m->nd == 3 ? 2 : 1), WG, m->g, m->leafblk);
   FMGCHK(hipGetLastError());
   // Poisson: lap has the constants as null space and its area-weighted sums
   // vanish, so the problem solved is lap(phi) = f - mean(f), and phi is

@@ -1440,9 +1440,9 @@ void enqueue_norms_nd(amrv_mg* m, int with_f) {
     hipLaunchKernelGGL((k_mg_resnorm<ND, false>), dim3(m->nb_init, g.nf), dim3(256), 0, m->st, g, with_f);
 }
 
-// one V-cycle, ending with the residual norms of its result
+// one V-cycle, ending (norms) with the residual norms of its result
 template <int ND>
-void enqueue_vcycle_nd(amrv_mg* m) {
+void enqueue_vcycle_nd(amrv_mg* m, bool norms) {
   const MgDev& g = m->g;
   const int nf = g.nf;
   const int pre = m->cfg.pre_sweeps, post = m->cfg.post_sweeps;
@@ -1480,7 +1480,7 @@ void enqueue_vcycle_nd(amrv_mg* m) {
   if (tiled(m)) {
     for (int l = m->tail - 1; l >= 0; l--)
       hipLaunchKernelGGL(k_mg_up2d, dim3((g.n[l] / TS) * (g.n[l] / TS), nf), dim3(TT), 0, m->st, g, l, post,
-                         l == 0 ? 1 : 0);
+                         l == 0 && norms ? 1 : 0);
     return;  // the finest level's up launch folded the norms
   }
   for (int l = m->tail - 1; l >= 0; l--) {
@@ -1494,14 +1494,14 @@ void enqueue_vcycle_nd(amrv_mg* m) {
           hipLaunchKernelGGL((k_mg_smooth<ND, false>), dim3(blocks_of(g.cells[l] >> 1), nf), dim3(256), 0, m->st, g,
                              l, c);
   }
-  enqueue_norms_nd<ND>(m, 0);
+  if (norms) enqueue_norms_nd<ND>(m, 0);
 }
 
-void enqueue_vcycle(amrv_mg* m) {
+void enqueue_vcycle(amrv_mg* m, bool norms = true) {
   if (m->g.nd == 2)
-    enqueue_vcycle_nd<2>(m);
+    enqueue_vcycle_nd<2>(m, norms);
   else
-    enqueue_vcycle_nd<3>(m);
+    enqueue_vcycle_nd<3>(m, norms);
 }
 
 // matrix: a V-cycle follows (else the explicit steps, which use its memory)
@@ -1646,8 +1646,8 @@ int mg_enqueue_correction(amrv_mg* m, const double* f, double* out, double lambd
   const size_t bytes = (size_t)m->g.cells[0] * sizeof(double);
   if (f != m->g.f[0][0]) MGCHK(hipMemcpyAsync(m->g.f[0][0], f, bytes, hipMemcpyDeviceToDevice, m->st));
   if (!e_zeroed) MGCHK(hipMemsetAsync(m->g.phi[0][0], 0, bytes, m->st));
-  for (int c = 0; c < cycles; c++)
-    if (int rc = launch_cycle(m)) return rc;
+  for (int c = 0; c < cycles; c++) enqueue_vcycle(m, false);  // no host check: no residual norms
+  MGCHK(hipGetLastError());
   if (out != m->g.phi[0][0]) MGCHK(hipMemcpyAsync(out, m->g.phi[0][0], bytes, hipMemcpyDeviceToDevice, m->st));
   return 0;
 }
