@@ -391,9 +391,13 @@ __host__ __device__ inline double prolong_delta(const FmgDev& g, int b, const in
   return d;
 }
 
-// index of cell c of level-1 block b in the n^ND grid
+// index of cell c of level-1 block b in the n^ND grid (in split order: 3D)
 template <int ND>
-__host__ __device__ inline size_t grid_index(const FmgDev& g, int b, const int* c, int n) {
+__device__ inline size_t grid_index(const FmgDev& g, int b, const int* c, int n, bool split) {
+  if constexpr (ND == 3)
+    if (split)
+      return amrv::split_idx<3>(g.ij[TS * b] * NB + c[0], g.ij[TS * b + 1] * NB + c[1], g.ij[TS * b + 2] * NB + c[2],
+                                31 - __clz(n));
   size_t i = 0;
 #pragma unroll
   for (int e = ND - 1; e >= 0; e--) i = i * n + (size_t)(g.ij[TS * b + e] * NB + c[e]);
@@ -464,12 +468,13 @@ __global__ void __launch_bounds__(WG) k_fmg_ghosts(FmgDev g, const int* leafblk)
 // the residual of the relaxation on level 1, written to the n^ND grid as the
 // correction problem L(e) = r, from e = 0
 template <int ND>
-__global__ void __launch_bounds__(WG) k_fmg_resid_grid(FmgDev g, int b0, int n, double* fgrid, double* vgrid) {
+__global__ void __launch_bounds__(WG) k_fmg_resid_grid(FmgDev g, int b0, int n, bool split, double* fgrid,
+                                                       double* vgrid) {
   const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
   if constexpr (ND == 2) {
     const int b = b0 + blockIdx.x;
     const int c[3] = {tx, ty, 0};
-    const size_t gi = grid_index<2>(g, b, c, n);
+    const size_t gi = grid_index<2>(g, b, c, n, split);
     fgrid[gi] = g.f[(size_t)b * ncb<2>() + cidx(c)] - apply_cell<2>(g, b, false, c);
     vgrid[gi] = 0.0;
   } else {
@@ -492,7 +497,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resid_grid(FmgDev g, int b0, int n, 
       apply_k<3, K, true>(g, b, false, c, uv, a);
 #pragma unroll
       for (int k = 0; k < K; k++) {
-        const size_t gi = grid_index<3>(g, b, c[k], n);
+        const size_t gi = grid_index<3>(g, b, c[k], n, split);
         fgrid[gi] = fv[k] - a[k];
         vgrid[gi] = 0.0;
       }
@@ -661,12 +666,13 @@ __global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_prolong(FmgDev g,
 
 // the level-1 correction, on colour 1 only (as k_fmg_prolong)
 template <int ND>
-__global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_from_grid(FmgDev g, int b0, int n, const double* vgrid) {
+__global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_from_grid(FmgDev g, int b0, int n, bool split,
+                                                                             const double* vgrid) {
   const int b = b0 + blockIdx.x;
   const int hx = threadIdx.x & 7, ty = (threadIdx.x >> 3) & (NB - 1), pz = ND == 3 ? threadIdx.x >> 7 : 0;
   for (int tz = pz; tz < nplanes<ND>(); tz += 2) {
     const int c[3] = {2 * hx + ((ty + tz + 1) & 1), ty, tz};
-    g.u[(size_t)b * ncb<ND>() + cidx(c)] += vgrid[grid_index<ND>(g, b, c, n)];
+    g.u[(size_t)b * ncb<ND>() + cidx(c)] += vgrid[grid_index<ND>(g, b, c, n, split)];
   }
 }
 
@@ -1201,6 +1207,7 @@ struct amrv_fmg {
   int* leafblk = nullptr;
   double* fgrid = nullptr;
   double* vgrid = nullptr;
+  bool grid_split = false;  // fgrid and vgrid in split order
   double* tmp[8] = {};  // leaf fields of the reaction-diffusion steps
   double* part = nullptr;  // per-leaf area-weighted sums, then [nleaves] = their mean
   double area = 0.0;       // L^nd (the domain's area or volume)
@@ -1269,14 +1276,14 @@ int vcycle(amrv_fmg* m) {
   }
   if (int rc = sweeps(m, 1, pre)) return rc;
   const int n = m->cfg.base * NB;
-  FMG_LAUNCH(k_fmg_resid_grid, level_grid(m, 1, 4), WG, m->g, m->T.lstart[1], n, m->fgrid, m->vgrid);
+  FMG_LAUNCH(k_fmg_resid_grid, level_grid(m, 1, 4), WG, m->g, m->T.lstart[1], n, m->grid_split, m->fgrid, m->vgrid);
   FMGCHK(hipGetLastError());
   // the level-1 correction: one of the uniform solver's V-cycles from zero
   // (it cuts the error by 20 or more; solved as a correction, what is left
   // shrinks with the residual from cycle to cycle), enqueued without a host
   // wait
   if (int rc = amrv::mg_enqueue_correction(m->base, m->fgrid, m->vgrid, m->g.lam, 1, true)) return rc;
-  FMG_LAUNCH(k_fmg_from_grid, nblocks(m, 1), m->nd == 3 ? WG : WG / 2, m->g, m->T.lstart[1], n, m->vgrid);
+  FMG_LAUNCH(k_fmg_from_grid, nblocks(m, 1), m->nd == 3 ? WG : WG / 2, m->g, m->T.lstart[1], n, m->grid_split, m->vgrid);
   FMGCHK(hipGetLastError());
   if (int rc2 = sweeps(m, 1, post)) return rc2;
   for (int l = 2; l <= L; l++) {
@@ -1387,7 +1394,7 @@ int amrv_fmg_create(const amrv_fmg_config* cfg, const int32_t* leaf_level, const
   }
   // the level-1 grid is the uniform solver's own right-hand side and
   // solution: k_fmg_resid_grid fills the one and zeroes the other
-  amrv::mg_correction_grids(m->base, &m->fgrid, &m->vgrid);
+  amrv::mg_correction_grids(m->base, &m->fgrid, &m->vgrid, &m->grid_split);
   // parents start from zero (every parent is restricted before it is read)
   e = hipMemsetAsync(g.u, 0, sizeof(double) * m->ncb * (size_t)T.nblk, m->st);
   if (e == hipSuccess) e = hipStreamSynchronize(m->st);

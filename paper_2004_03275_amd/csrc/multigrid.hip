@@ -41,6 +41,8 @@
 
 namespace {
 
+using amrv::split_idx;
+
 constexpr int MG_MAXL = 14;   // n <= 8192: 13 levels down to 2 cells per side
 constexpr int NFMAX = 2;
 constexpr int TAIL_CELLS = 4096;
@@ -70,6 +72,7 @@ struct MgDev {
                                 // second buffer (down writes it, up reads it)
   const double* par;
   double* cmat[NFMAX];        // [64 columns][64 cells]: the coarse matrix (null: grids below TAIL_CELLS)
+  int split0;                 // level 0 (and every level above the tail) in split order
   unsigned long long* hpart;  // pinned host slots of per-block maxima: [2][NFMAX][maxb]
   int maxb;
 };
@@ -643,16 +646,9 @@ __device__ __forceinline__ void coarse_exact(double* P, const double* F, int bc,
   if (threadIdx.x < C) P[k] = v;
 }
 
-// A tail level in LDS holds its two colours in two halves (the cells of one
-// colour are then consecutive: two doubles apart, as in the natural order, they
-// meet two-way bank conflicts).  The cells 2 xh, 2 xh + 1 of a row are a pair,
-// p = row * n / 2 + xh; each half holds one cell of the pair at p, so both
-// colours of a pair share their addresses up to the half.
-template <int ND>
-__device__ __forceinline__ int tail_idx(int x, int y, int z, int lg) {
-  const int i = ND == 3 ? (((z << lg) + y) << lg) + x : (y << lg) + x;
-  return (i >> 1) + (((x + y + z) & 1) << (ND * lg - 1));
-}
+// A tail level in LDS holds its two colours in two halves (mg_internal.hpp: the
+// cells of one colour are then consecutive; two doubles apart, as in the natural
+// order, they meet two-way bank conflicts).
 
 // LDS indices of a thread's pairs and right-hand sides, formed once per level
 // and kept in registers over its sweeps, so that a cell update is its
@@ -787,7 +783,7 @@ __device__ __forceinline__ void tail_restrict(const double* P, const double* F, 
     }
   const double fc = s * (ND == 3 ? 0.125 : 0.25);
   if constexpr (SPLIT) {
-    const int i = tail_idx<ND>(xc, yc, zc, lgc);
+    const int i = split_idx<ND>(xc, yc, zc, lgc);
     Fc[i] = fc;
     Pc[i] = ((xc + yc + zc) & 1) ? 0.0 : (0.0 - fc) * idgc;
   } else {
@@ -795,56 +791,61 @@ __device__ __forceinline__ void tail_restrict(const double* P, const double* F, 
   }
 }
 
-// the interpolated correction (prolong_cell's weights and order) where the
-// half-sweep of colour 0 that follows reads it: every cell of colour 1 and, with
-// Neumann walls (a cell at one sums its own old value), both cells of every
-// pair, which share their coarse rows; the others of colour 0 are recomputed
-// without their old values
+// the interpolated correction (prolong_cell's weights and order) added to the
+// colour-1 cell of pair p and, with both, to its colour-0 cell; coarse level in
+// split or natural order
+template <int ND, bool SPLIT>
+__device__ __forceinline__ void prolong_pair(double* P, const double* Pc, int p, int lg, int bc, bool both) {
+  const int n = 1 << lg, half = 1 << (ND * lg - 1), lgc = lg - 1, nc = n >> 1;
+  const int xc = p & (nc - 1), r = p >> lgc, y = ND == 3 ? r & (n - 1) : r, z = ND == 3 ? r >> lg : 0;
+  const bool odd = (y + z) & 1;  // the cell of colour 1 is the pair's left one
+  const int xl = im(xc, nc, bc), xr = ip(xc, nc, bc);
+  const int xa = odd ? xl : xr, xb = odd ? xr : xl;  // toward the cell of colour 1, of colour 0
+  auto row = [&](int yy, int zz, double& a, double& b) {
+    const int base = ND == 3 ? ((zz << lgc) + yy) << lgc : yy << lgc;
+    const int s = (yy + zz) & 1;
+    auto e = [&](int x) {
+      if constexpr (SPLIT) return Pc[((base + x) >> 1) + (((x + s) & 1) << (ND * lgc - 1))];
+      return Pc[base + x];
+    };
+    const double c = 0.75 * e(xc);
+    a = c + 0.25 * e(xa);
+    b = both ? c + 0.25 * e(xb) : 0.0;
+  };
+  const int yc = y >> 1, yn = (y & 1) ? ip(yc, nc, bc) : im(yc, nc, bc);
+  auto plane = [&](int zz, double& a, double& b) {
+    double a0, b0, a1, b1;
+    row(yc, zz, a0, b0);
+    row(yn, zz, a1, b1);
+    a = 0.75 * a0 + 0.25 * a1;
+    b = 0.75 * b0 + 0.25 * b1;
+  };
+  double d1, d0;
+  if constexpr (ND == 2) {
+    plane(0, d1, d0);
+  } else {
+    const int zc = z >> 1, zn = (z & 1) ? ip(zc, nc, bc) : im(zc, nc, bc);
+    double a0, b0, a1, b1;
+    plane(zc, a0, b0);
+    plane(zn, a1, b1);
+    d1 = 0.75 * a0 + 0.25 * a1;
+    d0 = 0.75 * b0 + 0.25 * b1;
+  }
+  P[half + p] += d1;
+  if (both) P[p] += d0;
+}
+
+// on a tail level where the half-sweep of colour 0 that follows reads it: every
+// cell of colour 1 and, with Neumann walls (a cell at one sums its own old
+// value), both cells of every pair, which share their coarse rows; the others
+// of colour 0 are recomputed without their old values
 template <int ND, int K, bool SPLIT>
 __device__ __forceinline__ void tail_prolong(double* P, const double* Pc, int t0, int lg, int bc) {
   constexpr int NT = tail_threads<ND>();
-  const int n = 1 << lg, half = 1 << (ND * lg - 1), lgc = lg - 1, nc = n >> 1;
-  const bool both = bc != AMRV_MG_PERIODIC;
 #pragma unroll
   for (int k = 0; k < K; k++) {
     const int p = t0 + k * NT;
-    if (p >= half) continue;
-    const int xc = p & (nc - 1), r = p >> lgc, y = ND == 3 ? r & (n - 1) : r, z = ND == 3 ? r >> lg : 0;
-    const bool odd = (y + z) & 1;  // the cell of colour 1 is the pair's left one
-    const int xl = im(xc, nc, bc), xr = ip(xc, nc, bc);
-    const int xa = odd ? xl : xr, xb = odd ? xr : xl;  // toward the cell of colour 1, of colour 0
-    auto row = [&](int yy, int zz, double& a, double& b) {
-      const int base = ND == 3 ? ((zz << lgc) + yy) << lgc : yy << lgc;
-      const int s = (yy + zz) & 1;
-      auto e = [&](int x) {
-        if constexpr (SPLIT) return Pc[((base + x) >> 1) + (((x + s) & 1) << (ND * lgc - 1))];
-        return Pc[base + x];
-      };
-      const double c = 0.75 * e(xc);
-      a = c + 0.25 * e(xa);
-      b = both ? c + 0.25 * e(xb) : 0.0;
-    };
-    const int yc = y >> 1, yn = (y & 1) ? ip(yc, nc, bc) : im(yc, nc, bc);
-    auto plane = [&](int zz, double& a, double& b) {
-      double a0, b0, a1, b1;
-      row(yc, zz, a0, b0);
-      row(yn, zz, a1, b1);
-      a = 0.75 * a0 + 0.25 * a1;
-      b = 0.75 * b0 + 0.25 * b1;
-    };
-    double d1, d0;
-    if constexpr (ND == 2) {
-      plane(0, d1, d0);
-    } else {
-      const int zc = z >> 1, zn = (z & 1) ? ip(zc, nc, bc) : im(zc, nc, bc);
-      double a0, b0, a1, b1;
-      plane(zc, a0, b0);
-      plane(zn, a1, b1);
-      d1 = 0.75 * a0 + 0.25 * a1;
-      d0 = 0.75 * b0 + 0.25 * b1;
-    }
-    P[half + p] += d1;
-    if (both) P[p] += d0;
+    if (p < (1 << (ND * lg - 1))) prolong_pair<ND, SPLIT>(P, Pc, p, lg, bc, bc != AMRV_MG_PERIODIC);
   }
 }
 
@@ -1173,6 +1174,176 @@ __global__ void __launch_bounds__(TAIL_THREADS) k_mg_tail_var(MgDev g, int top, 
   for (int i = threadIdx.x; i < g.cells[top]; i += blockDim.x) g.phi[f][top][i] = P(top)[i];
 }
 
+// ---- 3D levels above the tail (constant coefficient): phi and f with the two
+// colours in two halves (split_idx), so that a colour sweep reads one half of phi
+// and one of f and writes one; in the natural order every line was moved for
+// half its values (128^3, two fields: 20.9 -> 10.4 us a colour sweep, 4.8 TB/s) ---------------------
+
+// workgroup i of n to a contiguous range per XCD (workgroups are dealt to the 8
+// XCDs round robin), so that neighbouring rows and planes share an L2
+__device__ __forceinline__ int xcd_chunk(int i, int n) {
+  const int q = n >> 3, r = n & 7, x = i & 7;
+  return x * q + (x < r ? x : r) + (i >> 3);
+}
+
+// a colour sweep, two pairs (16-byte loads) per thread
+__global__ void __launch_bounds__(256) k_mg3_smooth(MgDev g, int l, int c) {
+  const int f = blockIdx.y, n = g.n[l], lg = g.lg[l], nh = n >> 1, half = 1 << (3 * lg - 1);
+  const int p = 2 * (xcd_chunk(blockIdx.x, gridDim.x) * 256 + threadIdx.x);
+  if (p >= half) return;
+  const bool per = g.bc == AMRV_MG_PERIODIC;
+  const int xh = p & (nh - 1), r = p >> (lg - 1), y = r & (n - 1), z = r >> lg;
+  double* own = g.phi[f][l] + (c ? half : 0);
+  const double* oth = g.phi[f][l] + (c ? 0 : half);
+  auto two = [](const double* a) { return *reinterpret_cast<const double2*>(a); };
+  // a neighbour row: the other colour, or (a Neumann wall) the cells themselves
+  auto at = [&](bool edge, int in, int wrap) { return two(!edge ? oth + p + in : (per ? oth + p + wrap : own + p)); };
+  const int zs = 1 << (2 * lg - 1);
+  const double2 fv = two(g.f[f][l] + (c ? half : 0) + p);
+  const double2 in = two(oth + p);
+  const double2 ym = at(y == 0, -nh, (n - 1) * nh), yp = at(y == n - 1, nh, -(n - 1) * nh);
+  const double2 zm = at(z == 0, -zs, half - zs), zp = at(z == n - 1, zs, zs - half);
+  // the outer x neighbours: of a pair's right cells p + 1, p + 2, of its left
+  // cells p - 1, p
+  const bool right = (y + z + c) & 1;
+  const double* q = right ? (xh + 2 == nh ? (per ? oth + p + 2 - nh : own + p + 1) : oth + p + 2)
+                          : (xh == 0 ? (per ? oth + p + nh - 1 : own + p) : oth + p - 1);
+  const double o = *q;
+  const double o0 = right ? in.y : o, o1 = right ? o : in.x;
+  const double ih2 = par_ih2(g, l), idg = par_idiag(g, f, l);
+  double2 v;
+  v.x = ((((in.x + o0) + (ym.x + yp.x)) + (zm.x + zp.x)) * ih2 - fv.x) * idg;
+  v.y = ((((in.y + o1) + (ym.y + yp.y)) + (zm.y + zp.y)) * ih2 - fv.y) * idg;
+  *reinterpret_cast<double2*>(own + p) = v;
+}
+
+// coarse right-hand side, and (a level above the tail) its values after the
+// first half-sweep from zero (tail_restrict)
+__global__ void __launch_bounds__(256) k_mg3_restrict(MgDev g, int l, int split) {
+  const int f = blockIdx.y;
+  const int t = xcd_chunk(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (t >= g.cells[l + 1]) return;
+  const double ih2 = par_ih2(g, l), lam = par_lam(g, f);
+  if (split)
+    tail_restrict<3, true>(g.phi[f][l], g.f[f][l], g.phi[f][l + 1], g.f[f][l + 1], t, g.lg[l], g.bc, ih2, lam,
+                           par_idiag(g, f, l + 1));
+  else
+    tail_restrict<3, false>(g.phi[f][l], g.f[f][l], nullptr, g.f[f][l + 1], t, g.lg[l], g.bc, ih2, lam, 0.0);
+}
+
+// the correction on colour 1 (and colour 0 at a Neumann wall: tail_prolong), one
+// coarse cell per thread: its 8 children from the 27 coarse values around it,
+// interpolated along x, y, z in turn as prolong_cell does (per pair of cells 12
+// loads for two: 26.5 -> 20.3 us at 128^3, two fields)
+template <bool SPLIT>
+__global__ void __launch_bounds__(256) k_mg3_prolong(MgDev g, int l) {
+  const int f = blockIdx.y, n = g.n[l], lg = g.lg[l], nc = n >> 1, lgc = lg - 1, bc = g.bc;
+  const int t = xcd_chunk(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (t >= g.cells[l + 1]) return;
+  int xc, yc, zc;
+  decode<3>(t, nc, lgc, xc, yc, zc);
+  const double* e = g.phi[f][l + 1];
+  double* P = g.phi[f][l];
+  const int half = 1 << (3 * lg - 1), pz = 1 << (2 * lg - 1);
+  const int p0 = (((2 * zc << lg) + 2 * yc) << lgc) + xc;
+  double w[2][2];  // the children of colour 1, loaded with the coarse values
+#pragma unroll
+  for (int dz = 0; dz < 2; dz++)
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++) w[dz][dy] = P[half + p0 + dy * nc + dz * pz];
+  const int xs[3] = {im(xc, nc, bc), xc, ip(xc, nc, bc)}, ys[3] = {im(yc, nc, bc), yc, ip(yc, nc, bc)},
+            zs[3] = {im(zc, nc, bc), zc, ip(zc, nc, bc)};
+  double a[3][3][2];  // along x: the left and right child's value per coarse row
+#pragma unroll
+  for (int k = 0; k < 3; k++)
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+      const int base = ((zs[k] << lgc) + ys[j]) << lgc, s = (ys[j] + zs[k]) & 1;
+      auto at = [&](int x) { return SPLIT ? e[((base + x) >> 1) + (((x + s) & 1) << (3 * lgc - 1))] : e[base + x]; };
+      const double c = 0.75 * at(xs[1]);
+      a[k][j][0] = c + 0.25 * at(xs[0]);
+      a[k][j][1] = c + 0.25 * at(xs[2]);
+    }
+  auto child = [&](int dx, int dy, int dz) {
+    const int jn = dy ? 2 : 0, kn = dz ? 2 : 0;
+    const double q0 = 0.75 * a[1][1][dx] + 0.25 * a[1][jn][dx], q1 = 0.75 * a[kn][1][dx] + 0.25 * a[kn][jn][dx];
+    return 0.75 * q0 + 0.25 * q1;
+  };
+#pragma unroll
+  for (int dz = 0; dz < 2; dz++)
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++) P[half + p0 + dy * nc + dz * pz] = w[dz][dy] + child((dy + dz + 1) & 1, dy, dz);
+  if (bc == AMRV_MG_PERIODIC || !(xc == 0 || xc == nc - 1 || yc == 0 || yc == nc - 1 || zc == 0 || zc == nc - 1)) return;
+#pragma unroll
+  for (int dz = 0; dz < 2; dz++)
+#pragma unroll
+    for (int dy = 0; dy < 2; dy++) {
+      const int dx = (dy + dz) & 1, x = 2 * xc + dx, y = 2 * yc + dy, z = 2 * zc + dz;
+      if (x == 0 || x == n - 1 || y == 0 || y == n - 1 || z == 0 || z == n - 1)
+        P[p0 + dy * nc + dz * pz] += child(dx, dy, dz);
+    }
+}
+
+// the cells of pair p by colour: value and Laplacian (lap_at's sums and order)
+__device__ __forceinline__ void pair_lap3(const double* P, int p, int n, int lg, int bc, double ih2, double* w,
+                                          double* lap) {
+  const int nh = n >> 1, half = 1 << (3 * lg - 1), zs = 1 << (2 * lg - 1);
+  const bool per = bc == AMRV_MG_PERIODIC;
+  const int xh = p & (nh - 1), r = p >> (lg - 1), y = r & (n - 1), z = r >> lg;
+  const bool odd = (y + z) & 1;  // the cell of colour 0 is the pair's right one
+  w[0] = P[p];
+  w[1] = P[half + p];
+#pragma unroll
+  for (int c = 0; c < 2; c++) {
+    const double* own = P + (c ? half : 0);
+    const double* oth = P + (c ? 0 : half);
+    auto at = [&](bool edge, int in, int wrap) { return !edge ? oth[p + in] : (per ? oth[p + wrap] : own[p]); };
+    const bool right = c ? !odd : odd;
+    const double o = right ? at(xh == nh - 1, 1, 1 - nh) : at(xh == 0, -1, nh - 1);
+    const double ym = at(y == 0, -nh, (n - 1) * nh), yp = at(y == n - 1, nh, -(n - 1) * nh);
+    const double zm = at(z == 0, -zs, half - zs), zp = at(z == n - 1, zs, zs - half);
+    double a = ((o + w[1 - c]) - 2.0 * w[c]) * ih2;
+    a = a + ((ym + yp) - 2.0 * w[c]) * ih2;
+    lap[c] = a + ((zm + zp) - 2.0 * w[c]) * ih2;
+  }
+}
+
+__global__ void __launch_bounds__(256) k_mg3_resnorm(MgDev g, int with_f) {
+  const int f = blockIdx.y, n = g.n[0], lg = g.lg[0], half = g.cells[0] >> 1;
+  const double ih2 = par_ih2(g, 0), lam = par_lam(g, f);
+  unsigned long long br = 0, bf = 0;
+  for (int p = xcd_chunk(blockIdx.x, gridDim.x) * 256 + threadIdx.x; p < half; p += gridDim.x * 256) {
+    double w[2], lap[2];
+    pair_lap3(g.phi[f][0], p, n, lg, g.bc, ih2, w, lap);
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+      const double fv = g.f[f][0][(c ? half : 0) + p];
+      const double r = fv - (lap[c] - lam * w[c]);
+      const unsigned long long a = (unsigned long long)__double_as_longlong(fabs(r));
+      const unsigned long long b = (unsigned long long)__double_as_longlong(fabs(fv));
+      br = a > br ? a : br;
+      bf = b > bf ? b : bf;
+    }
+  }
+  fold_norms(g, f, br, bf, with_f);
+}
+
+// a natural-order field to and from a split array, one pair per thread
+__global__ void __launch_bounds__(256) k_mg3_reorder(int lg, const double* src, double* dst, int to_split) {
+  const int p = blockIdx.x * 256 + threadIdx.x, half = 1 << (3 * lg - 1);
+  if (p >= half) return;
+  const int n = 1 << lg, r = p >> (lg - 1);
+  const bool odd = ((r & (n - 1)) + (r >> lg)) & 1;  // the left cell's colour
+  if (to_split) {
+    const double2 v = reinterpret_cast<const double2*>(src)[p];
+    dst[p] = odd ? v.y : v.x;
+    dst[half + p] = odd ? v.x : v.y;
+  } else {
+    const double a = src[p], b = src[half + p];
+    reinterpret_cast<double2*>(dst)[p] = odd ? double2{b, a} : double2{a, b};
+  }
+}
+
 // ---- divergence control of the MHD runs (Sec. 2.4): lap(phi) = div B*,
 // B = B* - grad phi, central differences (w(+1) - w(-1)) * (n / 2L) ---------
 
@@ -1192,6 +1363,14 @@ __device__ __forceinline__ double cdiv(const double* b0, const double* b1, const
   return d;
 }
 
+// index in a level-0 array of phi or f of the cell of natural index t
+template <int ND>
+__device__ __forceinline__ int idx0(const MgDev& g, int t, int x, int y, int z) {
+  if constexpr (ND == 3)
+    if (g.split0) return split_idx<3>(x, y, z, g.lg[0]);
+  return t;
+}
+
 // right-hand side div B*, initial guess 0
 template <int ND>
 __global__ void __launch_bounds__(256) k_mg_divb(MgDev g, const double* b0, const double* b1, const double* b2,
@@ -1200,8 +1379,9 @@ __global__ void __launch_bounds__(256) k_mg_divb(MgDev g, const double* b0, cons
   if (t >= g.cells[0]) return;
   int x, y, z;
   decode<ND>(t, g.n[0], g.lg[0], x, y, z);
-  g.f[0][0][t] = cdiv<ND>(b0, b1, b2, x, y, z, g.n[0], g.bc, c);
-  g.phi[0][0][t] = 0.0;
+  const int o = idx0<ND>(g, t, x, y, z);
+  g.f[0][0][o] = cdiv<ND>(b0, b1, b2, x, y, z, g.n[0], g.bc, c);
+  g.phi[0][0][o] = 0.0;
 }
 
 template <int ND>
@@ -1211,9 +1391,11 @@ __global__ void __launch_bounds__(256) k_mg_gradsub(MgDev g, double* b0, double*
   int x, y, z;
   decode<ND>(t, g.n[0], g.lg[0], x, y, z);
   const double* phi = g.phi[0][0];
-  b0[t] = b0[t] - cdiff<ND>(phi, x, y, z, g.n[0], g.bc, 0, c);
-  b1[t] = b1[t] - cdiff<ND>(phi, x, y, z, g.n[0], g.bc, 1, c);
-  if constexpr (ND == 3) b2[t] = b2[t] - cdiff<ND>(phi, x, y, z, g.n[0], g.bc, 2, c);
+  const int n = g.n[0], bc = g.bc;
+  auto at = [&](int xx, int yy, int zz) { return phi[idx0<ND>(g, (zz * n + yy) * n + xx, xx, yy, zz)]; };
+  b0[t] = b0[t] - (at(ip(x, n, bc), y, z) - at(im(x, n, bc), y, z)) * c;
+  b1[t] = b1[t] - (at(x, ip(y, n, bc), z) - at(x, im(y, n, bc), z)) * c;
+  if constexpr (ND == 3) b2[t] = b2[t] - (at(x, y, ip(z, n, bc)) - at(x, y, im(z, n, bc))) * c;
 }
 
 // max |div B| into the host slots of row 0
@@ -1270,10 +1452,13 @@ __global__ void __launch_bounds__(256) k_rd_split_rhs(MgDev g, RdK p, const doub
   if (t >= g.cells[0]) return;
   double ru, rv;
   react(p, u[t], v[t], ru, rv);
-  g.f[0][0][t] = -par_lam(g, 0) * (u[t] + dt * ru);
-  g.f[1][0][t] = -par_lam(g, 1) * (v[t] + dt * rv);
-  g.phi[0][0][t] = u[t];
-  g.phi[1][0][t] = v[t];
+  int x, y, z;
+  decode<ND>(t, g.n[0], g.lg[0], x, y, z);
+  const int o = idx0<ND>(g, t, x, y, z);
+  g.f[0][0][o] = -par_lam(g, 0) * (u[t] + dt * ru);
+  g.f[1][0][o] = -par_lam(g, 1) * (v[t] + dt * rv);
+  g.phi[0][0][o] = u[t];
+  g.phi[1][0][o] = v[t];
 }
 
 // IMEX first stage: f = -lambda ((w + dt F0(w)) + (dt/2) D lap(w)), initial
@@ -1294,10 +1479,11 @@ __global__ void __launch_bounds__(256) k_rd_imex_rhs(MgDev g, RdK p, const doubl
   Eu[t] = ru + du;
   Ev[t] = rv + dv;
   const double hdt = 0.5 * dt;
-  g.f[0][0][t] = -par_lam(g, 0) * ((u[t] + dt * ru) + hdt * du);
-  g.f[1][0][t] = -par_lam(g, 1) * ((v[t] + dt * rv) + hdt * dv);
-  g.phi[0][0][t] = u[t] + dt * (ru + du);
-  g.phi[1][0][t] = v[t] + dt * (rv + dv);
+  const int o = idx0<ND>(g, t, x, y, z);
+  g.f[0][0][o] = -par_lam(g, 0) * ((u[t] + dt * ru) + hdt * du);
+  g.f[1][0][o] = -par_lam(g, 1) * ((v[t] + dt * rv) + hdt * dv);
+  g.phi[0][0][o] = u[t] + dt * (ru + du);
+  g.phi[1][0][o] = v[t] + dt * (rv + dv);
 }
 
 // IMEX second stage: w1 = w + (dt/2) (F(w) + F(w*)), w* = the solve's phi
@@ -1318,6 +1504,36 @@ __global__ void __launch_bounds__(256) k_rd_imex_final(MgDev g, RdK p, double* u
   const double hdt = 0.5 * dt;
   u[t] = u[t] + hdt * (Eu[t] + fu);
   v[t] = v[t] + hdt * (Ev[t] + fv);
+}
+
+// the same in 3D on split phi, one pair of cells per thread
+__global__ void __launch_bounds__(256) k_rd3_imex_final(MgDev g, RdK p, double* u, double* v, const double* Eu,
+                                                        const double* Ev, double dt) {
+  const int q = xcd_chunk(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (q >= (g.cells[0] >> 1)) return;
+  const int n = g.n[0], lg = g.lg[0], r = q >> (lg - 1);
+  const bool odd = ((r & (n - 1)) + (r >> lg)) & 1;  // the left cell's colour
+  const double ih2 = par_ih2(g, 0), hdt = 0.5 * dt;
+  double su[2], sv[2], lu[2], lv[2], fu[2], fv[2];
+  pair_lap3(g.phi[0][0], q, n, lg, g.bc, ih2, su, lu);
+  pair_lap3(g.phi[1][0], q, n, lg, g.bc, ih2, sv, lv);
+#pragma unroll
+  for (int c = 0; c < 2; c++) {
+    double ru, rv;
+    react(p, su[c], sv[c], ru, rv);
+    fu[c] = ru + p.Du * lu[c];
+    fv[c] = rv + p.Dv * lv[c];
+  }
+  double2* u2 = reinterpret_cast<double2*>(u) + q;
+  double2* v2 = reinterpret_cast<double2*>(v) + q;
+  const double2 eu = reinterpret_cast<const double2*>(Eu)[q], ev = reinterpret_cast<const double2*>(Ev)[q];
+  double2 a = *u2, b = *v2;
+  a.x = a.x + hdt * (eu.x + (odd ? fu[1] : fu[0]));
+  a.y = a.y + hdt * (eu.y + (odd ? fu[0] : fu[1]));
+  b.x = b.x + hdt * (ev.x + (odd ? fv[1] : fv[0]));
+  b.y = b.y + hdt * (ev.y + (odd ? fv[0] : fv[1]));
+  *u2 = a;
+  *v2 = b;
 }
 
 int blocks_of(int n) { return (n + 255) / 256; }
@@ -1434,6 +1650,10 @@ bool tiled(const amrv_mg* m) {
 template <int ND>
 void enqueue_norms_nd(amrv_mg* m, int with_f) {
   const MgDev& g = m->g;
+  if (ND == 3 && g.split0) {
+    hipLaunchKernelGGL(k_mg3_resnorm, dim3(m->nb_init, g.nf), dim3(256), 0, m->st, g, with_f);
+    return;
+  }
   if (m->var)
     hipLaunchKernelGGL((k_mg_resnorm<ND, true>), dim3(m->nb_init, g.nf), dim3(256), 0, m->st, g, with_f);
   else
@@ -1449,6 +1669,13 @@ void enqueue_vcycle_nd(amrv_mg* m, bool norms) {
   if (tiled(m)) {
     for (int l = 0; l < m->tail; l++)
       hipLaunchKernelGGL(k_mg_down2d, dim3((g.n[l] / TS) * (g.n[l] / TS), nf), dim3(TT), 0, m->st, g, l, pre);
+  } else if (ND == 3 && g.split0) {
+    for (int l = 0; l < m->tail; l++) {
+      for (int h = l ? 1 : 0; h < 2 * pre; h++)  // below level 0 the restriction made the first half-sweep
+        hipLaunchKernelGGL(k_mg3_smooth, dim3(blocks_of(g.cells[l] >> 2), nf), dim3(256), 0, m->st, g, l, h & 1);
+      hipLaunchKernelGGL(k_mg3_restrict, dim3(blocks_of(g.cells[l + 1]), nf), dim3(256), 0, m->st, g, l,
+                         l + 1 < m->tail ? 1 : 0);
+    }
   } else {
     for (int l = 0; l < m->tail; l++) {
       for (int s = 0; s < pre; s++)
@@ -1456,12 +1683,12 @@ void enqueue_vcycle_nd(amrv_mg* m, bool norms) {
           if (m->var)
             hipLaunchKernelGGL((k_mg_smooth<ND, true>), dim3(blocks_of(g.cells[l] >> 1), nf), dim3(256), 0, m->st, g,
                                l, c);
-          else
+          else if constexpr (ND == 2)
             hipLaunchKernelGGL((k_mg_smooth<ND, false>), dim3(blocks_of(g.cells[l] >> 1), nf), dim3(256), 0, m->st,
                                g, l, c);
       if (m->var)
         hipLaunchKernelGGL((k_mg_restrict<ND, true>), dim3(blocks_of(g.cells[l + 1]), nf), dim3(256), 0, m->st, g, l);
-      else
+      else if constexpr (ND == 2)
         hipLaunchKernelGGL((k_mg_restrict<ND, false>), dim3(blocks_of(g.cells[l + 1]), nf), dim3(256), 0, m->st, g,
                            l);
     }
@@ -1483,6 +1710,18 @@ void enqueue_vcycle_nd(amrv_mg* m, bool norms) {
                          l == 0 && norms ? 1 : 0);
     return;  // the finest level's up launch folded the norms
   }
+  if (ND == 3 && g.split0) {
+    for (int l = m->tail - 1; l >= 0; l--) {
+      if (l + 1 < m->tail)
+        hipLaunchKernelGGL(k_mg3_prolong<true>, dim3(blocks_of(g.cells[l + 1]), nf), dim3(256), 0, m->st, g, l);
+      else
+        hipLaunchKernelGGL(k_mg3_prolong<false>, dim3(blocks_of(g.cells[l + 1]), nf), dim3(256), 0, m->st, g, l);
+      for (int h = 0; h < 2 * post; h++)
+        hipLaunchKernelGGL(k_mg3_smooth, dim3(blocks_of(g.cells[l] >> 2), nf), dim3(256), 0, m->st, g, l, h & 1);
+    }
+    if (norms) enqueue_norms_nd<ND>(m, 0);
+    return;
+  }
   for (int l = m->tail - 1; l >= 0; l--) {
     hipLaunchKernelGGL(k_mg_prolong<ND>, dim3(blocks_of(g.cells[l]), nf), dim3(256), 0, m->st, g, l);
     for (int s = 0; s < post; s++)
@@ -1490,7 +1729,7 @@ void enqueue_vcycle_nd(amrv_mg* m, bool norms) {
         if (m->var)
           hipLaunchKernelGGL((k_mg_smooth<ND, true>), dim3(blocks_of(g.cells[l] >> 1), nf), dim3(256), 0, m->st, g,
                              l, c);
-        else
+        else if constexpr (ND == 2)
           hipLaunchKernelGGL((k_mg_smooth<ND, false>), dim3(blocks_of(g.cells[l] >> 1), nf), dim3(256), 0, m->st, g,
                              l, c);
   }
@@ -1630,8 +1869,9 @@ int run_cycles(amrv_mg* m, double tol, int max_cycles, int unchecked, int* cycle
 
 namespace amrv {
 
-int mg_correction_grids(amrv_mg* m, double** f, double** e) {
-  if (!m || !f || !e) return set_error(AMRV_EINVAL, "null argument");
+int mg_correction_grids(amrv_mg* m, double** f, double** e, bool* split) {
+  if (!m || !f || !e || !split) return set_error(AMRV_EINVAL, "null argument");
+  *split = m->g.split0 != 0;
   *f = m->g.f[0][0];
   *e = m->g.phi[0][0];
   return 0;
@@ -1641,6 +1881,8 @@ int mg_enqueue_correction(amrv_mg* m, const double* f, double* out, double lambd
   if (!m || !f || !out) return set_error(AMRV_EINVAL, "null argument");
   if (m->g.nf != 1 || m->var) return set_error(AMRV_EINVAL, "a correction solve needs one field and the constant coefficient");
   if (!(lambda >= 0.0) || !std::isfinite(lambda)) return set_error(AMRV_EINVAL, "lambda must be non-negative and finite");
+  if (m->g.split0 && (f != m->g.f[0][0] || out != m->g.phi[0][0]))
+    return set_error(AMRV_EINVAL, "a correction on split arrays works in the solver's own");
   if (m->par_nf != 1 || m->par_lam0 != lambda)
     if (int rc = set_params(m, &lambda)) return rc;
   const size_t bytes = (size_t)m->g.cells[0] * sizeof(double);
@@ -1704,6 +1946,7 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
   int tail = 0;
   while (g.cells[tail] > TAIL_CELLS) tail++;
   m->tail = tail;
+  g.split0 = g.nd == 3 && tail > 0;
   int off = 0;
   for (int l = tail; l < L.nlev; l++) {
     if (g.cells[l] > COARSE_CELLS) off += 2 * g.cells[l];
@@ -1728,7 +1971,7 @@ int amrv_mg_create(const amrv_mg_config* cfg, void* workspace, size_t bytes, voi
   if (e == hipSuccess)
     e = lds_limit(d2 ? reinterpret_cast<const void*>(k_mg_tail_var<2>) : reinterpret_cast<const void*>(k_mg_tail_var<3>),
                   m->tail_lds_var);
-  m->nb_init = std::min(blocks_of(g.cells[0]), 256);
+  m->nb_init = std::min(blocks_of(g.cells[0]), g.nd == 3 ? 1024 : 256);
   m->nb_cycle = tiled(m) ? (g.n[0] / TS) * (g.n[0] / TS) : m->nb_init;
   g.maxb = std::max(m->nb_init, m->nb_cycle);
   const size_t hbytes = (size_t)2 * NFMAX * g.maxb * sizeof(unsigned long long);
@@ -1771,15 +2014,26 @@ int amrv_mg_solve(amrv_mg* m, const double* f, double* phi, const double* lambda
     if (m->var && !(lambda[i] > 0.0)) return set_error(AMRV_EINVAL, "a solve with a coefficient needs lambda > 0");
   if (int rc = set_params(m, lambda)) return rc;
   const size_t bytes = (size_t)m->g.cells[0] * sizeof(double);
+  // a caller's field to or from level 0
+  auto copy = [&](const double* src, double* dst, int to_level) -> int {
+    if (m->g.split0) {
+      hipLaunchKernelGGL(k_mg3_reorder, dim3(blocks_of(m->g.cells[0] >> 1)), dim3(256), 0, m->st, m->g.lg[0], src, dst,
+                         to_level);
+      MGCHK(hipGetLastError());
+    } else {
+      MGCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, m->st));
+    }
+    return 0;
+  };
   for (int i = 0; i < m->g.nf; i++) {
-    MGCHK(hipMemcpyAsync(m->g.f[i][0], f + (size_t)i * m->g.cells[0], bytes, hipMemcpyDeviceToDevice, m->st));
-    MGCHK(hipMemcpyAsync(m->g.phi[i][0], phi + (size_t)i * m->g.cells[0], bytes, hipMemcpyDeviceToDevice, m->st));
+    if (int rc = copy(f + (size_t)i * m->g.cells[0], m->g.f[i][0], 1)) return rc;
+    if (int rc = copy(phi + (size_t)i * m->g.cells[0], m->g.phi[i][0], 1)) return rc;
   }
   int c = 0;
   const int rc = run_cycles(m, tol, max_cycles, 0, &c, res_max, f_max);
   if (cycles) *cycles = c;
   for (int i = 0; i < m->g.nf; i++)
-    MGCHK(hipMemcpyAsync(phi + (size_t)i * m->g.cells[0], m->g.phi[i][0], bytes, hipMemcpyDeviceToDevice, m->st));
+    if (int rc2 = copy(m->g.phi[i][0], phi + (size_t)i * m->g.cells[0], 0)) return rc2;
   MGCHK(hipStreamSynchronize(m->st));
   return rc;
 }
@@ -1886,9 +2140,19 @@ int amrv_rd_step(amrv_mg* m, const amrv_rd_params* p, int32_t scheme, double dt,
       if (cycles_total) *cycles_total = total;
       return rc;
     }
-    if (scheme == AMRV_RD_SPLIT) {
+    if (scheme == AMRV_RD_SPLIT && g.split0) {
+      hipLaunchKernelGGL(k_mg3_reorder, dim3(blocks_of(g.cells[0] >> 1)), dim3(256), 0, m->st, g.lg[0], g.phi[0][0], u,
+                         0);
+      hipLaunchKernelGGL(k_mg3_reorder, dim3(blocks_of(g.cells[0] >> 1)), dim3(256), 0, m->st, g.lg[0], g.phi[1][0], v,
+                         0);
+      MGCHK(hipGetLastError());
+    } else if (scheme == AMRV_RD_SPLIT) {
       MGCHK(hipMemcpyAsync(u, g.phi[0][0], bytes, hipMemcpyDeviceToDevice, m->st));
       MGCHK(hipMemcpyAsync(v, g.phi[1][0], bytes, hipMemcpyDeviceToDevice, m->st));
+    } else if (g.split0) {
+      hipLaunchKernelGGL(k_rd3_imex_final, dim3(blocks_of(g.cells[0] >> 1)), dim3(256), 0, m->st, g, k, u, v,
+                         m->tmp[0], m->tmp[1], dt);
+      MGCHK(hipGetLastError());
     } else {
       hipLaunchKernelGGL(d2 ? k_rd_imex_final<2> : k_rd_imex_final<3>, dim3(nb), dim3(256), 0, m->st, g, k, u, v,
                          m->tmp[0], m->tmp[1], dt);
@@ -1908,6 +2172,7 @@ int amrv_mg_set_coefficient(amrv_mg* m, const double* eps) {
   }
   if (!eps) {
     m->var = false;
+    m->g.split0 = m->g.nd == 3 && m->tail > 0;
     m->g.eps[0] = m->eps[0];
     return 0;
   }
@@ -1924,6 +2189,7 @@ int amrv_mg_set_coefficient(amrv_mg* m, const double* eps) {
   }
   MGCHK(hipStreamSynchronize(m->st));
   m->var = true;
+  m->g.split0 = 0;  // the variable-coefficient kernels keep the natural order
   return 0;
 }
 
