@@ -148,8 +148,8 @@ int amrv_advance(amrv_forest* f, double dt);
  * each step takes dt = min(cfl / max_cells sum_d (|v_d| + c_d)/dx_d, t_end - t)
  * from the Courant reduction of the state it starts from (the last stage of
  * each step folds the reduction of its result into the same pass), so the
- * host does not synchronise between steps; the steps replay one captured
- * HIP graph.  *t (host) is the time before and after; a step starting at or
+ * host does not synchronise between steps; after the first 64 steps to one
+ * t_end they replay a captured HIP graph, eight at a time.  *t (host) is the time before and after; a step starting at or
  * after t_end does nothing.  *taken (may be NULL) counts the steps with
  * dt > 0.  Synchronises at the end; AMRV_ENONPHYSICAL if a step met a
  * non-physical state (the steps after it do nothing).  The same arithmetic

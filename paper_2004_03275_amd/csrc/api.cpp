@@ -42,6 +42,14 @@ int hip_fail(hipError_t e, const char* where) {
 
 constexpr size_t ALIGN = 256;
 
+// Device-timed steps are launched directly until a forest has run DGRAPH_AFTER of
+// them with one end time, then replayed from a graph of DGRAPH_STEPS.  A graph
+// costs its capture (several hundred us) and about 8 us between replays, so one
+// of a single step lost to direct launches (Sod 23.0 against 20.0 us a step,
+// KH 34.7 against 32.1), which in turn are bound by the host below about 4 us a
+// launch (Sod 18.8 us a step in calls of 20, 16 of them replayed).
+constexpr int DGRAPH_STEPS = 8, DGRAPH_AFTER = 64;
+
 struct Layout {
   size_t off_U[3], off_G, off_FF, off_lvl, off_ijk, off_nbr, off_slot, off_kind, off_fslot, off_sleaf, off_sface,
       off_rlist, off_plist, off_pp, off_lp, off_red, off_cnt, off_emax, off_flags, off_mw, off_mwb, off_mx, off_mz,
@@ -122,9 +130,10 @@ struct amrv_forest {
   bool graph_on = false, graph_valid = false;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t graph = nullptr;
-  hipGraphExec_t dexec = nullptr;  // device-timed step
+  hipGraphExec_t dexec = nullptr;  // DGRAPH_STEPS device-timed steps
   hipGraph_t dgraph = nullptr;
-  double dt_tend = 0.0;            // t_end baked into the captured device-timed step
+  double dt_tend = 0.0;            // t_end baked into the captured device-timed steps
+  int64_t dsteps = 0;              // device-timed steps launched directly since (for the same t_end)
   bool prof = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;  // recorded pairs
   std::vector<hipEvent_t> ev_free;
@@ -227,15 +236,21 @@ int enqueue_stage_update(amrv_forest* f, const Geo& geo, const StageArgs& a, int
 }
 
 // one full SSP step on the forest's stream; dt and the damping factor are
-// read from the device parameter block.  fold != null: the last stage folds
-// the Courant reduction of the new state into it.  With the fused restriction
+// read from the device parameter block.  With the fused restriction
 // stage s reads ghost-slab buffer s-1 and restricts its result into buffer
 // s mod S, so only the first stage after a state change runs the separate
 // restriction (assume_valid: the caller guarantees Gb[0] holds it, as before
 // a captured step).
-int enqueue_step(amrv_forest* f, unsigned long long* fold = nullptr, bool assume_valid = false) {
+// clk != null: a device-timed step, which folds the Courant reduction of its
+// result; its beginning is part of the first stage kernel in 1D and 2D unless
+// that is not the step's first kernel to need the GLM speed (the fluxes of
+// coarse-fine faces) or runs once per leaf
+int enqueue_step(amrv_forest* f, const StepClock* clk = nullptr, bool assume_valid = false) {
   const int S = f->cfg.rk_stages;
   const bool fused = fused_restriction(f), feat = fused_features(f);
+  const bool whole = f->tab.nd == 3;
+  const bool separate = whole || f->sched == AMRV_SCHED_PER_BLOCK || (f->lc.phys == PH_MHD && f->tab.nslot > 0);
+  if (clk && separate) HIPCHK(launch_step_begin(*clk, whole, f->st));
   if (f->sched == AMRV_SCHED_PERSISTENT && f->tab.nd > 1) HIPCHK(launch_reset_u32(f->cnt, CNT_QUEUES, f->st));
   for (int s = 1; s <= S; s++) {
     const double* in = s == 1 ? f->U[0] : (s == 2 ? f->U[1] : f->U[2]);
@@ -252,7 +267,10 @@ int enqueue_step(amrv_forest* f, unsigned long long* fold = nullptr, bool assume
     a.dtp = f->pp + PP_DT;
     a.stage = s;
     a.rk = S;
-    a.cflred = s == S ? fold : nullptr;
+    a.cflred = clk && s == S ? f->red : nullptr;
+    a.begin = clk && s == 1 && !separate;
+    a.end = clk && s == S && !whole;
+    if (clk) a.clk = *clk;
     a.Gw = fused ? f->Gb[s % S] : nullptr;
     a.Xout = feat && s == S ? (uint16_t*)(f->ws + f->lay.off_mx) : nullptr;
     a.Zd = zsplit_capable(f->cfg, f->tab) ? (double*)(f->ws + f->lay.off_zd) : nullptr;
@@ -261,31 +279,30 @@ int enqueue_step(amrv_forest* f, unsigned long long* fold = nullptr, bool assume
   }
   f->rvalid = fused;
   f->fvalid = feat;
-  if (f->cfg.physics == AMRV_MHD_GLM) {
-    const int ip = 2 + 2 * f->tab.nd;
-    double* psi = f->U[0] + (size_t)ip * f->tab.n * f->tab.ncell;
-    HIPCHK(launch_scale_var(psi, f->pp + PP_DAMP, (long long)f->tab.n * f->tab.ncell, f->st));
-  }
   return AMRV_OK;
+}
+
+void drop_step_graph(amrv_forest* f) {
+  if (f->dexec) (void)hipGraphExecDestroy(f->dexec);
+  if (f->dgraph) (void)hipGraphDestroy(f->dgraph);
+  f->dexec = nullptr;
+  f->dgraph = nullptr;
+  f->dsteps = 0;
 }
 
 void drop_graph(amrv_forest* f) {
   if (f->gexec) (void)hipGraphExecDestroy(f->gexec);
   if (f->graph) (void)hipGraphDestroy(f->graph);
-  if (f->dexec) (void)hipGraphExecDestroy(f->dexec);
-  if (f->dgraph) (void)hipGraphDestroy(f->dgraph);
+  drop_step_graph(f);
   f->gexec = nullptr;
   f->graph = nullptr;
-  f->dexec = nullptr;
-  f->dgraph = nullptr;
   f->graph_valid = false;
 }
 
 // a device-timed step: dt from the previous fold, then the step with a fold
 int enqueue_device_step(amrv_forest* f, double t_end, bool assume_valid = false) {
-  HIPCHK(launch_dt_update(f->red, f->pp, f->pp + PP_T, f->cnt + CNT_ERR, f->cfg.cfl, t_end, f->cfg.glm_cr,
-                          f->cfg.physics == AMRV_MHD_GLM, f->st));
-  return enqueue_step(f, f->red, assume_valid);
+  const StepClock c{f->red, f->cnt, f->pp, f->cfg.cfl, t_end, f->cfg.glm_cr, f->cfg.physics == AMRV_MHD_GLM};
+  return enqueue_step(f, &c, assume_valid);
 }
 
 // before replaying a captured step (which assumes it): the restriction of
@@ -468,6 +485,7 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
         const double rd = cfg->cada_radius * ((cfg->xmax[d] - cfg->xmin[d]) / cells);
         pp[PP_CTHR + 3 * l + d] = rd * rd;
       }
+  const unsigned cnt0[CNT_COUNT] = {0};
   double lp[LP_COUNT] = {0};
   lp[LP_EPS] = cfg->lohner_eps;
   lp[LP_WRHO] = cfg->lohner_w_rho;
@@ -486,6 +504,7 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
                      up(L.off_plist, t.plist.data(), 4 * t.plist.size()),
                      up(L.off_pp, pp, sizeof pp),
                      up(L.off_lp, lp, sizeof lp),
+                     up(L.off_cnt, cnt0, sizeof cnt0),
                      hipStreamSynchronize(f->st)};
   for (hipError_t x : es)
     if (x != hipSuccess) {
@@ -552,10 +571,10 @@ int amrv_get_state(amrv_forest* f, double* U, int64_t nd, int32_t on_device) {
 
 int amrv_max_dt(amrv_forest* f, double* dt_out) {
   if (!f || !dt_out) return fail(AMRV_EINVAL, "null argument");
-  HIPCHK(launch_reset_u32((unsigned*)f->red, 2 * RED_SLOTS * RED_STRIDE, f->st));
-  HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->st));
-  unsigned long long* res = f->red + RED_SLOTS * RED_STRIDE;
-  HIPCHK(launch_red_result(f->red, res, f->st));
+  HIPCHK(launch_reset_u32((unsigned*)f->red, 4 * RED_BUF, f->st));
+  HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->cnt, f->st));
+  unsigned long long* res = f->red + 2 * RED_BUF;
+  HIPCHK(launch_red_result(f->red, f->cnt, res, f->st));
   unsigned long long h[3] = {0, 0, 0};
   HIPCHK(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, f->st));
   HIPCHK(hipStreamSynchronize(f->st));
@@ -603,46 +622,46 @@ int amrv_advance_cfl(amrv_forest* f, int32_t nsteps, double t_end, double* t, in
   if (!std::isfinite(*t) || std::isnan(t_end)) return fail(AMRV_EINVAL, "bad time");
   // initial fold: the Courant reduction of the current state, unless the
   // last step of the previous call (or amrv_max_dt) left it in place
-  HIPCHK(launch_reset_u32(f->cnt + CNT_ERR, 2, f->st));
+  HIPCHK(launch_reset_u32(f->cnt + CNT_ERR, 3, f->st));
   int rc = set_scalars(f, PP_T, {*t});
   if (rc) return rc;
   if (!f->fold_valid) {
-    HIPCHK(launch_reset_u32((unsigned*)f->red, 2 * RED_SLOTS * RED_STRIDE, f->st));
-    HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->st));
+    HIPCHK(launch_reset_u32((unsigned*)f->red, 4 * RED_BUF, f->st));
+    HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->cnt, f->st));
   }
   f->fold_valid = false;
-  const bool graph = f->st != nullptr && f->sched != AMRV_SCHED_PER_BLOCK && !f->prof;
-  if (graph) {
-    rc = ensure_restricted(f);
-    if (rc) return rc;
-  }
-  if (graph && (!f->dexec || f->dt_tend != t_end)) {
-    if (f->dexec) (void)hipGraphExecDestroy(f->dexec);
-    if (f->dgraph) (void)hipGraphDestroy(f->dgraph);
-    f->dexec = nullptr;
-    f->dgraph = nullptr;
-    HIPCHK(hipStreamBeginCapture(f->st, hipStreamCaptureModeThreadLocal));
-    rc = enqueue_device_step(f, t_end, true);
-    hipGraph_t gr = nullptr;
-    hipError_t e = hipStreamEndCapture(f->st, &gr);
-    if (rc) {
-      if (gr) (void)hipGraphDestroy(gr);
-      return rc;
-    }
-    if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-    f->dgraph = gr;
-    HIPCHK(hipGraphInstantiate(&f->dexec, gr, nullptr, nullptr, 0));
+  if (f->dt_tend != t_end) {
+    drop_step_graph(f);
     f->dt_tend = t_end;
   }
-  for (int i = 0; i < nsteps; i++) {
-    if (graph) {
+  int i = 0;
+  if (f->st != nullptr && f->sched != AMRV_SCHED_PER_BLOCK && !f->prof && nsteps >= DGRAPH_STEPS &&
+      (f->dexec || f->dsteps >= DGRAPH_AFTER)) {
+    rc = ensure_restricted(f);
+    if (rc) return rc;
+    if (!f->dexec) {
+      HIPCHK(hipStreamBeginCapture(f->st, hipStreamCaptureModeThreadLocal));
+      for (int k = 0; k < DGRAPH_STEPS && !rc; k++) rc = enqueue_device_step(f, t_end, true);
+      hipGraph_t gr = nullptr;
+      hipError_t e = hipStreamEndCapture(f->st, &gr);
+      if (rc) {
+        if (gr) (void)hipGraphDestroy(gr);
+        return rc;
+      }
+      if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
+      f->dgraph = gr;
+      HIPCHK(hipGraphInstantiate(&f->dexec, gr, nullptr, nullptr, 0));
+    }
+    for (; i + DGRAPH_STEPS <= nsteps; i += DGRAPH_STEPS) {
       HIPCHK(hipGraphLaunch(f->dexec, f->st));
       f->rvalid = fused_restriction(f);
       f->fvalid = fused_features(f);
-    } else {
-      rc = enqueue_device_step(f, t_end);
-      if (rc) return rc;
     }
+  }
+  for (; i < nsteps; i++) {
+    rc = enqueue_device_step(f, t_end);
+    if (rc) return rc;
+    f->dsteps++;
   }
   double th = 0.0;
   unsigned cw[2] = {0, 0};

@@ -51,6 +51,16 @@ struct Sched {
                        // xcd_remap [x] the queue of XCD x over leaves [x*per_xcd, (x+1)*per_xcd)
 };
 
+// the device-timed steps' clock: reduction slots (two buffers, of the step's
+// parity and the next), counters and parameter block
+struct StepClock {
+  unsigned long long* red;
+  unsigned* cnt;
+  double* pp;
+  double cfl, t_end, glm_cr;
+  int mhd;
+};
+
 struct StageArgs {
   const double* Uin;   // stage input U^(s-1)
   const double* Un;    // step initial state U^n
@@ -58,7 +68,12 @@ struct StageArgs {
   const double* dtp;   // device-resident dt
   int stage;           // 1..rk
   int rk;              // 2 or 3
-  unsigned long long* cflred;  // last stage: fold the Courant reduction of the new state into these slots (or null)
+  unsigned long long* cflred;  // last stage: fold the Courant reduction of the new state into the slots of the
+                               // next step's buffer (or null)
+  int begin;           // first stage of a device-timed step: every workgroup takes dt (and c_h) from the
+                       // reduction slots itself, the first one writes them down (k_step_begin otherwise)
+  int end;             // last stage of a device-timed step: the first workgroup closes the step
+  StepClock clk;       // with begin or end
   double* Gw;          // 3D combined variant: restrict the stage output onto the coarse neighbours'
                        // ghost slabs of this buffer (the G layout), or null
   uint16_t* Xout;      // 3D combined variant, last stage: the learned flagger's features of the
@@ -91,7 +106,7 @@ hipError_t launch_prolong(const Geo& g, const LaunchCfg& c, const double* U, con
 hipError_t launch_stage(const Geo& g, const LaunchCfg& c, const StageArgs& a, const double* physp, const Sched& s,
                         int grid, hipStream_t st);
 hipError_t launch_cfl(const Geo& g, const LaunchCfg& c, const double* U, const double* physp,
-                      unsigned long long* red, hipStream_t st);
+                      unsigned long long* red, const unsigned* cnt, hipStream_t st);
 hipError_t launch_lohner(const Geo& g, const LaunchCfg& c, const double* U, const double* physp,
                          const double* lohp, int max_level, double* emax, int8_t* flags, const int8_t* only,
                          hipStream_t st);
@@ -102,28 +117,35 @@ hipError_t launch_transfer(const Geo& from, const double* Uf, const Geo& to, dou
                            const LaunchCfg& c, hipStream_t st);
 hipError_t launch_set_scalars(double* dst, const double* src_host_vals, int n, hipStream_t st);
 hipError_t launch_reset_u32(unsigned* p, int n, hipStream_t st);
-hipError_t launch_scale_var(double* U, const double* facp, long long count, hipStream_t st);
 // Courant reduction: RED_SLOTS slots of RED_STRIDE 64-bit words (a cache line
-// each), words 0..2 of each in use; RED_WORDS with the three result words that
-// follow the slots
-constexpr int RED_SLOTS = 256, RED_STRIDE = 8, RED_WORDS = RED_SLOTS * RED_STRIDE + 4;
-// the slots' maxima into three words
-hipError_t launch_red_result(const unsigned long long* red, unsigned long long* out, hipStream_t st);
-// device-side time step from a Courant reduction: dt = min(cfl / smax, t_end - t),
-// t += dt, c_h and the GLM damping factor into the parameter block, then the
-// reduction words are cleared for the next fold
-hipError_t launch_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err, double cfl, double t_end,
-                            double glm_cr, int mhd, hipStream_t st);
+// each), words 0..2 of each in use, in two buffers; RED_WORDS with the three
+// result words that follow them
+constexpr int RED_SLOTS = 256, RED_STRIDE = 8, RED_BUF = RED_SLOTS * RED_STRIDE, RED_WORDS = 2 * RED_BUF + 4;
+// the maxima of the current buffer's slots into three words
+hipError_t launch_red_result(const unsigned long long* red, const unsigned* cnt, unsigned long long* out,
+                             hipStream_t st);
+// A device-timed step k reads the Courant slots of buffer k & 1 and folds its
+// result's into the other.  Beginning: dt = min(cfl / smax, t_end - t), c_h and
+// the GLM damping factor into the parameter block, the time after the step and
+// the next counts beside the current ones (so that every workgroup of one launch
+// sees the same values); end: those become the current ones and the slots read
+// are cleared.  k_step_begin is the beginning as a launch of its own, for steps
+// whose first kernel is not the stage kernel and needs c_h; in 3D (whole) also
+// the end, and every fold goes to buffer 0.
+hipError_t launch_step_begin(const StepClock& c, bool whole, hipStream_t st);
 // device counters: [8s .. 8s+7] the work queues of stage s = 1..3 (cleared
-// before every step), [CNT_ERR] non-physical flag, [CNT_TAKEN] steps taken
-constexpr int CNT_QUEUES = 32, CNT_ERR = 40, CNT_TAKEN = 41, CNT_COUNT = 64;
+// before every step), [CNT_ERR] non-physical flag, [CNT_TAKEN] steps taken and
+// [CNT_TAKEN1] after the current step, [CNT_STEP] the step's number and
+// [CNT_STEP1] the next
+constexpr int CNT_QUEUES = 32, CNT_ERR = 40, CNT_TAKEN = 41, CNT_TAKEN1 = 42, CNT_STEP = 43, CNT_STEP1 = 44,
+              CNT_COUNT = 64;
 
 // device parameter block (written once per forest, plus dt / ch per step)
 // layout: [0] gamma [1] gm1 [2] igm1 [3] ch [4] dt [5] glm damping factor
-// [6] time [7] c_ad [8] gamma * c_ad; from [16]: (r dx)^2 of Cada's smoothness
+// [6] time [7] c_ad [8] gamma * c_ad [9] time after the current step; from [16]: (r dx)^2 of Cada's smoothness
 // switch per level and dimension, [16 + 3 l + d] (0: none)
 constexpr int PP_GAMMA = 0, PP_GM1 = 1, PP_IGM1 = 2, PP_CH = 3, PP_DT = 4, PP_DAMP = 5, PP_T = 6, PP_CAD = 7,
-              PP_GCAD = 8, PP_CTHR = 16, PP_COUNT = PP_CTHR + 3 * MAXLEV;
+              PP_GCAD = 8, PP_T1 = 9, PP_CTHR = 16, PP_COUNT = PP_CTHR + 3 * MAXLEV;
 // Loehner parameters: [0] eps [1] w_rho [2] w_p [3] tol [4] coarsen tol
 constexpr int LP_EPS = 0, LP_WRHO = 1, LP_WP = 2, LP_TOL = 3, LP_CTOL = 4, LP_COUNT = 8;
 

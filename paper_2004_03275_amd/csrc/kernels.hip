@@ -345,9 +345,10 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
     }
   };
 
-  const PhysParams P = load_phys(pp);
-  const double dt = pp[PP_DT];
-  if (dt == 0.0) return;  // a device-timed run that has reached its end time
+  PhysParams P = load_phys(pp);
+  double dt;
+  if (!stage_clock<ND, PH>(a, pp, P, dt)) return;
+  const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;  // GLM damping of psi, once a step
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const size_t vs = (size_t)g.n * g.ncell;  // variable stride of the state
   unsigned long long csmax = 0, ccmax = 0;
@@ -688,7 +689,8 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
         acc = acc + (sFy[v][(ty + 1) * NB + tx] - sFy[v][ty * NB + tx]) * rdy;
         if constexpr (ND == 3) acc = acc + zd[v];
         const double tmp = Ui[v] - dt * acc;
-        const double res = combine<NV>(a.stage, a.rk, a.stage > 1 ? Uo[v] : 0.0, tmp);
+        double res = combine<NV>(a.stage, a.rk, a.stage > 1 ? Uo[v] : 0.0, tmp);
+        if (PH == PH_MHD && v == S::IP) res = res * damp;
         out[v * vs + (size_t)k * NB * NB] = res;
         Ui[v] = res;
       }
@@ -733,7 +735,7 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
       }
     }
   }
-  if (a.cflred) cfl_fold(a.cflred, csmax, ccmax, cbad);
+  if (a.cflred) cfl_fold(fold_slots<ND>(a), csmax, ccmax, cbad);
 }
 
 // ---------------------------------------------------------------------------
@@ -848,9 +850,10 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
   __shared__ double sF[2][NV][NFX];   // fluxes: x [row][face]; y [face][column]
   __shared__ int sLeaf;
 
-  const PhysParams P = load_phys(pp);
-  const double dt = pp[PP_DT];
-  if (dt == 0.0) return;
+  PhysParams P = load_phys(pp);
+  double dt;
+  if (!stage_clock<ND, PH>(a, pp, P, dt)) return;
+  const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;  // GLM damping of psi, once a step
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const size_t vs = (size_t)g.n * g.ncell;
   unsigned long long csmax = 0, ccmax = 0;
@@ -1009,7 +1012,8 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
         acc = acc + (sF[1][v][(ty + 1) * NB + tx] - sF[1][v][ty * NB + tx]) * rdy;
         acc = acc + Zk[v];
         const double tmp = Ui[v] - dt * acc;
-        const double res = combine<NV>(a.stage, a.rk, a.stage > 1 ? Uo[v] : 0.0, tmp);
+        double res = combine<NV>(a.stage, a.rk, a.stage > 1 ? Uo[v] : 0.0, tmp);
+        if (PH == PH_MHD && v == S::IP) res = res * damp;
         out[v * vs + (size_t)k * NB * NB] = res;
         Ui[v] = res;
       }
@@ -1019,7 +1023,7 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
       }
     }
   }
-  if (a.cflred) cfl_fold(a.cflred, csmax, ccmax, cbad);
+  if (a.cflred) cfl_fold(fold_slots<ND>(a), csmax, ccmax, cbad);
 }
 
 // ---------------------------------------------------------------------------
@@ -1035,9 +1039,10 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
   __shared__ double sL[NV][CH + 2];
   __shared__ double sR[NV][CH + 2];
   __shared__ double sF[NV][CH + 1];
-  const PhysParams P = load_phys(pp);
-  const double dt = pp[PP_DT];
-  if (dt == 0.0) return;
+  PhysParams P = load_phys(pp);
+  double dt;
+  if (!stage_clock<1, PH>(a, pp, P, dt)) return;
+  const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;
   const int tid = threadIdx.x;
   const int nch = (g.nx + CH - 1) / CH;
   const int leaf = sc.mode == 0 ? sc.leaf0 : (int)(blockIdx.x / nch);
@@ -1108,6 +1113,7 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
       const double tmp = a.Uin[id] - dt * acc;
       const double un = a.stage == 1 ? 0.0 : a.Un[id];
       res[v] = combine<NV>(a.stage, a.rk, un, tmp);
+      if (PH == PH_MHD && v == S::IP) res[v] = res[v] * damp;
       a.Uout[id] = res[v];
     }
     if (a.cflred) {
@@ -1115,7 +1121,7 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
       cfl_cell<1, PH>(res, P, rd, csmax, ccmax, cbad);
     }
   }
-  if (a.cflred) cfl_fold(a.cflred, csmax, ccmax, cbad);
+  if (a.cflred) cfl_fold(fold_slots<1>(a), csmax, ccmax, cbad);
 }
 
 // ---------------------------------------------------------------------------
@@ -1129,7 +1135,7 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
 // patterns, so integer atomics give the exact maximum.
 template <int ND, int PH>
 __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U, const double* __restrict__ pp,
-                                             unsigned long long* red) {
+                                             unsigned long long* red, const unsigned* __restrict__ cnt) {
   constexpr int NV = Sys<ND, PH>::NV;
   const PhysParams P = load_phys(pp);
   const long long total = (long long)g.n * g.ncell;
@@ -1160,7 +1166,7 @@ __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U
     smax = sb > smax ? sb : smax;
     cmax = cb > cmax ? cb : cmax;
   }
-  cfl_fold(red, smax, cmax, bad);
+  cfl_fold(red + (cnt[CNT_STEP] & 1) * RED_BUF, smax, cmax, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -1252,12 +1258,6 @@ __global__ void k_set_scalars(double* dst, double a0, double a1, double a2, doub
 __global__ void k_reset_u32(unsigned* p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
-}
-
-__global__ void k_scale(double* U, const double* __restrict__ facp, long long count) {
-  const double fac = *facp;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (long long)gridDim.x * blockDim.x)
-    U[i] = U[i] * fac;
 }
 
 // ---------------------------------------------------------------------------
@@ -1479,17 +1479,17 @@ hipError_t launch_stage(const Geo& g, const LaunchCfg& c, const StageArgs& a, co
 }
 
 hipError_t launch_cfl(const Geo& g, const LaunchCfg& c, const double* U, const double* physp,
-                      unsigned long long* red, hipStream_t st) {
+                      unsigned long long* red, const unsigned* cnt, hipStream_t st) {
   const long long total = (long long)g.n * g.ncell;
   long long nb = (total + WGS - 1) / WGS;
   if (nb > 2048) nb = 2048;  // 8 workgroups per CU; the rest by the grid stride
 #define BODY_C(ND)                                                                                                    \
   if (c.phys == PH_MHD)                                                                                               \
-    hipLaunchKernelGGL((k_cfl<ND, PH_MHD>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red);                  \
+    hipLaunchKernelGGL((k_cfl<ND, PH_MHD>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);                  \
   else if (c.phys == PH_POLY)                                                                                         \
-    hipLaunchKernelGGL((k_cfl<ND, PH_POLY>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red);                 \
+    hipLaunchKernelGGL((k_cfl<ND, PH_POLY>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);                 \
   else                                                                                                                \
-    hipLaunchKernelGGL((k_cfl<ND, PH_EULER>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red);
+    hipLaunchKernelGGL((k_cfl<ND, PH_EULER>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);
   if (c.ndim == 1) {
     BODY_C(1)
   } else if (c.ndim == 2) {
@@ -1524,44 +1524,30 @@ hipError_t launch_lohner(const Geo& g, const LaunchCfg& c, const double* U, cons
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(WGS) k_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err,
-                                                   double cfl, double t_end, double glm_cr, int mhd) {
-  unsigned long long sb, cb;
-  int bad;
-  red_all(red, sb, cb, bad);
+// whole: the step's end too (3D, whose folds stay in one buffer)
+__global__ void __launch_bounds__(WGS) k_step_begin(StepClock c, int whole) {
+  double dt, ch;
+  step_begin(c, true, dt, ch);
+  if (!whole) return;
 #pragma unroll
-  for (int w = 0; w < 3; w++) red[threadIdx.x * RED_STRIDE + w] = 0ull;
-  if (threadIdx.x != 0) return;
-  if (bad) *err = 1u;
-  const double smax = __longlong_as_double((long long)sb);
-  const double ch = __longlong_as_double((long long)cb);
-  const double tn = *t;
-  double dt = 0.0;
-  if (tn < t_end && smax > 0.0 && !bad) {
-    dt = cfl / smax;
-    const double rem = t_end - tn;
-    if (rem < dt) dt = rem;
-    err[CNT_TAKEN - CNT_ERR] += 1u;
-  }
-  *t = tn + dt;
-  pp[PP_DT] = dt;
-  if (mhd) {
-    pp[PP_CH] = ch;
-    pp[PP_DAMP] = exp(-(dt * ch) / glm_cr);
+  for (int w = 0; w < 3; w++) c.red[threadIdx.x * RED_STRIDE + w] = 0ull;
+  if (threadIdx.x == 0) {
+    c.pp[PP_T] = c.pp[PP_T1];
+    c.cnt[CNT_TAKEN] = c.cnt[CNT_TAKEN1];
   }
 }
 
-hipError_t launch_dt_update(unsigned long long* red, double* pp, double* t, unsigned* err, double cfl, double t_end,
-                            double glm_cr, int mhd, hipStream_t st) {
-  hipLaunchKernelGGL(k_dt_update, dim3(1), dim3(WGS), 0, st, red, pp, t, err, cfl, t_end, glm_cr, mhd);
+hipError_t launch_step_begin(const StepClock& c, bool whole, hipStream_t st) {
+  hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(WGS), 0, st, c, whole ? 1 : 0);
   return hipGetLastError();
 }
 
-// the slots' result into out[0..2] (the slots keep their values)
-__global__ void __launch_bounds__(WGS) k_red_result(const unsigned long long* red, unsigned long long* out) {
+// the current slots' result into out[0..2] (the slots keep their values)
+__global__ void __launch_bounds__(WGS) k_red_result(const unsigned long long* red, const unsigned* cnt,
+                                                    unsigned long long* out) {
   unsigned long long sb, cb;
   int bad;
-  red_all(red, sb, cb, bad);
+  red_all(red + (cnt[CNT_STEP] & 1) * RED_BUF, sb, cb, bad);
   if (threadIdx.x == 0) {
     out[0] = sb;
     out[1] = cb;
@@ -1569,8 +1555,9 @@ __global__ void __launch_bounds__(WGS) k_red_result(const unsigned long long* re
   }
 }
 
-hipError_t launch_red_result(const unsigned long long* red, unsigned long long* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_red_result, dim3(1), dim3(WGS), 0, st, red, out);
+hipError_t launch_red_result(const unsigned long long* red, const unsigned* cnt, unsigned long long* out,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_red_result, dim3(1), dim3(WGS), 0, st, red, cnt, out);
   return hipGetLastError();
 }
 
@@ -1582,13 +1569,6 @@ hipError_t launch_set_scalars(double* dst, const double* vals, int n, hipStream_
 
 hipError_t launch_reset_u32(unsigned* p, int n, hipStream_t st) {
   hipLaunchKernelGGL(k_reset_u32, dim3((n + 255) / 256), dim3(256), 0, st, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_scale_var(double* U, const double* facp, long long count, hipStream_t st) {
-  long long nb = (count + 255) / 256;
-  if (nb > 8192) nb = 8192;
-  hipLaunchKernelGGL(k_scale, dim3((unsigned)nb), dim3(256), 0, st, U, facp, count);
   return hipGetLastError();
 }
 

@@ -189,7 +189,7 @@ __device__ __forceinline__ void cfl_fold(unsigned long long* red, unsigned long 
   }
 }
 
-// the maxima (and the non-physical flag) of all reduction slots, in every
+// the maxima (and the non-physical flag) of a buffer's reduction slots, in every
 // thread of a WGS-thread workgroup (WGS == RED_SLOTS: one slot per thread)
 __device__ __forceinline__ void red_all(const unsigned long long* red, unsigned long long& smax,
                                         unsigned long long& cmax, int& bad) {
@@ -217,6 +217,80 @@ __device__ __forceinline__ void red_all(const unsigned long long* red, unsigned 
   }
 }
 
+
+// the beginning of a device-timed step (internal.hpp), in every thread of the
+// workgroup: dt and, for MHD, c_h; write: this workgroup notes them down
+__device__ __forceinline__ void step_begin(const StepClock& k, bool write, double& dt, double& ch) {
+  const unsigned step = k.cnt[CNT_STEP];
+  const double tn = k.pp[PP_T];
+  unsigned long long sb, cb;
+  int bad;
+  red_all(k.red + (step & 1) * RED_BUF, sb, cb, bad);
+  const double smax = __longlong_as_double((long long)sb);
+  ch = __longlong_as_double((long long)cb);
+  dt = 0.0;
+  if (tn < k.t_end && smax > 0.0 && !bad) {
+    dt = k.cfl / smax;
+    const double rem = k.t_end - tn;
+    if (rem < dt) dt = rem;
+  }
+  if (write && threadIdx.x == 0) {
+    k.pp[PP_DT] = dt;
+    k.pp[PP_T1] = tn + dt;
+    k.cnt[CNT_STEP1] = step + 1;
+    k.cnt[CNT_TAKEN1] = k.cnt[CNT_TAKEN] + (dt != 0.0 ? 1u : 0u);
+    if (bad) k.cnt[CNT_ERR] = 1u;
+    if (k.mhd) {
+      k.pp[PP_CH] = ch;
+      k.pp[PP_DAMP] = exp(-(dt * ch) / k.glm_cr);
+    }
+  }
+}
+
+// the end of a device-timed step, by the first workgroup of its last stage (the
+// others of that launch read the next step's number only)
+__device__ __forceinline__ void step_end(const StepClock& k) {
+  if (blockIdx.x) return;
+  unsigned long long* r = k.red + ((k.cnt[CNT_STEP1] + 1) & 1) * RED_BUF + threadIdx.x * RED_STRIDE;
+  r[0] = 0ull;
+  r[1] = 0ull;
+  r[2] = 0ull;
+  if (threadIdx.x == 0) {
+    k.pp[PP_T] = k.pp[PP_T1];
+    k.cnt[CNT_STEP] = k.cnt[CNT_STEP1];
+    k.cnt[CNT_TAKEN] = k.cnt[CNT_TAKEN1];
+  }
+}
+
+// a stage's dt; false: nothing to do (a device-timed run at its end time).  In 1D
+// and 2D, where a stage takes 6 to 40 us, the step begins and ends inside its
+// stage kernels: a launch between them cost 4.5 us of a 27 us step of 256 leaves.
+// The 3D kernels are register-bound and leave it to k_step_begin (5 us of a
+// 1.5 ms step and more; the clock inside them cost 8% of the exact 3D kernel).
+template <int ND, int PH>
+__device__ __forceinline__ bool stage_clock(const StageArgs& a, const double* __restrict__ pp, PhysParams& P,
+                                            double& dt) {
+  if constexpr (ND < 3) {
+    if (a.begin) {
+      double ch;
+      step_begin(a.clk, blockIdx.x == 0, dt, ch);
+      if constexpr (PH == PH_MHD) P.ch = ch;
+    } else {
+      dt = pp[PP_DT];
+    }
+    if (a.end) step_end(a.clk);
+  } else {
+    dt = pp[PP_DT];
+  }
+  return dt != 0.0;
+}
+
+// where the last stage folds its Courant maxima
+template <int ND>
+__device__ __forceinline__ unsigned long long* fold_slots(const StageArgs& a) {
+  if constexpr (ND < 3) return a.cflred + (a.clk.cnt[CNT_STEP1] & 1) * RED_BUF;
+  return a.cflred;
+}
 
 __device__ __forceinline__ int pick_leaf(const Sched& sc, int b) {
   if (sc.mode == 0) return sc.leaf0;
