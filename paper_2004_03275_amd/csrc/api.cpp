@@ -173,8 +173,12 @@ int stage_grid(const amrv_forest* f, int mode) {
     return mode == AMRV_SCHED_PER_BLOCK ? nch : (int)(t.n * nch);
   }
   if (mode == AMRV_SCHED_PER_BLOCK) return 1;
-  if (mode == AMRV_SCHED_PERSISTENT) return f->pwgs > 0 ? f->pwgs : 2 * f->ncu;
-  return f->xcd ? 8 * (int)((t.n + 7) / 8) : (int)t.n;
+  // the 2D stage kernel runs one workgroup per CU, which loads its next leaf
+  // while it computes one (k_stage_plane)
+  const bool plane = t.nd == 2 && f->lc.variant == 0;
+  if (mode == AMRV_SCHED_PERSISTENT) return f->pwgs > 0 ? f->pwgs : (plane ? 1 : 2) * f->ncu;
+  const int all = f->xcd ? 8 * (int)((t.n + 7) / 8) : (int)t.n;
+  return plane ? std::min(all, std::max(8, f->ncu & ~7)) : all;
 }
 
 // enqueue the coarse-fine pre-pass on state U into geo's ghost-slab buffer;

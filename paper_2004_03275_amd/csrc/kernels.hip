@@ -287,7 +287,7 @@ __global__ void __launch_bounds__(WGS) k_transfer(Geo gf, const double* __restri
 // Global loads are issued one phase or one plane ahead of their use, so the
 // memory latency overlaps the FP64 work of the current plane.
 //
-// SPLIT = false: x and y share the slope and flux phases (3 barriers per
+// SPLIT = false (3D; k_stage_plane in 2D): x and y share the slope and flux phases (3 barriers per
 // plane, separate x/y LDS arrays).  SPLIT = true: x, then y, through one set
 // of LDS arrays (5 barriers per plane, 40% less LDS, so more workgroups fit
 // on a compute unit).  Both evaluate identical expressions.
@@ -535,10 +535,9 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
         for (int v = 0; v < NV; v++) sP[v][rdst] = w[v];
         if (k + 1 < NZ) load_strided<NV>(rptr + (k + 1) * rks, rvs, Cr);
       }
-      // operands of this plane's update (loaded early, consumed in phase 5;
-      // in 3D the combined variant already holds U_in of the plane)
+      // U^n of this plane's update (loaded early, consumed in phase 5; the
+      // combined variant already holds U_in of the plane)
       if constexpr (!SPLIT) {
-        if constexpr (ND != 3) load_strided<NV>(own + k * NB * NB, vs, Ui);
         if (a.stage > 1) load_strided<NV>(ownn + k * NB * NB, vs, Uo);
       }
       __syncthreads();
@@ -734,6 +733,223 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
         restrict_leaf<NV>(g, a, leaf, tid);
       }
     }
+  }
+  if (a.cflred) cfl_fold(fold_slots<ND>(a), csmax, ccmax, cbad);
+}
+
+// ---------------------------------------------------------------------------
+// stage update, 2D: one 576-thread workgroup per 16^2 leaf
+// ---------------------------------------------------------------------------
+
+// The expressions of k_stage_tile on the one plane a 2D leaf has.  A leaf is a
+// chain of phases (primitives, limited slopes, face fluxes, update), each a
+// serial piece of FP64 work behind a barrier, and its latency bounds the
+// launch: with 256 threads the 384 cells with their ghost ring, the 576 slopes
+// and the 544 faces took 2, 3 and 3 rounds.  576 threads (nine waves) take each
+// phase in one.  Every load a leaf waits for (its tables, then the cells they
+// lead to) is issued a leaf ahead, so one resident workgroup per CU suffices,
+// which leaves 168 registers per thread (no spills) and LDS enough for any
+// system; forests of more leaves than CUs walk them, each XCD its own eighth.
+// One stage, 256 threads per leaf and workgroups per leaf -> this: Orszag-Tang
+// 1,024 leaves 44.1 -> 28.3 us (4 leaves per CU; VALU issue alone 2.8 us a
+// leaf), Kelvin-Helmholtz 256 leaves 8.8 -> 7.2 us, 1,024 leaves 17.6 us, dam
+// break 84 leaves 9.2 -> 6.6 us (a launch that touches memory once: 3 us).
+constexpr int WGS2 = 576;
+
+template <int PH, int FLUX, int LIM, int AR>
+__global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a,
+                                                                            const double* __restrict__ pp, Sched sc) {
+  constexpr int ND = 2;
+  using S = Sys<ND, PH>;
+  constexpr int NV = S::NV;
+  constexpr int PW = NB + 4;
+  constexpr int NSX = NB * 18;  // x slopes: 16 rows x cells -1..16, [row][cell+1]; then y [cell+1][column]
+  constexpr int NFX = NB * 17;  // x faces: 16 rows x faces 0..16, [row][face]; then y [face][column]
+  static_assert(2 * NSX == WGS2 && 2 * NFX <= WGS2, "one item per thread");
+  // an asymmetric limiter's half slopes serve one face each: formed in the flux
+  // phase from four primitives (as in k_stage_tile)
+  constexpr bool RCF = lim_asym<LIM>();
+  __shared__ double sP[NV][PW * PW];  // primitives incl. the 2-cell ghost ring, (y+2)*PW + x+2
+  __shared__ double sS[RCF ? 1 : NV][RCF ? 1 : 2 * NSX];
+  __shared__ double sF[NV][2 * NFX];
+  // MHD: the cells' conserved values wait here for the update (14 registers that
+  // HLLC would spill; one workgroup per CU has the LDS to spare)
+  constexpr bool KEEP = PH == PH_MHD;
+  __shared__ double sU[KEEP ? NV : 1][KEEP ? NB * NB : 1];
+  __shared__ int sLeaf;
+
+  const int tid = threadIdx.x;
+  const size_t vs = (size_t)g.n * g.ncell;  // variable stride of the state
+
+  // this thread's cell: its own (tid < 256), or of the x ring, or of the y ring
+  const bool own = tid < NB * NB, cell = tid < NB * NB + 128;
+  int rface = 0, rlayer = 0, ra1 = 0, dst = ((tid >> 4) + 2) * PW + (tid & 15) + 2;
+  if (!own && cell) {
+    const int u = tid - NB * NB, c = (u >> 4) & 3;
+    const int across = c < 2 ? c - 2 : 14 + c;
+    const bool yring = u >= 64;
+    ra1 = u & 15;
+    rface = (yring ? 2 : 0) + (c >= 2);
+    rlayer = c < 2 ? 1 - c : c - 2;
+    dst = yring ? (across + 2) * PW + ra1 + 2 : (ra1 + 2) * PW + across + 2;
+  }
+  // this thread's face: in row (or column) fr, face fm of 0..16; fbf: the leaf's
+  // face it lies in (-1: none)
+  const bool fyd = tid >= NFX;
+  const int fu = fyd ? tid - NFX : tid;
+  const int fr = fyd ? fu % NB : fu / 17, fm = fyd ? fu / NB : fu % 17;
+  const int fbf = tid >= 2 * NFX ? -1 : fm == 0 ? 2 * fyd : (fm == NB ? 2 * fyd + 1 : -1);
+
+  // leaves of this workgroup: its own and every `step`-th of its XCD's share
+  // (one in mode 0, the queue's in mode 2)
+  int leaf = sc.mode == 2 ? g.n : pick_leaf(sc, blockIdx.x);
+  const int step = sc.xcd_remap ? (int)gridDim.x >> 3 : (int)gridDim.x;
+  const int stop = sc.mode != 1 ? 0 : sc.xcd_remap ? min(g.n, ((int)(blockIdx.x & 7) + 1) * sc.per_xcd) : g.n;
+  if (sc.mode == 1 && leaf >= stop) leaf = g.n;
+  if (sc.mode == 2) {
+    if (tid == 0) sLeaf = queue_next(sc, g.n);
+    __syncthreads();
+    leaf = sLeaf;
+  }
+  // a leaf's tables as this thread needs them: the kind, neighbour and slot of
+  // its ring cell's face and the kind of its face's
+  int nkd = NB_SAME, nnb = 0, nsl = 0, nfk = NB_SAME;
+  auto tables = [&](int l) {
+    if (!own && cell) {
+      nkd = g.kind[l * 6 + rface];
+      nnb = g.nbr[l * 6 + rface];
+      nsl = g.slot[l * 6 + rface];
+    }
+    if (fbf >= 0) nfk = g.kind[l * 6 + fbf];
+  };
+  double Cn[NV];  // the next leaf's values, loaded a leaf ahead
+  auto loads = [&](int l) {
+    if (!cell) return;
+    const double* p = a.Uin + (size_t)l * g.ncell + tid;
+    size_t pvs = vs;
+    if (!own) {
+      if (nkd == NB_SAME || nkd == NB_BND) {
+        const int along = nkd == NB_SAME ? (rface & 1 ? rlayer : NB - 1 - rlayer) : (rface & 1 ? NB - 1 : 0);
+        p = a.Uin + (size_t)nnb * g.ncell + (rface < 2 ? along + NB * ra1 : ra1 + NB * along);
+      } else {
+        p = g.G + (size_t)nsl * NV * 2 * g.T + (size_t)rlayer * g.T + ra1;
+        pvs = 2 * (size_t)g.T;
+      }
+    }
+    load_strided<NV>(p, pvs, Cn);
+  };
+  if (leaf < g.n) {
+    tables(leaf);
+    loads(leaf);
+  }
+
+  PhysParams P = load_phys(pp);
+  double dt;
+  if (!stage_clock<ND, PH>(a, pp, P, dt)) return;
+  const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;  // GLM damping of psi, once a step
+  unsigned long long csmax = 0, ccmax = 0;
+  int cbad = 0;
+
+  while (leaf < g.n) {
+    const int lvl = g.lvl[leaf];
+    const double rdx = g.rdx[lvl][0], rdy = g.rdx[lvl][1];
+    const double thx = pp[PP_CTHR + 3 * lvl], thy = pp[PP_CTHR + 3 * lvl + 1];
+    const int fkind = nfk;
+    int next = leaf + step < stop ? leaf + step : g.n;
+    if (sc.mode == 2 && tid == 0) sLeaf = queue_next(sc, g.n);
+
+    // (1) the cells' primitives to LDS; then the next leaf's loads
+    double Ui[NV], Uo[NV];
+#pragma unroll
+    for (int v = 0; v < NV; v++) Ui[v] = Cn[v];
+    if (own && a.stage > 1) load_strided<NV>(a.Un + (size_t)leaf * g.ncell + tid, vs, Uo);
+    if (cell) {
+      double w[NV];
+      cons2prim<ND, PH>(Ui, w, P);
+#pragma unroll
+      for (int v = 0; v < NV; v++) {
+        sP[v][dst] = w[v];
+        if (KEEP && own) sU[v][tid] = Ui[v];
+      }
+    }
+    __syncthreads();
+    if (sc.mode == 2) next = sLeaf;
+    if (next < g.n) tables(next);
+
+    // (2) limited slopes of the leaf's cells and the first ghost layer
+    if constexpr (!RCF) {
+      const bool yd = tid >= NSX;
+      const int u = yd ? tid - NSX : tid;
+      const int b = yd ? (u / NB + 1) * PW + u % NB + 2 : (u / 18 + 2) * PW + u % 18 + 1;
+      const int st = yd ? PW : 1;
+#pragma unroll
+      for (int v = 0; v < NV; v++) {
+        const double vm = sP[v][b - st], v0 = sP[v][b], vp = sP[v][b + st];
+        sS[v][tid] = 0.5 * limiter<LIM>(v0 - vm, vp - v0, yd ? thy : thx);
+      }
+      __syncthreads();
+    }
+    if (next < g.n) loads(next);
+
+    // (3) face fluxes; a y face as an x face of the state with its x and y
+    // components exchanged (k_stage_tile)
+    if (tid < 2 * NFX) {
+      const int bl = fyd ? (fm + 1) * PW + fr + 2 : (fr + 2) * PW + fm + 1;
+      const int st = fyd ? PW : 1;
+      double F[NV];
+      if (!(fkind == NB_SAME || fkind == NB_BND)) {
+        cf_flux<NV, ND>(g, leaf, fbf, fkind, fr, 0, F);
+      } else {
+        double vl[NV], vr[NV];
+        if constexpr (RCF) {
+          const double th = fyd ? thy : thx;
+#pragma unroll
+          for (int v = 0; v < NV; v++) {
+            const double pa0 = sP[v][bl - st], pa = sP[v][bl], pb = sP[v][bl + st], pb1 = sP[v][bl + 2 * st];
+            const double da = pa - pa0, dab = pb - pa, db = pb1 - pb;
+            vl[v] = pa + 0.5 * limiter<LIM>(da, dab, th);
+            vr[v] = pb - 0.5 * limiter<LIM>(db, dab, th);
+          }
+        } else {
+          const int s0 = fyd ? NSX + fm * NB + fr : fr * 18 + fm;
+          const int s1 = s0 + (fyd ? NB : 1);
+#pragma unroll
+          for (int v = 0; v < NV; v++) {
+            vl[v] = sP[v][bl] + sS[v][s0];
+            vr[v] = sP[v][bl + st] - sS[v][s1];
+          }
+        }
+        if (fyd) {
+          swap_xy<ND, PH>(vl);
+          swap_xy<ND, PH>(vr);
+        }
+        riemann<ND, PH, FLUX, 0>(vl, vr, F, P);
+        if (fyd) swap_xy<ND, PH>(F);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; v++) sF[v][tid] = F[v];
+    }
+    __syncthreads();
+
+    // (4) divergence (x, then y) and the SSP combination
+    if (own) {
+      const int tx = tid & 15, ty = tid >> 4;
+#pragma unroll
+      for (int v = 0; v < NV; v++) {
+        double acc = (sF[v][ty * 17 + tx + 1] - sF[v][ty * 17 + tx]) * rdx;
+        acc = acc + (sF[v][NFX + (ty + 1) * NB + tx] - sF[v][NFX + ty * NB + tx]) * rdy;
+        const double tmp = (KEEP ? sU[v][tid] : Ui[v]) - dt * acc;
+        double res = combine<NV>(a.stage, a.rk, a.stage > 1 ? Uo[v] : 0.0, tmp);
+        if (PH == PH_MHD && v == S::IP) res = res * damp;
+        a.Uout[v * vs + (size_t)leaf * g.ncell + tid] = res;
+        Ui[v] = res;
+      }
+      if (a.cflred) {
+        const double rd[3] = {rdx, rdy, 0.0};
+        cfl_cell<ND, PH>(Ui, P, rd, csmax, ccmax, cbad);
+      }
+    }
+    leaf = next;
   }
   if (a.cflred) cfl_fold(fold_slots<ND>(a), csmax, ccmax, cbad);
 }
@@ -1379,9 +1595,13 @@ hipError_t AMRV_UNIT_LAUNCHER(const Geo& g, const LaunchCfg& c, const StageArgs&
   dispatch(c, [&](auto nd, auto ph, auto fl, auto lm) {
     constexpr int ND = decltype(nd)::value, FL = decltype(fl)::value, LM = decltype(lm)::value;
     constexpr int PH = decltype(ph)::value;
-    if constexpr (in_ilp_unit<ND, PH, LM>())
-      hipLaunchKernelGGL((k_stage_tile<ND, PH, FL, LM, false, AMRV_STAGE_UNIT>), dim3(grid), dim3(WGS), 0, st, g, a,
-                         physp, s);
+    if constexpr (in_ilp_unit<ND, PH, LM>()) {
+      if constexpr (ND == 2)
+        hipLaunchKernelGGL((k_stage_plane<PH, FL, LM, AMRV_STAGE_UNIT>), dim3(grid), dim3(WGS2), 0, st, g, a, physp, s);
+      else
+        hipLaunchKernelGGL((k_stage_tile<ND, PH, FL, LM, false, AMRV_STAGE_UNIT>), dim3(grid), dim3(WGS), 0, st, g, a,
+                           physp, s);
+    }
   });
   return hipGetLastError();
 }
@@ -1466,10 +1686,12 @@ hipError_t launch_stage(const Geo& g, const LaunchCfg& c, const StageArgs& a, co
     constexpr int PH = decltype(ph)::value;
     if constexpr (ND == 1)
       hipLaunchKernelGGL((k_stage_line<PH, FL, LM>), dim3(grid), dim3(WGS), 0, st, g, a, physp, s);
-    else if (c.variant == 1 || (lim_asym<LM>() && !in_ilp_unit<ND, PH, LM>()))
+    else if (c.variant == 1 || (ND == 3 && lim_asym<LM>() && !in_ilp_unit<ND, PH, LM>()))
       hipLaunchKernelGGL((k_stage_tile<ND, PH, FL, LM, true, 0>), dim3(grid), dim3(WGS), 0, st, g, a, physp, s);
     else if constexpr (in_ilp_unit<ND, PH, LM>())
       combined = true;
+    else if constexpr (ND == 2)
+      hipLaunchKernelGGL((k_stage_plane<PH, FL, LM, 0>), dim3(grid), dim3(WGS2), 0, st, g, a, physp, s);
     else if constexpr (!lim_asym<LM>())
       hipLaunchKernelGGL((k_stage_tile<ND, PH, FL, LM, false, 0>), dim3(grid), dim3(WGS), 0, st, g, a, physp, s);
   });

@@ -190,20 +190,23 @@ __device__ __forceinline__ void cfl_fold(unsigned long long* red, unsigned long 
 }
 
 // the maxima (and the non-physical flag) of a buffer's reduction slots, in every
-// thread of a WGS-thread workgroup (WGS == RED_SLOTS: one slot per thread)
+// thread of a workgroup of WGS threads or more (WGS == RED_SLOTS: the first WGS
+// read one slot each)
 __device__ __forceinline__ void red_all(const unsigned long long* red, unsigned long long& smax,
                                         unsigned long long& cmax, int& bad) {
   static_assert(WGS == RED_SLOTS, "one slot per thread");
   __shared__ unsigned long long sr[2][WGS / 64];
   __shared__ int sb[WGS / 64];
-  const unsigned long long* r = red + threadIdx.x * RED_STRIDE;
-  const unsigned long long s0 = r[0], c0 = r[1], b0 = r[2];
-  const unsigned long long s = wave_max_u64(s0), c = wave_max_u64(c0);
-  const int b = __any(b0 != 0);
-  if ((threadIdx.x & 63) == 0) {
-    sr[0][threadIdx.x >> 6] = s;
-    sr[1][threadIdx.x >> 6] = c;
-    sb[threadIdx.x >> 6] = b;
+  if (threadIdx.x < WGS) {
+    const unsigned long long* r = red + threadIdx.x * RED_STRIDE;
+    const unsigned long long s0 = r[0], c0 = r[1], b0 = r[2];
+    const unsigned long long s = wave_max_u64(s0), c = wave_max_u64(c0);
+    const int b = __any(b0 != 0);
+    if ((threadIdx.x & 63) == 0) {
+      sr[0][threadIdx.x >> 6] = s;
+      sr[1][threadIdx.x >> 6] = c;
+      sb[threadIdx.x >> 6] = b;
+    }
   }
   __syncthreads();
   smax = 0;
@@ -250,7 +253,7 @@ __device__ __forceinline__ void step_begin(const StepClock& k, bool write, doubl
 // the end of a device-timed step, by the first workgroup of its last stage (the
 // others of that launch read the next step's number only)
 __device__ __forceinline__ void step_end(const StepClock& k) {
-  if (blockIdx.x) return;
+  if (blockIdx.x || threadIdx.x >= WGS) return;
   unsigned long long* r = k.red + ((k.cnt[CNT_STEP1] + 1) & 1) * RED_BUF + threadIdx.x * RED_STRIDE;
   r[0] = 0ull;
   r[1] = 0ull;
