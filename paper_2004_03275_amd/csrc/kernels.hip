@@ -965,17 +965,32 @@ __global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a,
 // stage_zsplit_fast.hip), as for k_stage_tile.
 // ---------------------------------------------------------------------------
 
+// Each leaf's planes are shared out over 2^lc workgroups (launcher, below):
+// leaf and planes k0 .. k1 - 1 of this one.  Leaves differ in their work (where
+// the flow is flat the limiter and the Riemann solver take their short ways),
+// and 512 leaves of one workgroup each filled the chip exactly once, so a launch
+// took as long as its slowest pair: 2 planes a workgroup brought k_stage_xy of
+// 512 leaves from 389 to 256 us (4: 277, 8: 330).
+__device__ __forceinline__ void pick_planes(const Sched& sc, int lc, int& leaf, int& k0, int& k1) {
+  const int b = blockIdx.x;
+  const int i = sc.mode != 0 && sc.xcd_remap ? b >> 3 : b;
+  leaf = sc.mode == 0 ? sc.leaf0 : sc.xcd_remap ? (b & 7) * sc.per_xcd + (i >> lc) : i >> lc;
+  k0 = (i & ((1 << lc) - 1)) << (4 - lc);
+  k1 = k0 + (NB >> lc);
+}
+
 // (1) of the stage update for whole columns: thread (tx, ty) streams its
 // column through the planes, with the z slope of cell k+1 and the flux of face
 // k+1/2 in registers, and writes (F_{k+1/2} - F_{k-1/2}) * rdz of every cell
 // to a.Zd (the state layout).  No LDS, no barrier.
 template <int PH, int FLUX, int LIM, int AR>
-__global__ void __launch_bounds__(WGS, 2) k_stage_zcol(Geo g, StageArgs a, const double* __restrict__ pp, Sched sc) {
+__global__ void __launch_bounds__(WGS, 2) k_stage_zcol(Geo g, StageArgs a, const double* __restrict__ pp, Sched sc, int lc) {
   constexpr int ND = 3;
   constexpr int NV = Sys<ND, PH>::NV;
   const PhysParams P = load_phys(pp);
   if (pp[PP_DT] == 0.0) return;  // a device-timed run that has reached its end time
-  const int leaf = pick_leaf(sc, blockIdx.x);
+  int leaf, k0, k1;
+  pick_planes(sc, lc, leaf, k0, k1);
   if (leaf >= g.n) return;
   const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
   const size_t vs = (size_t)g.n * g.ncell;
@@ -1006,16 +1021,19 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_zcol(Geo g, StageArgs a, const
   double V0[NV], V1[NV], C2[NV], VLz[NV], Flo[NV];
   {
     double vm2[NV], vm1[NV], c[NV], lo[NV], hi[NV], vlm1[NV];
-    own_prim<ND, PH>(g, a.Uin, leaf, tx, ty, -2, vm2, P);
-    own_prim<ND, PH>(g, a.Uin, leaf, tx, ty, -1, vm1, P);
-    load_strided<NV>(own, vs, c);
+    own_prim<ND, PH>(g, a.Uin, leaf, tx, ty, k0 - 2, vm2, P);
+    own_prim<ND, PH>(g, a.Uin, leaf, tx, ty, k0 - 1, vm1, P);
+    load_strided<NV>(own + k0 * NB * NB, vs, c);
     cons2prim<ND, PH>(c, V0, P);
-    load_strided<NV>(own + NB * NB, vs, c);
+    load_strided<NV>(own + (k0 + 1) * NB * NB, vs, c);
     cons2prim<ND, PH>(c, V1, P);
-    load_strided<NV>(own + 2 * NB * NB, vs, C2);
+    if (k0 + 2 < NB)
+      load_strided<NV>(own + (k0 + 2) * NB * NB, vs, C2);
+    else
+      load_strided<NV>(zptr, zvs, C2);
     muscl<NV, LIM>(vm2, vm1, V0, lo, vlm1, thz);
     muscl<NV, LIM>(vm1, V0, V1, lo, hi, thz);
-    if (kd4 == NB_SAME || kd4 == NB_BND) {
+    if (k0 > 0 || kd4 == NB_SAME || kd4 == NB_BND) {
       riemann<ND, PH, FLUX, 2>(vlm1, lo, Flo, P);
     } else {
       cf_flux<NV, ND>(g, leaf, 4, kd4, tx, ty, Flo);
@@ -1023,13 +1041,14 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_zcol(Geo g, StageArgs a, const
 #pragma unroll
     for (int v = 0; v < NV; v++) VLz[v] = hi[v];
   }
-  for (int k = 0; k < NB; k++) {
+  for (int k = k0; k < k1; k++) {
     double V2[NV], VR1[NV], VL1[NV], Fhi[NV];
     cons2prim<ND, PH>(C2, V2, P);
     const int pn = k + 3;
-    if (pn < NB)
+    if (pn >= k1 + 2) {
+    } else if (pn < NB)
       load_strided<NV>(own + pn * NB * NB, vs, C2);
-    else if (pn < NB + 2)
+    else
       load_strided<NV>(zptr + (pn - NB) * zls, zvs, C2);
     muscl<NV, LIM>(V0, V1, V2, VR1, VL1, thz);
     if (k == NB - 1 && !(kd5 == NB_SAME || kd5 == NB_BND)) {
@@ -1056,7 +1075,7 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_zcol(Geo g, StageArgs a, const
 // stored and no slope phase or barrier is needed), then the divergence and
 // the SSP combination.  Two barriers per plane, 68 KB of LDS for MHD.
 template <int PH, int FLUX, int LIM, int AR>
-__global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const double* __restrict__ pp, Sched sc) {
+__global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const double* __restrict__ pp, Sched sc, int lc) {
   constexpr int ND = 3;
   using S = Sys<ND, PH>;
   constexpr int NV = S::NV;
@@ -1096,7 +1115,7 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
   const int rdst = (ry + 2) * PW + rx + 2;
 
   for (int iter = 0;; iter++) {
-    int leaf;
+    int leaf, k0 = 0, k1 = NB;  // the leaf and its planes k0 .. k1 - 1
     if (sc.mode == 2) {
       if (tid == 0) sLeaf = queue_next(sc, g.n);
       __syncthreads();
@@ -1104,7 +1123,7 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
       __syncthreads();
     } else {
       if (iter) break;
-      leaf = pick_leaf(sc, blockIdx.x);
+      pick_planes(sc, lc, leaf, k0, k1);
     }
     if (leaf >= g.n) break;
 
@@ -1144,10 +1163,10 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
     }
 
     double Cq[NV], Cr[NV], Ui[NV], Uo[NV], Zk[NV];
-    load_strided<NV>(own, vs, Cq);
-    if (ring) load_strided<NV>(rptr, rvs, Cr);
+    load_strided<NV>(own + k0 * NB * NB, vs, Cq);
+    if (ring) load_strided<NV>(rptr + k0 * rks, rvs, Cr);
 
-    for (int k = 0; k < NB; k++) {
+    for (int k = k0; k < k1; k++) {
       // (2) plane k (own cell and ring cell) to LDS; the next plane's loads,
       // U^n and the z divergence of this plane issued for phase 5
       {
@@ -1159,13 +1178,13 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
           Ui[v] = Cq[v];
         }
       }
-      if (k + 1 < NB) load_strided<NV>(own + (k + 1) * NB * NB, vs, Cq);
+      if (k + 1 < k1) load_strided<NV>(own + (k + 1) * NB * NB, vs, Cq);
       if (ring) {
         double w[NV];
         cons2prim<ND, PH>(Cr, w, P);
 #pragma unroll
         for (int v = 0; v < NV; v++) sP[v][rdst] = w[v];
-        if (k + 1 < NB) load_strided<NV>(rptr + (k + 1) * rks, rvs, Cr);
+        if (k + 1 < k1) load_strided<NV>(rptr + (k + 1) * rks, rvs, Cr);
       }
       if (a.stage > 1) load_strided<NV>(ownn + k * NB * NB, vs, Uo);
       load_strided<NV>(zdp + k * NB * NB, vs, Zk);
@@ -1173,7 +1192,7 @@ __global__ void __launch_bounds__(WGS, 2) k_stage_xy(Geo g, StageArgs a, const d
 
       // (3)+(4) face fluxes; a y face is solved as an x face of the state
       // with its x and y components exchanged (as in k_stage_tile)
-      for (int t = tid; t < 2 * NFX; t += WGS) {
+      for (int t = (tid + 64 * k) & (WGS - 1); t < 2 * NFX; t += WGS) {
         const bool yd = t >= NFX;
         const int u = yd ? t - NFX : t;
         int r, m, bl, st;
@@ -1562,8 +1581,7 @@ constexpr bool in_ilp_unit() {
 #define AMRV_ZSPLIT_LAUNCHER launch_stage_zsplit
 #define AMRV_ZSPLIT_AR 0
 #endif
-// z columns over every leaf (one workgroup per leaf, XCD remap as the
-// schedule's), then the x/y planes in the schedule the forest uses
+// z columns over every leaf (XCD remap as the schedule's), then the x/y planes in the schedule the forest uses
 hipError_t AMRV_ZSPLIT_LAUNCHER(const Geo& g, const LaunchCfg& c, const StageArgs& a, const double* physp,
                                 const Sched& s, int grid, hipStream_t st) {
   Sched zs = s;
@@ -1572,12 +1590,21 @@ hipError_t AMRV_ZSPLIT_LAUNCHER(const Geo& g, const LaunchCfg& c, const StageArg
     zs.mode = 1;
     zgrid = s.xcd_remap ? 8 * ((g.n + 7) / 8) : g.n;
   }
+  // log2 of the workgroups per leaf: 8 for the planes, each on its own; 2 for the
+  // columns, which form two planes' primitives and a face again per piece; more
+  // of them where the leaves are too few for two workgroups per CU (27 leaves,
+  // a stage: 2 and 8 workgroups 84 us, 1 and 8 109 us; 512: 344 and 344 us)
+  int zl = 1, xl = 3;
+  while (zl < 3 && (zgrid << zl) < 512) zl++;
+  if ((zgrid << xl) < 256) xl = 4;
   dispatch(c, [&](auto nd, auto ph, auto fl, auto lm) {
     constexpr int ND = decltype(nd)::value, FL = decltype(fl)::value, LM = decltype(lm)::value;
     constexpr int PH = decltype(ph)::value;
     if constexpr (ND == 3 && PH == PH_MHD) {
-      hipLaunchKernelGGL((k_stage_zcol<PH, FL, LM, AMRV_ZSPLIT_AR>), dim3(zgrid), dim3(WGS), 0, st, g, a, physp, zs);
-      hipLaunchKernelGGL((k_stage_xy<PH, FL, LM, AMRV_ZSPLIT_AR>), dim3(grid), dim3(WGS), 0, st, g, a, physp, s);
+      hipLaunchKernelGGL((k_stage_zcol<PH, FL, LM, AMRV_ZSPLIT_AR>), dim3(zgrid << zl), dim3(WGS), 0, st, g, a, physp,
+                         zs, zl);
+      hipLaunchKernelGGL((k_stage_xy<PH, FL, LM, AMRV_ZSPLIT_AR>), dim3(s.mode == 2 ? grid : zgrid << xl), dim3(WGS),
+                         0, st, g, a, physp, s, xl);
     }
   });
   return hipGetLastError();
