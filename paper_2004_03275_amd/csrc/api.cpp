@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -108,6 +109,60 @@ namespace amrv {
 int set_error(int code, const char* msg) { return fail(code, msg); }
 }  // namespace amrv
 
+// Pinned words a kernel leaves a call's result in: read after the call's own
+// synchronisation, without a copy from device to pageable memory (with it, the
+// clearing launch and the upload of c_h a host-chosen step of 84 leaves took 110
+// us, without 84).  Cache lines
+// of one page for all forests, more pages beyond 64 of them, freed when empty
+// except for one, which stays for the next forest (a regrid makes one, and the
+// allocation takes longer than a step).
+class HostWords {
+  struct Page {
+    unsigned long long* at;
+    uint64_t used;
+  };
+  std::mutex mu;
+  std::vector<Page> pages;
+  static constexpr int LINE = 8;
+
+ public:
+  unsigned long long* take() {
+    std::lock_guard<std::mutex> lock(mu);
+    for (Page& p : pages)
+      for (int i = 0; i < 64; i++)
+        if (!(p.used >> i & 1)) {
+          p.used |= uint64_t(1) << i;
+          return p.at + LINE * i;
+        }
+    void* q = nullptr;
+    try {
+      pages.reserve(pages.size() + 1);
+    } catch (...) {
+      return nullptr;
+    }
+    if (hipHostMalloc(&q, 64 * LINE * sizeof(unsigned long long), hipHostMallocPortable) != hipSuccess) return nullptr;
+    pages.push_back({static_cast<unsigned long long*>(q), 1});
+    return pages.back().at;
+  }
+  void give(const unsigned long long* w) {
+    std::lock_guard<std::mutex> lock(mu);
+    for (size_t k = 0; k < pages.size(); k++) {
+      Page& p = pages[k];
+      if (w < p.at || w >= p.at + 64 * LINE) continue;
+      p.used &= ~(uint64_t(1) << ((w - p.at) / LINE));
+      if (p.used == 0 && pages.size() > 1) {
+        (void)hipHostFree(p.at);
+        pages.erase(pages.begin() + k);
+      }
+      return;
+    }
+  }
+};
+HostWords& host_words() {
+  static HostWords* w = new HostWords;  // outlives every forest, also those destroyed at exit
+  return *w;
+}
+
 struct amrv_forest {
   amrv_config cfg{};
   Tables tab;
@@ -133,6 +188,8 @@ struct amrv_forest {
   hipGraphExec_t dexec = nullptr;  // DGRAPH_STEPS device-timed steps
   hipGraph_t dgraph = nullptr;
   double dt_tend = 0.0;            // t_end baked into the captured device-timed steps
+  unsigned long long* host = nullptr;  // pinned words for results (HostWords)
+  bool third_clear = false;        // amrv_max_dt's reduction slots are clear
   int64_t dsteps = 0;              // device-timed steps launched directly since (for the same t_end)
   bool prof = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev;  // recorded pairs
@@ -303,10 +360,28 @@ void drop_graph(amrv_forest* f) {
   f->graph_valid = false;
 }
 
+StepClock step_clock(const amrv_forest* f, double t_end) {
+  return {f->red, f->cnt, f->pp, f->cfg.cfl, t_end, f->cfg.glm_cr, f->cfg.physics == AMRV_MHD_GLM};
+}
+
 // a device-timed step: dt from the previous fold, then the step with a fold
 int enqueue_device_step(amrv_forest* f, double t_end, bool assume_valid = false) {
-  const StepClock c{f->red, f->cnt, f->pp, f->cfg.cfl, t_end, f->cfg.glm_cr, f->cfg.physics == AMRV_MHD_GLM};
+  const StepClock c = step_clock(f, t_end);
   return enqueue_step(f, &c, assume_valid);
+}
+
+int need_host(amrv_forest* f) {
+  if (!f->host) f->host = host_words().take();
+  return f->host ? AMRV_OK : fail(AMRV_ENOMEM, "pinned host memory");
+}
+
+// wait for the kernel that leaves its result in f->host (if that fails, the
+// words are given up: a kernel may still write them)
+int host_sync(amrv_forest* f) {
+  const hipError_t e = hipStreamSynchronize(f->st);
+  if (e == hipSuccess) return AMRV_OK;
+  f->host = nullptr;
+  return hip_fail(e, "hipStreamSynchronize");
 }
 
 // before replaying a captured step (which assumes it): the restriction of
@@ -522,6 +597,7 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
 int amrv_forest_destroy(amrv_forest* f) {
   if (!f) return AMRV_OK;
   drop_graph(f);
+  if (f->host) host_words().give(f->host);
   delete f;
   return AMRV_OK;
 }
@@ -575,22 +651,23 @@ int amrv_get_state(amrv_forest* f, double* U, int64_t nd, int32_t on_device) {
 
 int amrv_max_dt(amrv_forest* f, double* dt_out) {
   if (!f || !dt_out) return fail(AMRV_EINVAL, "null argument");
-  HIPCHK(launch_reset_u32((unsigned*)f->red, 4 * RED_BUF, f->st));
-  HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->cnt, f->st));
-  unsigned long long* res = f->red + 2 * RED_BUF;
-  HIPCHK(launch_red_result(f->red, f->cnt, res, f->st));
-  unsigned long long h[3] = {0, 0, 0};
-  HIPCHK(hipMemcpyAsync(h, res, sizeof h, hipMemcpyDeviceToHost, f->st));
-  HIPCHK(hipStreamSynchronize(f->st));
+  int rc = need_host(f);
+  if (rc) return rc;
+  unsigned long long* third = f->red + 2 * RED_BUF;
+  if (!f->third_clear) HIPCHK(launch_reset_u32((unsigned*)third, 2 * RED_BUF, f->st));
+  f->third_clear = false;
+  HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, third, nullptr, f->st));
+  HIPCHK(launch_red_result(f->red, f->cnt, f->pp, f->host, f->st));
+  f->third_clear = true;
+  rc = host_sync(f);
+  if (rc) return rc;
   f->fold_valid = true;
-  if (h[2]) return fail(AMRV_ENONPHYSICAL, "non-physical state (rho <= 0, p <= 0 or NaN)");
+  if (f->host[2]) return fail(AMRV_ENONPHYSICAL, "non-physical state (rho <= 0, p <= 0 or NaN)");
   double smax, cmax;
-  std::memcpy(&smax, &h[0], 8);
-  std::memcpy(&cmax, &h[1], 8);
+  std::memcpy(&smax, &f->host[0], 8);
+  std::memcpy(&cmax, &f->host[1], 8);
   if (!(smax > 0.0)) return fail(AMRV_ENONPHYSICAL, "zero signal speed");
   f->ch = cmax;
-  int rc = set_scalars(f, PP_CH, {cmax});
-  if (rc) return rc;
   *dt_out = f->cfg.cfl / smax;
   return AMRV_OK;
 }
@@ -626,9 +703,9 @@ int amrv_advance_cfl(amrv_forest* f, int32_t nsteps, double t_end, double* t, in
   if (!std::isfinite(*t) || std::isnan(t_end)) return fail(AMRV_EINVAL, "bad time");
   // initial fold: the Courant reduction of the current state, unless the
   // last step of the previous call (or amrv_max_dt) left it in place
-  HIPCHK(launch_reset_u32(f->cnt + CNT_ERR, 3, f->st));
-  int rc = set_scalars(f, PP_T, {*t});
+  int rc = need_host(f);
   if (rc) return rc;
+  HIPCHK(launch_run_begin(step_clock(f, t_end), *t, f->st));
   if (!f->fold_valid) {
     HIPCHK(launch_reset_u32((unsigned*)f->red, 4 * RED_BUF, f->st));
     HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, f->red, f->cnt, f->st));
@@ -667,22 +744,18 @@ int amrv_advance_cfl(amrv_forest* f, int32_t nsteps, double t_end, double* t, in
     if (rc) return rc;
     f->dsteps++;
   }
-  double th = 0.0;
-  unsigned cw[2] = {0, 0};
-  HIPCHK(hipMemcpyAsync(&th, f->pp + PP_T, sizeof th, hipMemcpyDeviceToHost, f->st));
-  HIPCHK(hipMemcpyAsync(cw, f->cnt + CNT_ERR, sizeof cw, hipMemcpyDeviceToHost, f->st));
-  HIPCHK(hipStreamSynchronize(f->st));
-  *t = th;
-  if (taken) *taken = (int32_t)cw[1];
+  HIPCHK(launch_run_result(step_clock(f, t_end), f->host, f->st));
+  rc = host_sync(f);
+  if (rc) return rc;
+  const int64_t done = (int64_t)f->host[3];
+  const bool bad = f->host[2] != 0;
+  std::memcpy(t, &f->host[0], 8);
+  if (taken) *taken = (int32_t)done;
   // every step folded the Courant reduction of its result: it stays valid
-  f->fold_valid = (int64_t)cw[1] == (int64_t)nsteps && !cw[0];
+  f->fold_valid = done == (int64_t)nsteps && !bad;
   // the GLM speed of the latest fold (the next amrv_advance needs it)
-  if (f->cfg.physics == AMRV_MHD_GLM) {
-    double ch = 0.0;
-    HIPCHK(hipMemcpy(&ch, f->pp + PP_CH, sizeof ch, hipMemcpyDeviceToHost));
-    f->ch = ch;
-  }
-  if (cw[0]) return fail(AMRV_ENONPHYSICAL, "non-physical state during a device-timed run");
+  if (f->cfg.physics == AMRV_MHD_GLM) std::memcpy(&f->ch, &f->host[1], 8);
+  if (bad) return fail(AMRV_ENONPHYSICAL, "non-physical state during a device-timed run");
   return AMRV_OK;
 }
 

@@ -118,12 +118,17 @@ hipError_t launch_transfer(const Geo& from, const double* Uf, const Geo& to, dou
 hipError_t launch_set_scalars(double* dst, const double* src_host_vals, int n, hipStream_t st);
 hipError_t launch_reset_u32(unsigned* p, int n, hipStream_t st);
 // Courant reduction: RED_SLOTS slots of RED_STRIDE 64-bit words (a cache line
-// each), words 0..2 of each in use, in two buffers; RED_WORDS with the three
-// result words that follow them
-constexpr int RED_SLOTS = 256, RED_STRIDE = 8, RED_BUF = RED_SLOTS * RED_STRIDE, RED_WORDS = 2 * RED_BUF + 4;
-// the maxima of the current buffer's slots into three words
-hipError_t launch_red_result(const unsigned long long* red, const unsigned* cnt, unsigned long long* out,
+// each), words 0..2 of each in use, in two buffers (StepClock) and a third for
+// amrv_max_dt, clear between calls
+constexpr int RED_SLOTS = 256, RED_STRIDE = 8, RED_BUF = RED_SLOTS * RED_STRIDE, RED_WORDS = 3 * RED_BUF;
+// the maxima of the third buffer's slots into host words 0..2, c_h into the
+// parameter block and both into the current buffer, and the third cleared
+hipError_t launch_red_result(unsigned long long* red, const unsigned* cnt, double* pp, unsigned long long* host,
                              hipStream_t st);
+// the start and the result of a device-timed run: its time and cleared counts;
+// time, c_h, error flag and steps taken into host words 0..3
+hipError_t launch_run_begin(const StepClock& c, double t, hipStream_t st);
+hipError_t launch_run_result(const StepClock& c, unsigned long long* host, hipStream_t st);
 // A device-timed step k reads the Courant slots of buffer k & 1 and folds its
 // result's into the other.  Beginning: dt = min(cfl / smax, t_end - t), c_h and
 // the GLM damping factor into the parameter block, the time after the step and

@@ -1401,7 +1401,7 @@ __global__ void __launch_bounds__(WGS) k_cfl(Geo g, const double* __restrict__ U
     smax = sb > smax ? sb : smax;
     cmax = cb > cmax ? cb : cmax;
   }
-  cfl_fold(red + (cnt[CNT_STEP] & 1) * RED_BUF, smax, cmax, bad);
+  cfl_fold(red + (cnt ? (cnt[CNT_STEP] & 1) * RED_BUF : 0), smax, cmax, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -1791,22 +1791,56 @@ hipError_t launch_step_begin(const StepClock& c, bool whole, hipStream_t st) {
   return hipGetLastError();
 }
 
-// the current slots' result into out[0..2] (the slots keep their values)
-__global__ void __launch_bounds__(WGS) k_red_result(const unsigned long long* red, const unsigned* cnt,
-                                                    unsigned long long* out) {
+// amrv_max_dt's result (internal.hpp)
+__global__ void __launch_bounds__(WGS) k_red_result(unsigned long long* red, const unsigned* cnt, double* pp,
+                                                    unsigned long long* host) {
+  unsigned long long* third = red + 2 * RED_BUF;
   unsigned long long sb, cb;
   int bad;
-  red_all(red + (cnt[CNT_STEP] & 1) * RED_BUF, sb, cb, bad);
+  red_all(third, sb, cb, bad);
+  const unsigned at = (cnt[CNT_STEP] & 1) * RED_BUF;
+#pragma unroll
+  for (int w = 0; w < 3; w++) {
+    const int i = threadIdx.x * RED_STRIDE + w;
+    third[i] = 0ull;
+    red[i + (at ^ RED_BUF)] = 0ull;
+    red[i + at] = threadIdx.x ? 0ull : w == 0 ? sb : w == 1 ? cb : (unsigned long long)bad;
+  }
   if (threadIdx.x == 0) {
-    out[0] = sb;
-    out[1] = cb;
-    out[2] = (unsigned long long)bad;
+    host[0] = sb;
+    host[1] = cb;
+    host[2] = (unsigned long long)bad;
+    if (!bad && sb) pp[PP_CH] = __longlong_as_double((long long)cb);
   }
 }
 
-hipError_t launch_red_result(const unsigned long long* red, const unsigned* cnt, unsigned long long* out,
+hipError_t launch_red_result(unsigned long long* red, const unsigned* cnt, double* pp, unsigned long long* host,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_red_result, dim3(1), dim3(WGS), 0, st, red, cnt, out);
+  hipLaunchKernelGGL(k_red_result, dim3(1), dim3(WGS), 0, st, red, cnt, pp, host);
+  return hipGetLastError();
+}
+
+__global__ void k_run_begin(StepClock c, double t) {
+  c.pp[PP_T] = t;
+  c.cnt[CNT_ERR] = 0u;
+  c.cnt[CNT_TAKEN] = 0u;
+  c.cnt[CNT_TAKEN1] = 0u;
+}
+
+hipError_t launch_run_begin(const StepClock& c, double t, hipStream_t st) {
+  hipLaunchKernelGGL(k_run_begin, dim3(1), dim3(1), 0, st, c, t);
+  return hipGetLastError();
+}
+
+__global__ void k_run_result(StepClock c, unsigned long long* host) {
+  host[0] = (unsigned long long)__double_as_longlong(c.pp[PP_T]);
+  host[1] = (unsigned long long)__double_as_longlong(c.pp[PP_CH]);
+  host[2] = c.cnt[CNT_ERR];
+  host[3] = c.cnt[CNT_TAKEN];
+}
+
+hipError_t launch_run_result(const StepClock& c, unsigned long long* host, hipStream_t st) {
+  hipLaunchKernelGGL(k_run_result, dim3(1), dim3(1), 0, st, c, host);
   return hipGetLastError();
 }
 
