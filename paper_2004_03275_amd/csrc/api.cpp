@@ -242,8 +242,11 @@ int stage_grid(const amrv_forest* f, int mode) {
 // restriction skipped when the buffer already holds it
 int enqueue_ghosts(amrv_forest* f, const Geo& geo, const double* U, bool fluxes, bool restrict_too = true) {
   const int nr = (int)f->tab.rlist.size(), np = (int)f->tab.plist.size();
-  if (nr && restrict_too) HIPCHK(launch_restrict(geo, f->lc, U, f->rlist, nr, f->st));
-  if (np) HIPCHK(launch_prolong(geo, f->lc, U, f->pp, f->plist, np, fluxes, f->st));
+  // 1D and 2D: one launch for both (k_prolong_flux)
+  const bool together = f->tab.nd < 3;
+  if (nr && restrict_too && !together) HIPCHK(launch_restrict(geo, f->lc, U, f->rlist, nr, f->st));
+  if (np)
+    HIPCHK(launch_prolong(geo, f->lc, U, f->pp, f->plist, np, fluxes, f->rlist, together ? nr : 0, f->st));
   return AMRV_OK;
 }
 

@@ -97,12 +97,14 @@ struct LaunchCfg {
   int arith;    // 0 correctly rounded (default), 1 fast arithmetic where the stage kernel has that form
 };
 
+// coarse-side ghost slabs (restriction) of a 3D forest
 hipError_t launch_restrict(const Geo& g, const LaunchCfg& c, const double* U, const int32_t* list, int nlist,
                            hipStream_t st);
 // fine-side ghost slabs (prolongation) and, with fluxes, the fine-side face
-// fluxes of the same coarse-fine faces
+// fluxes of the same coarse-fine faces; in 1D and 2D the coarse side's nr slots
+// of rlist too
 hipError_t launch_prolong(const Geo& g, const LaunchCfg& c, const double* U, const double* physp,
-                          const int32_t* list, int nlist, bool fluxes, hipStream_t st);
+                          const int32_t* list, int nlist, bool fluxes, const int32_t* rlist, int nr, hipStream_t st);
 hipError_t launch_stage(const Geo& g, const LaunchCfg& c, const StageArgs& a, const double* physp, const Sched& s,
                         int grid, hipStream_t st);
 hipError_t launch_cfl(const Geo& g, const LaunchCfg& c, const double* U, const double* physp,
