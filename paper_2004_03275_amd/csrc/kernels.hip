@@ -1500,6 +1500,37 @@ __device__ __forceinline__ void rho_p(const Geo& g, const double* __restrict__ U
   p = pressure<ND, PH>(v, P);
 }
 
+// the estimator of a cell: its (density, pressure) q0 and, per dimension, those
+// of its lower and upper neighbours
+template <int ND>
+__device__ __forceinline__ double lohner_cell(double2 q0, const double2* lo, const double2* hi, double eps, double wr,
+                                              double wp) {
+  double nr = 0.0, dr = 0.0, np = 0.0, dp = 0.0;
+#pragma unroll
+  for (int d = 0; d < ND; d++) {
+    const double d2r = hi[d].x - 2.0 * q0.x + lo[d].x;
+    const double ddr =
+        fabs(hi[d].x - q0.x) + fabs(q0.x - lo[d].x) + eps * (fabs(hi[d].x) + 2.0 * fabs(q0.x) + fabs(lo[d].x));
+    const double d2p = hi[d].y - 2.0 * q0.y + lo[d].y;
+    const double ddp =
+        fabs(hi[d].y - q0.y) + fabs(q0.y - lo[d].y) + eps * (fabs(hi[d].y) + 2.0 * fabs(q0.y) + fabs(lo[d].y));
+    nr = d == 0 ? d2r * d2r : nr + d2r * d2r;
+    dr = d == 0 ? ddr * ddr : dr + ddr * ddr;
+    np = d == 0 ? d2p * d2p : np + d2p * d2p;
+    dp = d == 0 ? ddp * ddp : dp + ddp * ddp;
+  }
+  const double er = dr > 0.0 ? sqrt(nr / dr) : 0.0;
+  const double ep = dp > 0.0 ? sqrt(np / dp) : 0.0;
+  return wr * er + wp * ep;
+}
+
+// 3D: a thread walks the column (tx, ty) with the planes below and above in
+// registers and the plane's own values, with a ring of one ghost cell, in LDS
+// (two planes, so one barrier each; the ring is another wave's every plane).
+// Forming each cell's density and pressure once instead of seven times took
+// 19,384 leaves from 2,561 to 1,146 us (their state at the copy's rate: 620 us;
+// four divisions and two square roots a cell).  1D and 2D form them from the
+// state.
 template <int ND, int PH>
 __global__ void __launch_bounds__(WGS) k_lohner(Geo g, const double* __restrict__ U, const double* __restrict__ pp,
                                                 const double* __restrict__ lp, int max_level, double* emax_out,
@@ -1510,34 +1541,46 @@ __global__ void __launch_bounds__(WGS) k_lohner(Geo g, const double* __restrict_
   const PhysParams P = load_phys(pp);
   const double eps = lp[LP_EPS], wr = lp[LP_WRHO], wp = lp[LP_WP];
   double m = 0.0;
-  for (int cell = threadIdx.x; cell < g.ncell; cell += WGS) {
-    const int x = cell % g.nx;
-    const int y = ND > 1 ? (cell / g.nx) % g.nx : 0;
-    const int z = ND > 2 ? cell / (g.nx * g.nx) : 0;
-    double r0, p0;
-    rho_p<ND, PH>(g, U, leaf, x, y, z, P, r0, p0);
-    double nr = 0.0, dr = 0.0, np = 0.0, dp = 0.0;
-#pragma unroll
-    for (int d = 0; d < ND; d++) {
-      int lo[3] = {x, y, z}, hi[3] = {x, y, z};
-      lo[d] -= 1;
-      hi[d] += 1;
-      double rm, pm, rp, pq;
-      rho_p<ND, PH>(g, U, leaf, lo[0], lo[1], lo[2], P, rm, pm);
-      rho_p<ND, PH>(g, U, leaf, hi[0], hi[1], hi[2], P, rp, pq);
-      const double d2r = rp - 2.0 * r0 + rm;
-      const double ddr = fabs(rp - r0) + fabs(r0 - rm) + eps * (fabs(rp) + 2.0 * fabs(r0) + fabs(rm));
-      const double d2p = pq - 2.0 * p0 + pm;
-      const double ddp = fabs(pq - p0) + fabs(p0 - pm) + eps * (fabs(pq) + 2.0 * fabs(p0) + fabs(pm));
-      nr = d == 0 ? d2r * d2r : nr + d2r * d2r;
-      dr = d == 0 ? ddr * ddr : dr + ddr * ddr;
-      np = d == 0 ? d2p * d2p : np + d2p * d2p;
-      dp = d == 0 ? ddp * ddp : dp + ddp * ddp;
+  if constexpr (ND == 3) {
+    constexpr int RW = NB + 2;
+    __shared__ double2 sq[2][RW * RW];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4, at = (ty + 1) * RW + tx + 1;
+    const int side = (tid >> 4) & 3, a = tid & 15;
+    const int rx = side == 0 ? -1 : side == 1 ? NB : a, ry = side == 2 ? -1 : side == 3 ? NB : a;
+    double2 below, here;
+    rho_p<ND, PH>(g, U, leaf, tx, ty, -1, P, below.x, below.y);
+    rho_p<ND, PH>(g, U, leaf, tx, ty, 0, P, here.x, here.y);
+    for (int z = 0; z < NB; z++) {
+      double2* q = sq[z & 1];
+      double2 above;
+      q[at] = here;
+      if ((tid >> 6) == (z & 3)) {
+        double2 w;
+        rho_p<ND, PH>(g, U, leaf, rx, ry, z, P, w.x, w.y);
+        q[(ry + 1) * RW + rx + 1] = w;
+      }
+      rho_p<ND, PH>(g, U, leaf, tx, ty, z + 1, P, above.x, above.y);
+      __syncthreads();
+      const double2 lo[3] = {q[at - 1], q[at - RW], below}, hi[3] = {q[at + 1], q[at + RW], above};
+      const double e = lohner_cell<ND>(here, lo, hi, eps, wr, wp);
+      if (e > m) m = e;
+      below = here;
+      here = above;
     }
-    const double er = dr > 0.0 ? sqrt(nr / dr) : 0.0;
-    const double ep = dp > 0.0 ? sqrt(np / dp) : 0.0;
-    const double e = wr * er + wp * ep;
-    if (e > m) m = e;
+  } else {
+    for (int cell = threadIdx.x; cell < g.ncell; cell += WGS) {
+      const int x = cell % g.nx;
+      const int y = ND > 1 ? (cell / g.nx) % g.nx : 0;
+      double2 q0, lo[ND], hi[ND];
+      rho_p<ND, PH>(g, U, leaf, x, y, 0, P, q0.x, q0.y);
+#pragma unroll
+      for (int d = 0; d < ND; d++) {
+        rho_p<ND, PH>(g, U, leaf, x - (d == 0), y - (d == 1), 0, P, lo[d].x, lo[d].y);
+        rho_p<ND, PH>(g, U, leaf, x + (d == 0), y + (d == 1), 0, P, hi[d].x, hi[d].y);
+      }
+      const double e = lohner_cell<ND>(q0, lo, hi, eps, wr, wp);
+      if (e > m) m = e;
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
