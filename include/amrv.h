@@ -227,7 +227,7 @@ int amrv_mlp_train(const uint16_t* X, const float* y, const int32_t* order, int6
  * training loops, harnesses that forbid hipMalloc).  Same arguments,
  * arithmetic and results as amrv_mlp_train; the scratch lives in a
  * library-held static device array of amrv_mlp_train_workspace_bytes(4096)
- * bytes (about 3.1 MiB), one per GPU, resolved on the first call on a
+ * bytes (about 5.1 MiB), one per GPU, resolved on the first call on a
  * device and kept until the process ends.  batch <= 4096 (larger:
  * AMRV_ENOMEM).  The call allocates nothing: no hipMalloc, no hipFree.
  * Every call on one GPU shares that GPU's scratch and leaves its contents

@@ -10,10 +10,10 @@
 //   k_mlp_infer     refine and coarsen logits of all leaves: bfloat16 MFMA
 //                   products (v_mfma_f32_16x16x32_bf16), binary32 accumulation,
 //                   and each leaf's three-way flag from its two logits
-//   k_mlp_grad      a batch's forward pass, class-weighted binary cross-entropy
-//                   and backward pass (weight gradients again as bfloat16 MFMA
-//                   products with binary32 accumulation), partial gradients
-//   k_mlp_step      their sum in a fixed order, Adam
+//   k_mlp_rows      a batch's forward pass, class-weighted binary cross-entropy
+//                   and backward pass
+//   k_mlp_update    its gradients (weight gradients again as bfloat16 MFMA
+//                   products with binary32 accumulation) and Adam
 // Reductions run in a fixed order, so results are deterministic.
 #include <type_traits>
 
@@ -236,32 +236,37 @@ __global__ void __launch_bounds__(256) k_mlp_infer(const uint16_t* __restrict__ 
 // training step: the batch's rows over many workgroups, then one update launch
 // ---------------------------------------------------------------------------
 
-// A step is two launches.  k_mlp_grad: each workgroup takes `rows` rows of the
-// batch through the forward and backward pass with every activation in LDS
-// and writes its own partial gradient (part[workgroup][NPARAM + 1], the last
-// value its loss sum); k_mlp_step adds the partials in workgroup order and
-// applies Adam, so the sums have a fixed order and the result is
-// deterministic.  Bound by latency (0.03 GFLOP a batch of 1,024).  One
-// workgroup per batch, its activations in global scratch, left 255 CUs idle:
-// 1,060 us a batch of 1,024; 32 rows per workgroup (one K step of the
-// 16x16x32 products, 32 workgroups) 13.2 us + 4.0 us.
+// A step is two launches.  k_mlp_rows: each workgroup takes 32 rows of the
+// batch (one K step of the 16x16x32 products) through the forward and backward
+// pass with every activation in LDS and writes what the gradients are made of;
+// k_mlp_update: a wave per 16x16 tile of dW1 and dW2, and per 16 parameters of
+// the rest, runs over all rows of the batch in row order and applies Adam to
+// its own parameters.  Every gradient is one chain over the rows: a sum of the
+// workgroups' partial sums is as exact, but bfloat16 roundings of the weights
+// carry a last-place difference to 3% of a weight within an epoch of small
+// batches.  Bound by latency (0.03 GFLOP a batch of 1,024).  One workgroup per
+// batch took 1,060 us a batch of 1,024; now 9.5 + 11.2 us.
 constexpr int TR = 32;           // rows of a K step
 constexpr int TS = TR + 8;       // LDS row stride of the [feature][row] arrays (16-byte multiples, spread over banks)
 constexpr int HS = MLP_NH + 8;   // and of the [row][unit] arrays
 
-// rows per workgroup: 32, or 64 where 32 would give more than 64 partials (the
-// scratch then stays below that of a whole batch's activations)
-constexpr int mlp_train_rows(int B) { return B <= 64 * TR ? TR : 2 * TR; }
+// what k_mlp_rows leaves for k_mlp_update (mlp_train_scratch_bytes_c)
+struct TrainScratch {
+  uint16_t *xT, *h1T, *dh2T, *dh1T;  // [feature or unit][B]
+  uint16_t* h2;                      // [B][64]
+  float *dh2, *dh1;                  // [B][64], before their rounding
+  float *dz, *loss;                  // [B][2], [B]
+};
 
-__global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X, const float* __restrict__ Y,
-                                                  const int32_t* __restrict__ order, int n, int B, int batch, int rows,
+__global__ void __launch_bounds__(256) k_mlp_rows(const uint16_t* __restrict__ X, const float* __restrict__ Y,
+                                                  const int32_t* __restrict__ order, int n, int B, int batch,
                                                   const float* __restrict__ w, const uint16_t* __restrict__ wb,
-                                                  TrainHyper hp, float* __restrict__ part) {
+                                                  TrainHyper hp, TrainScratch s) {
   __shared__ __attribute__((aligned(16))) uint16_t xT[MLP_NIN * TS];
   __shared__ __attribute__((aligned(16))) uint16_t h1[TR * HS], h1T[MLP_NH * TS], h2[TR * HS];
   __shared__ __attribute__((aligned(16))) uint16_t dh2[TR * HS], dh2T[MLP_NH * TS], dh1T[MLP_NH * TS];
   __shared__ float dh1[TR * (MLP_NH + 1)];
-  __shared__ float zs[TR][MLP_NOUT], dz[TR][MLP_NOUT], ls[TR];
+  __shared__ float zs[TR][MLP_NOUT], dz[TR][MLP_NOUT];
   const int tid = threadIdx.x, wave = tid >> 6, l = tid & 63;
   const int lm = l & 15, lk = 8 * (l >> 4), lq = 4 * (l >> 4);
   const int b0 = batch * B;
@@ -270,15 +275,8 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X
   const float Bv = (float)nvalid;
   const int rt = wave & 1, np = wave >> 1;  // forward: a 16-row tile and half of the output units per wave
 
-  f32x4 g1[8], g2[4];  // dW1, dW2 tiles of this wave
-#pragma unroll
-  for (int i = 0; i < 8; i++) g1[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 4; i++) g2[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float gs = 0.f, gb1 = 0.f;  // W3 (threads 0..127), b3 (128, 129), loss (130), b2 (192..255); b1 (192..255)
-
-  const int rend = min(B, (int)(blockIdx.x + 1) * rows);
-  for (int r0 = blockIdx.x * rows; r0 < rend; r0 += TR) {
+  const int r0 = blockIdx.x * TR;
+  {
     // layer 1; the rows (zeros past the batch's last sample) also to xT
     {
       const int r = r0 + rt * 16 + lm;
@@ -358,11 +356,12 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X
       }
       dz[tid][0] = d[0];
       dz[tid][1] = d[1];
-      ls[tid] = lr;
+      s.dz[(size_t)(r0 + tid) * MLP_NOUT] = d[0];
+      s.dz[(size_t)(r0 + tid) * MLP_NOUT + 1] = d[1];
+      s.loss[r0 + tid] = lr;
     }
     __syncthreads();
-    // dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0] (binary32, then bfloat16); the
-    // W3, b3, b2 gradients and the loss
+    // dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0] (binary32, then bfloat16)
     auto dh2_of = [&](int r, int c, float wr, float wc) -> float {
       return from_bf16(h2[r * HS + c]) > 0.f ? dz[r][0] * wr + dz[r][1] * wc : 0.f;
     };
@@ -372,23 +371,12 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X
       uint16_t t[8];
 #pragma unroll
       for (int j = 0; j < 8; j++) {
-        t[j] = to_bf16(dh2_of(ra + j, c, wr, wc));
+        const float d = dh2_of(ra + j, c, wr, wc);
+        s.dh2[(size_t)(r0 + ra + j) * MLP_NH + c] = d;
+        t[j] = to_bf16(d);
         dh2[(ra + j) * HS + c] = t[j];
       }
       __builtin_memcpy(&dh2T[c * TS + ra], t, 16);
-      if (wave == 3) {
-#pragma unroll 8
-        for (int r = 0; r < TR; r++) gs = gs + dh2_of(r, c, wr, wc);
-      }
-    }
-    if (tid < MLP_NOUT * MLP_NH) {
-      const int o = tid / MLP_NH, c = tid % MLP_NH;
-#pragma unroll 8
-      for (int r = 0; r < TR; r++) gs = gs + dz[r][o] * from_bf16(h2[r * HS + c]);
-    } else if (tid < MLP_NOUT * MLP_NH + MLP_NOUT) {
-      for (int r = 0; r < TR; r++) gs = gs + dz[r][tid - MLP_NOUT * MLP_NH];
-    } else if (tid == MLP_NOUT * MLP_NH + MLP_NOUT) {
-      for (int r = 0; r < TR; r++) gs = gs + ls[r];
     }
     __syncthreads();
     // dh1 = dh2 W2 * [h1 > 0]: 8 tiles, two per wave
@@ -408,75 +396,140 @@ __global__ void __launch_bounds__(256) k_mlp_grad(const uint16_t* __restrict__ X
       }
     }
     __syncthreads();
-    // dW2 += dh2^T h1 (16 tiles), dW1 += dh1^T X (32 tiles), K = 32 rows; b1
-#pragma unroll
-    for (int j = 0; j < 4; j++)
-      g2[j] = mfma(load8(dh2T + (j * 16 + lm) * TS + lk), load8(h1T + (wave * 16 + lm) * TS + lk), g2[j]);
-#pragma unroll
-    for (int j = 0; j < 8; j++)
-      g1[j] = mfma(load8(dh1T + ((j >> 1) * 16 + lm) * TS + lk), load8(xT + ((2 * wave + (j & 1)) * 16 + lm) * TS + lk), g1[j]);
-    if (wave == 3) {
-#pragma unroll 8
-      for (int r = 0; r < TR; r++) gb1 = gb1 + dh1[r * (MLP_NH + 1) + l];
-    }
-    __syncthreads();
-  }
-  float* p = part + (size_t)blockIdx.x * MLP_PART;
-#pragma unroll
-  for (int j = 0; j < 4; j++)
-#pragma unroll
-    for (int i = 0; i < 4; i++) p[MLP_W2 + (j * 16 + lq + i) * MLP_NH + wave * 16 + lm] = g2[j][i];
-#pragma unroll
-  for (int j = 0; j < 8; j++)
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-      p[MLP_W1 + ((j >> 1) * 16 + lq + i) * MLP_NIN + (2 * wave + (j & 1)) * 16 + lm] = g1[j][i];
-  if (tid < MLP_NOUT * MLP_NH + MLP_NOUT + 1) p[MLP_W3 + tid] = gs;  // W3, b3, then the loss sum at NPARAM
-  if (wave == 3) {
-    p[MLP_B2 + l] = gs;
-    p[MLP_B1 + l] = gb1;
+    // the transposed operands and the rows' values to memory, 16 bytes a thread
+    auto put = [&](uint16_t* to, const uint16_t* from) { __builtin_memcpy(to, from, 16); };
+    for (int i = tid; i < MLP_NIN * TR / 8; i += 256)
+      put(s.xT + (size_t)(i >> 2) * B + r0 + 8 * (i & 3), xT + (i >> 2) * TS + 8 * (i & 3));
+    const int u = tid >> 2, q = 8 * (tid & 3);
+    put(s.h1T + (size_t)u * B + r0 + q, h1T + u * TS + q);
+    put(s.dh2T + (size_t)u * B + r0 + q, dh2T + u * TS + q);
+    put(s.dh1T + (size_t)u * B + r0 + q, dh1T + u * TS + q);
+    put(s.h2 + (size_t)(r0 + (tid >> 3)) * MLP_NH + 8 * (tid & 7), h2 + (tid >> 3) * HS + 8 * (tid & 7));
+    for (int i = tid; i < TR * MLP_NH; i += 256)
+      s.dh1[(size_t)r0 * MLP_NH + i] = dh1[(i >> 6) * (MLP_NH + 1) + (i & 63)];
   }
 }
 
-// one parameter per thread: the partial gradients added in workgroup order,
-// Adam on the binary32 master weight, and its bfloat16 operand copies; the
-// thread past the last parameter writes the batch's mean loss
-__global__ void __launch_bounds__(256) k_mlp_step(const float* __restrict__ part, int nparts, int nvalid,
-                                                  float* __restrict__ w, float* __restrict__ am, float* __restrict__ av,
-                                                  uint16_t* __restrict__ wb, TrainHyper hp, float c1, float c2,
-                                                  float* __restrict__ loss_out, float* __restrict__ grad_out) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i > MLP_NPARAM) return;
-  float gr = 0.f;
-  int k = 0;
-  for (; k + 8 <= nparts; k += 8) {
-    float t[8];
+// Workgroups 0..11: the 32 + 16 tiles of dW1 = dh1^T X and dW2 = dh2^T h1, one
+// per wave; 12..15 b1, 16..19 b2, 20..27 W3, 28 b3 and the loss: 16 sums each,
+// their terms staged in LDS (1,024 rows at a time), one lane a sum.  Then Adam
+// on the binary32 master weights and their bfloat16 operand copies.
+constexpr int UPD_WGS = 29, UPD_ROWS = 1024;
+
+__global__ void __launch_bounds__(256) k_mlp_update(TrainScratch s, int B, int nvalid, float* __restrict__ w,
+                                                    float* __restrict__ am, float* __restrict__ av,
+                                                    uint16_t* __restrict__ wb, TrainHyper hp, float c1, float c2,
+                                                    float* __restrict__ loss_out, float* __restrict__ grad_out) {
+  __shared__ __attribute__((aligned(16))) float term[UPD_ROWS * 16];
+  const int tid = threadIdx.x, l = tid & 63, lm = l & 15, lk = 8 * (l >> 4);
+  const int b = blockIdx.x;
+  auto adam = [&](int i, float gr) {
+    if (grad_out) grad_out[i] = gr;
+    const float m = hp.beta1 * am[i] + (1.f - hp.beta1) * gr;
+    const float v = hp.beta2 * av[i] + (1.f - hp.beta2) * gr * gr;
+    am[i] = m;
+    av[i] = v;
+    const float wn = w[i] - hp.lr * (m / c1) / (sqrtf(v / c2) + hp.eps);
+    w[i] = wn;
+    const uint16_t h = to_bf16(wn);
+    if (i < MLP_B1) {
+      wb[MLP_WB_W1 + i] = h;
+    } else if (i >= MLP_W2 && i < MLP_B2) {
+      const int q = i - MLP_W2;
+      wb[MLP_WB_W2 + q] = h;
+      wb[MLP_WB_W2T + (q % MLP_NH) * MLP_NH + q / MLP_NH] = h;
+    } else if (i >= MLP_W3 && i < MLP_B3) {
+      wb[MLP_WB_W3 + i - MLP_W3] = h;
+    }
+  };
+  if (b < 12) {
+    const int tile = 4 * b + (tid >> 6);
+    const bool one = tile < 32;
+    const int mt = one ? tile >> 3 : (tile - 32) >> 2, nt = one ? tile & 7 : tile & 3;
+    const uint16_t* pa = (one ? s.dh1T : s.dh2T) + (size_t)(mt * 16 + lm) * B + lk;
+    const uint16_t* pb = (one ? s.xT : s.h1T) + (size_t)(nt * 16 + lm) * B + lk;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    int k = 0;
+    for (; k + 8 * TR <= B; k += 8 * TR) {
+      bf16x8 ra[8], rb[8];
 #pragma unroll
-    for (int j = 0; j < 8; j++) t[j] = part[(size_t)(k + j) * MLP_PART + i];
+      for (int j = 0; j < 8; j++) {
+        ra[j] = load8(pa + k + j * TR);
+        rb[j] = load8(pb + k + j * TR);
+      }
 #pragma unroll
-    for (int j = 0; j < 8; j++) gr = gr + t[j];
-  }
-  for (; k < nparts; k++) gr = gr + part[(size_t)k * MLP_PART + i];
-  if (i == MLP_NPARAM) {
-    if (loss_out) *loss_out = gr / (float)nvalid;
+      for (int j = 0; j < 8; j++) acc = mfma(ra[j], rb[j], acc);
+    }
+    for (; k < B; k += TR) acc = mfma(load8(pa + k), load8(pb + k), acc);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int row = mt * 16 + 4 * (l >> 4) + i, col = nt * 16 + lm;
+      adam(one ? MLP_W1 + row * MLP_NIN + col : MLP_W2 + row * MLP_NH + col, acc[i]);
+    }
     return;
   }
-  if (grad_out) grad_out[i] = gr;
-  const float m = hp.beta1 * am[i] + (1.f - hp.beta1) * gr;
-  const float v = hp.beta2 * av[i] + (1.f - hp.beta2) * gr * gr;
-  am[i] = m;
-  av[i] = v;
-  const float wn = w[i] - hp.lr * (m / c1) / (sqrtf(v / c2) + hp.eps);
-  w[i] = wn;
-  const uint16_t b = to_bf16(wn);
-  if (i < MLP_B1) {
-    wb[MLP_WB_W1 + i] = b;
-  } else if (i >= MLP_W2 && i < MLP_B2) {
-    const int q = i - MLP_W2;
-    wb[MLP_WB_W2 + q] = b;
-    wb[MLP_WB_W2T + (q % MLP_NH) * MLP_NH + q / MLP_NH] = b;
-  } else if (i >= MLP_W3 && i < MLP_B3) {
-    wb[MLP_WB_W3 + i - MLP_W3] = b;
+  const int c0 = 16 * ((b - 12) & 3), o = b >= 24 ? 1 : 0;  // columns; W3's output
+  float g = 0.f;
+  for (int r0 = 0; r0 < B; r0 += UPD_ROWS) {
+    const int rows = min(UPD_ROWS, B - r0);
+    // eight loads a thread in flight
+    if (b < 20) {
+      const float* src = (b < 16 ? s.dh1 : s.dh2) + (size_t)r0 * MLP_NH + c0;
+      for (int i0 = 0; i0 < rows * 4; i0 += 8 * 256) {
+        float4 t[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+          const int i = min(i0 + j * 256 + tid, rows * 4 - 1);
+          t[j] = *reinterpret_cast<const float4*>(src + (size_t)(i >> 2) * MLP_NH + 4 * (i & 3));
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+          *reinterpret_cast<float4*>(term + 4 * min(i0 + j * 256 + tid, rows * 4 - 1)) = t[j];
+      }
+    } else if (b < 28) {
+      const uint16_t* src = s.h2 + (size_t)r0 * MLP_NH + c0;
+      for (int i0 = 0; i0 < rows * 2; i0 += 8 * 256) {
+        uint16_t t[8][8];
+        float d[8];
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+          const int i = min(i0 + j * 256 + tid, rows * 2 - 1);
+          __builtin_memcpy(t[j], src + (size_t)(i >> 1) * MLP_NH + 8 * (i & 1), 16);
+          d[j] = s.dz[(size_t)(r0 + (i >> 1)) * MLP_NOUT + o];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++) {
+          const int i = min(i0 + j * 256 + tid, rows * 2 - 1);
+#pragma unroll
+          for (int q = 0; q < 8; q++) term[8 * i + q] = d[j] * from_bf16(t[j][q]);
+        }
+      }
+    } else {
+      for (int r = tid; r < rows; r += 256) {
+        term[16 * r] = s.dz[(size_t)(r0 + r) * MLP_NOUT];
+        term[16 * r + 1] = s.dz[(size_t)(r0 + r) * MLP_NOUT + 1];
+        term[16 * r + 2] = s.loss[r0 + r];
+      }
+    }
+    __syncthreads();
+    if (tid < 16) {  // rows is a multiple of 32
+      for (int r = 0; r < rows; r += 32) {
+        float t[32];
+#pragma unroll
+        for (int j = 0; j < 32; j++) t[j] = term[16 * (r + j) + tid];
+#pragma unroll
+        for (int j = 0; j < 32; j++) g = g + t[j];
+      }
+    }
+    __syncthreads();
+  }
+  if (tid >= 16) return;
+  if (b < 28) {
+    adam((b < 16 ? MLP_B1 : b < 20 ? MLP_B2 : MLP_W3 + o * MLP_NH) + c0 + tid, g);
+  } else if (tid < MLP_NOUT) {
+    adam(MLP_B3 + tid, g);
+  } else if (tid == MLP_NOUT && loss_out) {
+    *loss_out = g / (float)nvalid;
   }
 }
 
@@ -524,18 +577,33 @@ size_t mlp_train_scratch_bytes(int B) { return mlp_train_scratch_bytes_c(B); }
 hipError_t launch_mlp_train(const uint16_t* X, const float* Y, const int32_t* order, int n, int B, int first_batch,
                             int nbatch, float* w, float* am, float* av, const TrainHyper& hp, int t0, void* ws,
                             float* loss_out, float* grad_out, hipStream_t st) {
-  const int rows = mlp_train_rows(B), nparts = (B + rows - 1) / rows;
-  uint16_t* wb = (uint16_t*)ws;
-  float* part = (float*)((char*)ws + mlp_align256(2 * (size_t)MLP_WB_COUNT));
+  char* at = (char*)ws;
+  auto take = [&](size_t bytes) {
+    void* p = at;
+    at += mlp_align256(bytes);
+    return p;
+  };
+  uint16_t* wb = (uint16_t*)take(2 * (size_t)MLP_WB_COUNT);
+  const size_t n2 = 2 * (size_t)MLP_NH * B, n4 = 4 * (size_t)MLP_NH * B;
+  TrainScratch s;
+  s.xT = (uint16_t*)take(2 * (size_t)MLP_NIN * B);
+  s.h1T = (uint16_t*)take(n2);
+  s.dh2T = (uint16_t*)take(n2);
+  s.dh1T = (uint16_t*)take(n2);
+  s.h2 = (uint16_t*)take(n2);
+  s.dh2 = (float*)take(n4);
+  s.dh1 = (float*)take(n4);
+  s.dz = (float*)take(4 * (size_t)MLP_NOUT * B);
+  s.loss = (float*)take(4 * (size_t)B);
   hipLaunchKernelGGL(k_mlp_prep, dim3(16), dim3(256), 0, st, w, wb);
   for (int b = first_batch; b < first_batch + nbatch; b++) {
     const int t = t0 + (b - first_batch) + 1;
     const float c1 = (float)(1.0 - pow((double)hp.beta1, (double)t));
     const float c2 = (float)(1.0 - pow((double)hp.beta2, (double)t));
     const int nvalid = n - b * B < B ? n - b * B : B;
-    hipLaunchKernelGGL(k_mlp_grad, dim3(nparts), dim3(256), 0, st, X, Y, order, n, B, b, rows, w, wb, hp, part);
-    hipLaunchKernelGGL(k_mlp_step, dim3(MLP_NPARAM / 256 + 1), dim3(256), 0, st, part, nparts, nvalid, w, am, av, wb, hp,
-                       c1, c2, loss_out ? loss_out + b : nullptr, b + 1 == first_batch + nbatch ? grad_out : nullptr);
+    hipLaunchKernelGGL(k_mlp_rows, dim3(B / TR), dim3(256), 0, st, X, Y, order, n, B, b, w, wb, hp, s);
+    hipLaunchKernelGGL(k_mlp_update, dim3(UPD_WGS), dim3(256), 0, st, s, B, nvalid, w, am, av, wb, hp, c1, c2,
+                       loss_out ? loss_out + b : nullptr, b + 1 == first_batch + nbatch ? grad_out : nullptr);
   }
   return hipGetLastError();
 }

@@ -38,12 +38,11 @@ hipError_t launch_mlp_infer(const uint16_t* X, int n, const uint16_t* wb, const 
                             hipStream_t st);
 // device scratch of one training call with batch B (256-byte aligned pieces)
 constexpr size_t mlp_align256(size_t b) { return (b + 255) / 256 * 256; }
-// floats of one workgroup's partial gradient and loss sum (a 256-byte multiple)
-constexpr int MLP_PART = (int)(mlp_align256(4 * (size_t)(MLP_NPARAM + 1)) / 4);
-constexpr int mlp_train_parts_c(int B) { return B <= 2048 ? (B + 31) / 32 : (B + 63) / 64; }
 constexpr size_t mlp_train_scratch_bytes_c(int B) {
-  return mlp_align256(2 * (size_t)MLP_WB_COUNT)                  // bfloat16 operand copies
-         + 4 * (size_t)MLP_PART * (size_t)mlp_train_parts_c(B);  // partial gradients
+  return mlp_align256(2 * (size_t)MLP_WB_COUNT)                                          // bfloat16 operand copies
+         + mlp_align256(2 * (size_t)MLP_NIN * B) + 4 * mlp_align256(2 * (size_t)MLP_NH * B)  // batch, activations
+         + 2 * mlp_align256(4 * (size_t)MLP_NH * B)                                      // their gradients, binary32
+         + mlp_align256(4 * (size_t)MLP_NOUT * B) + mlp_align256(4 * (size_t)B);         // logit gradients, losses
 }
 size_t mlp_train_scratch_bytes(int B);
 // the library-held scratch of amrv_mlp_train_noalloc: the largest batch
