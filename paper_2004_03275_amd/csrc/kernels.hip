@@ -891,6 +891,7 @@ __global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a,
     if (tid == 0) sLeaf = queue_next(sc, g.n);
     __syncthreads();
     leaf = sLeaf;
+    __syncthreads();  // read by every wave before thread 0 takes the next leaf
   }
   // a leaf's tables as this thread needs them: the kind, neighbour and slot of
   // its ring cell's face and the kind of its face's
