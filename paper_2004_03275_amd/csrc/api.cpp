@@ -373,7 +373,14 @@ int enqueue_device_step(amrv_forest* f, double t_end, bool assume_valid = false)
   return enqueue_step(f, &c, assume_valid);
 }
 
+// the pinned words of a call that waits for the GPU.  Such a call cannot be part
+// of a graph: it is refused before it enqueues anything, since work recorded
+// instead of run would leave the marks of clear slots and filled slabs false
+// (and a wait would end the caller's capture, with the stream unusable after it)
 int need_host(amrv_forest* f) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (f->st && hipStreamIsCapturing(f->st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
+    return hip_fail(hipErrorStreamCaptureUnsupported, "a call that waits for the GPU");
   if (!f->host) f->host = host_words().take();
   return f->host ? AMRV_OK : fail(AMRV_ENOMEM, "pinned host memory");
 }
@@ -661,9 +668,9 @@ int amrv_max_dt(amrv_forest* f, double* dt_out) {
   f->third_clear = false;
   HIPCHK(launch_cfl(f->geo, f->lc, f->U[0], f->pp, third, nullptr, f->st));
   HIPCHK(launch_red_result(f->red, f->cnt, f->pp, f->host, f->st));
-  f->third_clear = true;
   rc = host_sync(f);
   if (rc) return rc;
+  f->third_clear = true;
   f->fold_valid = true;
   if (f->host[2]) return fail(AMRV_ENONPHYSICAL, "non-physical state (rho <= 0, p <= 0 or NaN)");
   double smax, cmax;
