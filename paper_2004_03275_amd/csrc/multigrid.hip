@@ -1328,6 +1328,15 @@ __global__ void __launch_bounds__(256) k_mg3_resnorm(MgDev g, int with_f) {
   fold_norms(g, f, br, bf, with_f);
 }
 
+// a pair of cells of a caller's field, which need only be aligned as doubles are
+// (one 16-byte access all the same: global memory takes those at any 4 bytes)
+__device__ __forceinline__ double2 load_pair(const double* p) {
+  double2 v;
+  __builtin_memcpy(&v, p, sizeof v);
+  return v;
+}
+__device__ __forceinline__ void store_pair(double* p, double2 v) { __builtin_memcpy(p, &v, sizeof v); }
+
 // a natural-order field to and from a split array, one pair per thread
 __global__ void __launch_bounds__(256) k_mg3_reorder(int lg, const double* src, double* dst, int to_split) {
   const int p = blockIdx.x * 256 + threadIdx.x, half = 1 << (3 * lg - 1);
@@ -1335,12 +1344,12 @@ __global__ void __launch_bounds__(256) k_mg3_reorder(int lg, const double* src, 
   const int n = 1 << lg, r = p >> (lg - 1);
   const bool odd = ((r & (n - 1)) + (r >> lg)) & 1;  // the left cell's colour
   if (to_split) {
-    const double2 v = reinterpret_cast<const double2*>(src)[p];
+    const double2 v = load_pair(src + 2 * (size_t)p);
     dst[p] = odd ? v.y : v.x;
     dst[half + p] = odd ? v.x : v.y;
   } else {
     const double a = src[p], b = src[half + p];
-    reinterpret_cast<double2*>(dst)[p] = odd ? double2{b, a} : double2{a, b};
+    store_pair(dst + 2 * (size_t)p, odd ? double2{b, a} : double2{a, b});
   }
 }
 
@@ -1524,16 +1533,16 @@ __global__ void __launch_bounds__(256) k_rd3_imex_final(MgDev g, RdK p, double* 
     fu[c] = ru + p.Du * lu[c];
     fv[c] = rv + p.Dv * lv[c];
   }
-  double2* u2 = reinterpret_cast<double2*>(u) + q;
-  double2* v2 = reinterpret_cast<double2*>(v) + q;
+  double* u2 = u + 2 * (size_t)q;
+  double* v2 = v + 2 * (size_t)q;
   const double2 eu = reinterpret_cast<const double2*>(Eu)[q], ev = reinterpret_cast<const double2*>(Ev)[q];
-  double2 a = *u2, b = *v2;
+  double2 a = load_pair(u2), b = load_pair(v2);
   a.x = a.x + hdt * (eu.x + (odd ? fu[1] : fu[0]));
   a.y = a.y + hdt * (eu.y + (odd ? fu[0] : fu[1]));
   b.x = b.x + hdt * (ev.x + (odd ? fv[1] : fv[0]));
   b.y = b.y + hdt * (ev.y + (odd ? fv[0] : fv[1]));
-  *u2 = a;
-  *v2 = b;
+  store_pair(u2, a);
+  store_pair(v2, b);
 }
 
 int blocks_of(int n) { return (n + 255) / 256; }

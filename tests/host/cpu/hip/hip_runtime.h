@@ -206,3 +206,31 @@ typedef struct Stream* hipStream_t;
 enum hipError_t { hipSuccess, hipErrorUnknown };
 inline hipError_t hipGetLastError() { return hipSuccess; }
 #define hipLaunchKernelGGL(...) ((void)0)
+
+// the runtime calls of the sources' host code: never reached
+typedef struct Graph* hipGraph_t;
+typedef struct GraphExec* hipGraphExec_t;
+typedef struct Event* hipEvent_t;
+enum { hipStreamCaptureModeThreadLocal, hipMemcpyDeviceToDevice, hipFuncAttributeMaxDynamicSharedMemorySize };
+inline const char* hipGetErrorString(hipError_t) { return "no GPU"; }
+#define EMU_NO_GPU(name)             \
+  template <class... A>              \
+  inline hipError_t name(A&&...) {   \
+    return hipErrorUnknown;          \
+  }
+EMU_NO_GPU(hipStreamBeginCapture)
+EMU_NO_GPU(hipStreamEndCapture)
+EMU_NO_GPU(hipStreamSynchronize)
+EMU_NO_GPU(hipGraphInstantiate)
+EMU_NO_GPU(hipGraphLaunch)
+EMU_NO_GPU(hipGraphDestroy)
+EMU_NO_GPU(hipGraphExecDestroy)
+EMU_NO_GPU(hipEventCreate)
+EMU_NO_GPU(hipEventRecord)
+EMU_NO_GPU(hipEventDestroy)
+EMU_NO_GPU(hipEventElapsedTime)
+EMU_NO_GPU(hipMemcpyAsync)
+EMU_NO_GPU(hipMemsetAsync)
+EMU_NO_GPU(hipFuncSetAttribute)
+EMU_NO_GPU(hipHostMalloc)
+EMU_NO_GPU(hipHostFree)
