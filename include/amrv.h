@@ -282,7 +282,7 @@ int amrv_regrid_transfer(amrv_forest* from, amrv_forest* to);
  * keeps consecutive leaves on the same XCD (grid: the workgroup-to-leaf map;
  * persistent: one work queue per XCD over an eighth of the leaves, drained
  * by that XCD's workgroups first); persistent_wgs is the persistent grid size
- * (0 = 2 per compute unit).  The default is AMRV_SCHED_GRID with
+ * (0 = 2 per compute unit, 1 in 2D with variant 0).  The default is AMRV_SCHED_GRID with
  * the remap on, or the result of amrv_autotune. */
 int amrv_set_schedule(amrv_forest* f, int32_t sched, int32_t xcd_remap, int32_t persistent_wgs);
 int amrv_get_schedule(const amrv_forest* f, int32_t* sched, int32_t* xcd_remap, int32_t* persistent_wgs);

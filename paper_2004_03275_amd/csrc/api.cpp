@@ -1024,9 +1024,13 @@ int amrv_autotune(amrv_forest* f, int32_t reps) {
   for (int var : vars) {
     cands.push_back({AMRV_SCHED_GRID, 0, 0, var});
     cands.push_back({AMRV_SCHED_GRID, 1, 0, var});
+    // from what fits a CU at a time (k_stage_plane: one workgroup, the others two); a
+    // second round of workgroups finds the queue empty (KH of 1,024 leaves, 1, 2 and 3
+    // per CU: 23.1, 24.2, 27.4 us)
+    const int fit = f->tab.nd == 2 && var == 0 ? 1 : 2;
     if (f->tab.nd > 1)
       for (int x : {0, 1})
-        for (int k : {2, 3, 4}) cands.push_back({AMRV_SCHED_PERSISTENT, x, k * f->ncu, var});
+        for (int k = fit; k < fit + 3; k++) cands.push_back({AMRV_SCHED_PERSISTENT, x, k * f->ncu, var});
   }
   const int s0 = f->sched, x0 = f->xcd, p0 = f->pwgs, v0 = f->lc.variant;
   hipEvent_t e0, e1;
