@@ -79,17 +79,17 @@ inline void fail(const char* what) {
 
 enum Order { ASCENDING, DESCENDING, RANDOM };
 
-// every workgroup of a one-dimensional launch, one after another
-inline void launch(unsigned grid, unsigned threads, Order order, const std::function<void()>& kernel) {
+// every workgroup of a launch, one after another
+inline void launch(dim3 grid, unsigned threads, Order order, const std::function<void()>& kernel) {
   static std::mt19937 rng(3);
   body = kernel;
-  gridDim = dim3(grid);
+  gridDim = grid;
   blockDim = dim3(threads);
   const unsigned waves = (threads + 63) / 64;
   std::vector<unsigned> turn(waves);
   for (unsigned w = 0; w < waves; w++) turn[w] = order == DESCENDING ? waves - 1 - w : w;
-  for (unsigned b = 0; b < grid; b++) {
-    blockIdx = dim3(b, 0, 0);
+  for (unsigned b = 0; b < grid.x * grid.y; b++) {
+    blockIdx = dim3(b % grid.x, b / grid.x, 0);
     fibers.resize(threads);
     lane_value.assign(waves * 64, 0);
     for (unsigned t = 0; t < threads; t++) {
@@ -211,7 +211,13 @@ inline hipError_t hipGetLastError() { return hipSuccess; }
 typedef struct Graph* hipGraph_t;
 typedef struct GraphExec* hipGraphExec_t;
 typedef struct Event* hipEvent_t;
-enum { hipStreamCaptureModeThreadLocal, hipMemcpyDeviceToDevice, hipFuncAttributeMaxDynamicSharedMemorySize };
+enum {
+  hipStreamCaptureModeThreadLocal,
+  hipMemcpyDeviceToDevice,
+  hipMemcpyDeviceToHost,
+  hipMemcpyHostToDevice,
+  hipFuncAttributeMaxDynamicSharedMemorySize
+};
 inline const char* hipGetErrorString(hipError_t) { return "no GPU"; }
 #define EMU_NO_GPU(name)             \
   template <class... A>              \
