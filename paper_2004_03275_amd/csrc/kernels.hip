@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
     }
   };
 
-  PhysParams P = load_phys(pp);
+  PhysParams P = load_phys<(ND == 3)>(pp);
   double dt;
   if (!stage_clock<ND, PH>(a, pp, P, dt)) return;
   const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;  // GLM damping of psi, once a step
@@ -925,7 +925,7 @@ __global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a,
     loads(leaf);
   }
 
-  PhysParams P = load_phys(pp);
+  PhysParams P = load_phys<false>(pp);
   double dt;
   if (!stage_clock<ND, PH>(a, pp, P, dt)) return;
   const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;  // GLM damping of psi, once a step
@@ -1356,7 +1356,7 @@ __global__ void __launch_bounds__(WGS) k_stage_line(Geo g, StageArgs a, const do
   __shared__ double sL[NV][CH + 2];
   __shared__ double sR[NV][CH + 2];
   __shared__ double sF[NV][CH + 1];
-  PhysParams P = load_phys(pp);
+  PhysParams P = load_phys<false>(pp);
   double dt;
   if (!stage_clock<1, PH>(a, pp, P, dt)) return;
   const double damp = PH == PH_MHD && a.stage == a.rk ? pp[PP_DAMP] : 1.0;

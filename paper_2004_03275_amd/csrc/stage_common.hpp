@@ -106,12 +106,14 @@ __device__ __forceinline__ void cf_flux(const Geo& g, int leaf, int f, int kind,
   }
 }
 
+// CH false: without c_h
+template <bool CH = true>
 __device__ __forceinline__ PhysParams load_phys(const double* __restrict__ pp) {
   PhysParams P;
   P.gamma = pp[PP_GAMMA];
   P.gm1 = pp[PP_GM1];
   P.igm1 = pp[PP_IGM1];
-  P.ch = pp[PP_CH];
+  P.ch = CH ? pp[PP_CH] : 0.0;
   P.cad = pp[PP_CAD];
   P.gcad = pp[PP_GCAD];
   return P;
@@ -270,6 +272,10 @@ __device__ __forceinline__ void step_end(const StepClock& k) {
 // stage kernels: a launch between them cost 4.5 us of a 27 us step of 256 leaves.
 // The 3D kernels are register-bound and leave it to k_step_begin (5 us of a
 // 1.5 ms step and more; the clock inside them cost 8% of the exact 3D kernel).
+// The clock writes the block that pp points to, which the kernels take as
+// unaliased: what a launch writes (beginning: dt, c_h, the damping factor, the
+// time after the step; end: the time) it reads through the clock's own pointer
+// or not at all, so here alone dt and, in 1D and 2D, c_h are read.
 template <int ND, int PH>
 __device__ __forceinline__ bool stage_clock(const StageArgs& a, const double* __restrict__ pp, PhysParams& P,
                                             double& dt) {
@@ -280,6 +286,7 @@ __device__ __forceinline__ bool stage_clock(const StageArgs& a, const double* __
       if constexpr (PH == PH_MHD) P.ch = ch;
     } else {
       dt = pp[PP_DT];
+      if constexpr (PH == PH_MHD) P.ch = pp[PP_CH];
     }
     if (a.end) step_end(a.clk);
   } else {
