@@ -27,6 +27,13 @@
  *    of its own (its one static array, the training scratch of
  *    amrv_mlp_train_noalloc, is part of the loaded code object).  The HIP
  *    stream is borrowed; all work is enqueued on it.
+ *  - Pinned host memory: the first amrv_max_dt or amrv_advance_cfl on a forest
+ *    takes 64 bytes of a page that all forests share (one allocation per 64
+ *    forests; AMRV_ENOMEM if it fails); amrv_forest_destroy gives them back.
+ *    The multigrid solvers allocate theirs when they are created.
+ *  - Calls that wait for the GPU cannot be captured into a HIP graph;
+ *    amrv_max_dt and amrv_advance_cfl return AMRV_EDEVICE while the forest's
+ *    stream is being captured and enqueue nothing.
  *  - State layout: conserved binary64 U[var][leaf][z][y][x], interior cells
  *    only, leaves in the caller's order.  Hydrodynamics: var = (rho, m_x,
  *    [m_y, m_z,] E); MHD: (rho, m.., E, B.., psi); polytrope: (rho, m..).
@@ -44,7 +51,7 @@ extern "C" {
 #define AMRV_EINVAL (-1)        /* bad config, argument, size or dt */
 #define AMRV_EUNBALANCED (-2)   /* leaves overlap, leave gaps or break 2:1 balance */
 #define AMRV_ENONPHYSICAL (-3)  /* rho <= 0, p <= 0 or NaN in the state */
-#define AMRV_ENOMEM (-4)        /* workspace too small */
+#define AMRV_ENOMEM (-4)        /* workspace too small, or no pinned host memory */
 #define AMRV_EDEVICE (-5)       /* HIP runtime error */
 #define AMRV_ENOTSUP (-6)       /* configuration valid but not supported by the kernels */
 
@@ -148,8 +155,10 @@ int amrv_advance(amrv_forest* f, double dt);
  * each step takes dt = min(cfl / max_cells sum_d (|v_d| + c_d)/dx_d, t_end - t)
  * from the Courant reduction of the state it starts from (the last stage of
  * each step folds the reduction of its result into the same pass), so the
- * host does not synchronise between steps; after the first 64 steps to one
- * t_end they replay a captured HIP graph, eight at a time.  *t (host) is the time before and after; a step starting at or
+ * host does not synchronise between steps.  The steps are launched directly,
+ * or, in a call of eight steps or more on a forest that had run 64 to the same
+ * t_end before the call, replayed from a captured HIP graph, eight at a time.
+ * *t (host) is the time before and after; a step starting at or
  * after t_end does nothing.  *taken (may be NULL) counts the steps with
  * dt > 0.  Synchronises at the end; AMRV_ENONPHYSICAL if a step met a
  * non-physical state (the steps after it do nothing).  The same arithmetic

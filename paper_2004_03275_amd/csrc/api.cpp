@@ -43,8 +43,10 @@ int hip_fail(hipError_t e, const char* where) {
 
 constexpr size_t ALIGN = 256;
 
-// Device-timed steps are launched directly until a forest has run DGRAPH_AFTER of
-// them with one end time, then replayed from a graph of DGRAPH_STEPS.  A graph
+// Device-timed steps are launched directly; a call of DGRAPH_STEPS or more on a
+// forest that has run DGRAPH_AFTER of them to the same end time replays them from
+// a graph of DGRAPH_STEPS (a call decides once, as it starts: capturing in the
+// middle of one leaves the GPU idle meanwhile).  A graph
 // costs its capture (several hundred us) and about 8 us between replays, so one
 // of a single step lost to direct launches (Sod 23.0 against 20.0 us a step,
 // KH 34.7 against 32.1), which in turn are bound by the host below about 4 us a
