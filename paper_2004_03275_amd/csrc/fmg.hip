@@ -37,8 +37,8 @@
 // A cycle has no host wait: a solve enqueues as many cycles as the previous
 // solve needed, less one, before it first reads back the problem's residual
 // over the leaves, then checks after every cycle (the stopping rule max |r|
-// <= tol max |f|).  Kernels are templated on the dimension; a 256-thread
-// workgroup walks a block plane by plane.
+// <= tol max |f|).  Kernels are templated on the dimension; a workgroup takes a
+// block or, in 3D on levels of few blocks, a share of its planes.
 //
 // Layout in the caller's workspace (256-byte aligned arrays):
 //   tables   lvl, ij[3], nbr[6], chi[8], cnb[6], par per block (2D uses the
@@ -359,36 +359,27 @@ __host__ __device__ inline double apply_cell(const FmgDev& g, int b, bool leaf, 
 // other leaf cell keeps the f that loading the problem put there.
 
 // a block of level >= 2 adds the bi/trilinear interpolation of its parent's
-// change e = u - uo: weights 9, 3, 3, 1 (/16) in 2D, 27, 9, 3, 1 (/64) in 3D,
-// from the parent cell and its neighbours toward the fine cell, the parent's
-// own cell where that neighbour lies outside the parent
-template <int ND>
-__host__ __device__ inline double prolong_delta(const FmgDev& g, int b, const int* c) {
-  constexpr int NCB = ncb<ND>();
+// change e = u - uo: weights 9, 3, 3, 1 (/16) in 2D, 27, 9, 3, 1 (/64) in 3D
+// (k_fmg_prolong), from the parent cell and its neighbours toward the fine cell,
+// the parent's own cell where that neighbour lies outside the parent
+__host__ __device__ inline double prolong_delta_2d(const FmgDev& g, int b, const int* c) {
+  constexpr int NCB = ncb<2>();
   const int p = g.par[b];
-  int I[3] = {0, 0, 0}, I2[3] = {0, 0, 0};
+  int I[2], I2[2];
 #pragma unroll
-  for (int e = 0; e < ND; e++) {
+  for (int e = 0; e < 2; e++) {
     I[e] = (g.ij[TS * b + e] & 1) * 8 + (c[e] >> 1);
     const int n2 = I[e] + ((c[e] & 1) ? 1 : -1);
     I2[e] = n2 < 0 ? 0 : (n2 > NB - 1 ? NB - 1 : n2);
   }
   const double* up = g.u + (size_t)p * NCB;
   const double* uq = g.uo + (size_t)p * NCB;
-  auto e = [&](int a, int bb, int cc) {
-    const int k[3] = {a ? I2[0] : I[0], bb ? I2[1] : I[1], cc ? I2[2] : I[2]};
+  auto e = [&](int a, int bb) {
+    const int k[3] = {a ? I2[0] : I[0], bb ? I2[1] : I[1], 0};
     const int i = cidx(k);
     return up[i] - uq[i];
   };
-  double d;
-  if constexpr (ND == 2) {
-    d = (9.0 * e(0, 0, 0) + 3.0 * e(1, 0, 0) + 3.0 * e(0, 1, 0) + e(1, 1, 0)) * (1.0 / 16.0);
-  } else {
-    d = (27.0 * e(0, 0, 0) + 9.0 * (e(1, 0, 0) + e(0, 1, 0) + e(0, 0, 1)) +
-         3.0 * (e(1, 1, 0) + e(1, 0, 1) + e(0, 1, 1)) + e(1, 1, 1)) *
-        (1.0 / 64.0);
-  }
-  return d;
+  return (9.0 * e(0, 0) + 3.0 * e(1, 0) + 3.0 * e(0, 1) + e(1, 1)) * (1.0 / 16.0);
 }
 
 // index of cell c of level-1 block b in the n^ND grid (in split order: 3D)
@@ -551,8 +542,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resid_restrict(FmgDev g, int b0) {
 }
 
 
-// a parent block in 3D: L(u) + r (fas_cell's first case) four planes at a
-// time (apply_k)
+// a parent block in 3D: L(u) + r, four planes at a time (apply_k)
 __device__ inline void fas_parent_3d(const FmgDev& g, int b) {
   constexpr int K = 4;
   const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
@@ -630,7 +620,7 @@ __global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_prolong(FmgDev g,
   double* ub = g.u + (size_t)b * ncb<ND>() + NB * NB / 2 + (threadIdx.x & 127);
   if constexpr (ND == 2) {
     const int c[3] = {2 * hx + ((ty + 1) & 1), ty, 0};
-    ub[0] += prolong_delta<2>(g, b, c);
+    ub[0] += prolong_delta_2d(g, b, c);
   } else {
     constexpr int E = 10;  // the octant and one cell around it, clamped to the parent
     __shared__ double e[E * E * E];
@@ -651,7 +641,7 @@ __global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_prolong(FmgDev g,
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < 8; k++) {
-      // prolong_delta's weights and order
+      // the weights above prolong_delta_2d
       const int z = 2 * k + pz, x = 2 * hx + ((ty + z + 1) & 1);
       const int a = (x >> 1) + 1, bb = (ty >> 1) + 1, cc = (z >> 1) + 1;
       const int da = (x & 1) ? 1 : -1, db = (ty & 1) ? E : -E, dc = (z & 1) ? E * E : -E * E;
@@ -1141,8 +1131,8 @@ int build_tree(const amrv_fmg_config* c, const int32_t* level, const int32_t* ij
   return 0;
 }
 
-// the uniform solver of the level-1 grid: one field, the forest's boundary,
-// per-colour sweeps (its smoother choice does not change its result)
+// the uniform solver of the level-1 grid: one field, the forest's boundary, in
+// 2D the tiled launches (the smoother choice does not change its result)
 amrv_mg_config base_config(const amrv_fmg_config* c) {
   amrv_mg_config mc{};
   mc.ndim = fmg_ndim(c);
@@ -1152,7 +1142,7 @@ amrv_mg_config base_config(const amrv_fmg_config* c) {
   mc.pre_sweeps = 2;
   mc.post_sweeps = 2;
   mc.use_graph = 0;
-  mc.smoother = AMRV_MG_TILED;  // 2D: three launches a cycle at 128^2 instead of twelve (3D has per-colour launches only)
+  mc.smoother = AMRV_MG_TILED;  // three launches a cycle at 128^2 instead of twelve (3D has per-colour launches only)
   mc.length = c->length;
   return mc;
 }
@@ -1264,7 +1254,7 @@ int sweeps(amrv_fmg* m, int l, int count) {
   return 0;
 }
 
-// one V-cycle (enqueued; the level-1 solve synchronises inside)
+// one V-cycle (enqueued without a host wait)
 int vcycle(amrv_fmg* m) {
   const int L = m->T.nlev;
   const int pre = m->cfg.pre_sweeps, post = m->cfg.post_sweeps;

@@ -15,9 +15,10 @@
 // plus k_cfl (Courant reduction, Sec. 2.1) and k_lohner (Sec. 1.3 flags).
 //
 // The stencil work is FP64 VALU and HBM traffic: there is no matrix-core
-// contraction here.  The 2D/3D stage kernel streams a 16^3 block through a
-// 16x16 workgroup plane by plane: z-direction data stays in registers, the
-// x/y planes of primitive values, face states and fluxes in LDS.
+// contraction here.  The 3D stage kernel streams a 16^3 block through a 16x16
+// workgroup plane by plane: z-direction data stays in registers, the x/y planes
+// of primitive values, face states and fluxes in LDS.  The 2D one takes a 16^2
+// block's phases with a thread per slope and face (k_stage_plane).
 #include <float.h>
 
 #include <type_traits>
@@ -96,11 +97,12 @@ __device__ __forceinline__ void restrict_item(const Geo& g, const double* __rest
   for (int v = 0; v < NV; v++) g.G[out + (size_t)v * 2 * g.T] = r[v];
 }
 
-template <int ND, int NV>
+// 3D (1D and 2D: in k_prolong_flux)
+template <int NV>
 __global__ void __launch_bounds__(WGS) k_restrict(Geo g, const double* __restrict__ U, const int32_t* __restrict__ list,
                                                   int nlist) {
   const long long i = (long long)blockIdx.x * WGS + threadIdx.x;
-  if (i < (long long)nlist * 2 * g.T) restrict_item<ND, NV>(g, U, list, i);
+  if (i < (long long)nlist * 2 * g.T) restrict_item<3, NV>(g, U, list, i);
 }
 
 // Fine side of a coarse-fine face, one thread per transverse position t:
@@ -838,8 +840,7 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
 constexpr int WGS2 = 576;
 
 template <int PH, int FLUX, int LIM, int AR>
-__global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a,
-                                                                            const double* __restrict__ pp, Sched sc) {
+__global__ void __launch_bounds__(WGS2, 3) k_stage_plane(Geo g, StageArgs a, const double* __restrict__ pp, Sched sc) {
   constexpr int ND = 2;
   using S = Sys<ND, PH>;
   constexpr int NV = S::NV;
@@ -1766,11 +1767,11 @@ hipError_t launch_restrict(const Geo& g, const LaunchCfg& c, const double* U, co
   if (nlist <= 0) return hipSuccess;
   const unsigned nb = blocks_for((long long)nlist * 2 * g.T);
   if (c.phys == PH_MHD)
-    hipLaunchKernelGGL((k_restrict<3, Sys<3, PH_MHD>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
+    hipLaunchKernelGGL((k_restrict<Sys<3, PH_MHD>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
   else if (c.phys == PH_POLY)
-    hipLaunchKernelGGL((k_restrict<3, Sys<3, PH_POLY>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
+    hipLaunchKernelGGL((k_restrict<Sys<3, PH_POLY>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
   else
-    hipLaunchKernelGGL((k_restrict<3, Sys<3, PH_EULER>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
+    hipLaunchKernelGGL((k_restrict<Sys<3, PH_EULER>::NV>), dim3(nb), dim3(WGS), 0, st, g, U, list, nlist);
   return hipGetLastError();
 }
 
@@ -1847,9 +1848,9 @@ hipError_t launch_cfl(const Geo& g, const LaunchCfg& c, const double* U, const d
   if (nb > 2048) nb = 2048;  // 8 workgroups per CU; the rest by the grid stride
 #define BODY_C(ND)                                                                                                    \
   if (c.phys == PH_MHD)                                                                                               \
-    hipLaunchKernelGGL((k_cfl<ND, PH_MHD>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);                  \
+    hipLaunchKernelGGL((k_cfl<ND, PH_MHD>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);             \
   else if (c.phys == PH_POLY)                                                                                         \
-    hipLaunchKernelGGL((k_cfl<ND, PH_POLY>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);                 \
+    hipLaunchKernelGGL((k_cfl<ND, PH_POLY>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);            \
   else                                                                                                                \
     hipLaunchKernelGGL((k_cfl<ND, PH_EULER>), dim3((unsigned)nb), dim3(WGS), 0, st, g, U, physp, red, cnt);
   if (c.ndim == 1) {

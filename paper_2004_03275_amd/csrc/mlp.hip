@@ -31,7 +31,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// 8 consecutive bfloat16 values (16 bytes, 16-byte aligned) as an MFMA operand
+// 8 consecutive bfloat16 values as an MFMA operand (copied: a caller's rows need only a bfloat16's alignment)
 __device__ __forceinline__ bf16x8 load8(const uint16_t* p) {
   bf16x8 r;
   __builtin_memcpy(&r, p, 16);
@@ -276,138 +276,136 @@ __global__ void __launch_bounds__(256) k_mlp_rows(const uint16_t* __restrict__ X
   const int rt = wave & 1, np = wave >> 1;  // forward: a 16-row tile and half of the output units per wave
 
   const int r0 = blockIdx.x * TR;
+  // layer 1; the rows (zeros past the batch's last sample) also to xT
   {
-    // layer 1; the rows (zeros past the batch's last sample) also to xT
-    {
-      const int r = r0 + rt * 16 + lm;
-      const uint16_t* xr = r < nvalid ? X + (size_t)order[b0 + r] * MLP_NIN : nullptr;
-      bf16x8 xa[4];
+    const int r = r0 + rt * 16 + lm;
+    const uint16_t* xr = r < nvalid ? X + (size_t)order[b0 + r] * MLP_NIN : nullptr;
+    bf16x8 xa[4];
 #pragma unroll
-      for (int kt = 0; kt < 4; kt++) xa[kt] = xr ? load8(xr + kt * 32 + lk) : zero8();
+    for (int kt = 0; kt < 4; kt++) xa[kt] = xr ? load8(xr + kt * 32 + lk) : zero8();
 #pragma unroll
-      for (int k2 = 0; k2 < 2; k2++) {
-        uint16_t t[8];
-        const bf16x8 v = np ? xa[2 + k2] : xa[k2];
-        __builtin_memcpy(t, &v, 16);
+    for (int k2 = 0; k2 < 2; k2++) {
+      uint16_t t[8];
+      const bf16x8 v = np ? xa[2 + k2] : xa[k2];
+      __builtin_memcpy(t, &v, 16);
 #pragma unroll
-        for (int j = 0; j < 8; j++) xT[((2 * np + k2) * 32 + lk + j) * TS + rt * 16 + lm] = t[j];
-      }
-#pragma unroll
-      for (int q = 0; q < 2; q++) {
-        const int u = (2 * np + q) * 16 + lm;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kt = 0; kt < 4; kt++) acc = mfma(xa[kt], load8(wb + MLP_WB_W1 + u * MLP_NIN + kt * 32 + lk), acc);
-        const float bias = w[MLP_B1 + u];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-          const float a = acc[i] + bias;
-          const uint16_t hb = to_bf16(a > 0.f ? a : 0.f);
-          h1[(rt * 16 + lq + i) * HS + u] = hb;
-          h1T[u * TS + rt * 16 + lq + i] = hb;
-        }
-      }
+      for (int j = 0; j < 8; j++) xT[((2 * np + k2) * 32 + lk + j) * TS + rt * 16 + lm] = t[j];
     }
-    __syncthreads();
-    // layer 2
 #pragma unroll
     for (int q = 0; q < 2; q++) {
       const int u = (2 * np + q) * 16 + lm;
       f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++)
-        acc = mfma(load8(h1 + (rt * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2 + u * MLP_NH + kt * 32 + lk), acc);
-      const float bias = w[MLP_B2 + u];
+      for (int kt = 0; kt < 4; kt++) acc = mfma(xa[kt], load8(wb + MLP_WB_W1 + u * MLP_NIN + kt * 32 + lk), acc);
+      const float bias = w[MLP_B1 + u];
 #pragma unroll
       for (int i = 0; i < 4; i++) {
         const float a = acc[i] + bias;
-        h2[(rt * 16 + lq + i) * HS + u] = to_bf16(a > 0.f ? a : 0.f);
+        const uint16_t hb = to_bf16(a > 0.f ? a : 0.f);
+        h1[(rt * 16 + lq + i) * HS + u] = hb;
+        h1T[u * TS + rt * 16 + lq + i] = hb;
       }
     }
-    __syncthreads();
-    // logits, in unit order
-    if (tid < TR * MLP_NOUT) {
-      const int o = tid >> 5, r = tid & 31;
-      float z = 0.f;
-      for (int k = 0; k < MLP_NH; k++) z = z + from_bf16(h2[r * HS + k]) * from_bf16(wb[MLP_WB_W3 + o * MLP_NH + k]);
-      zs[r][o] = z + w[MLP_B3 + o];
-    }
-    __syncthreads();
-    // logit gradients and loss per row.  The label is Loehner's class (+1
-    // refine, -1 coarsen, 0 keep): target 1 of the refine output for +1, of
-    // the coarsen output for -1; each output's class-weighted binary
-    // cross-entropy, summed
-    if (tid < TR) {
-      float d[MLP_NOUT] = {0.f, 0.f}, lr = 0.f;
-      if (r0 + tid < nvalid) {
-        const float lab = Y[order[b0 + r0 + tid]];
-#pragma unroll
-        for (int o = 0; o < MLP_NOUT; o++) {
-          const float z = zs[tid][o];
-          const float y = o == 0 ? (lab > 0.5f ? 1.f : 0.f) : (lab < -0.5f ? 1.f : 0.f);
-          const float pw = o == 0 ? hp.pos_weight : hp.pos_weight_c;
-          const float sg = 1.f / (1.f + expf(-z));
-          d[o] = ((1.f - y) * sg - pw * y * (1.f - sg)) / Bv;
-          // -(pw y log s + (1-y) log(1-s)) with log s = -softplus(-z)
-          const float sp_neg = fmaxf(-z, 0.f) + log1pf(expf(-fabsf(z)));
-          const float sp_pos = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));
-          lr = lr + (pw * y * sp_neg + (1.f - y) * sp_pos);
-        }
-      }
-      dz[tid][0] = d[0];
-      dz[tid][1] = d[1];
-      s.dz[(size_t)(r0 + tid) * MLP_NOUT] = d[0];
-      s.dz[(size_t)(r0 + tid) * MLP_NOUT + 1] = d[1];
-      s.loss[r0 + tid] = lr;
-    }
-    __syncthreads();
-    // dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0] (binary32, then bfloat16)
-    auto dh2_of = [&](int r, int c, float wr, float wc) -> float {
-      return from_bf16(h2[r * HS + c]) > 0.f ? dz[r][0] * wr + dz[r][1] * wc : 0.f;
-    };
-    {
-      const int c = tid & 63, ra = 8 * wave;
-      const float wr = from_bf16(wb[MLP_WB_W3 + c]), wc = from_bf16(wb[MLP_WB_W3 + MLP_NH + c]);
-      uint16_t t[8];
-#pragma unroll
-      for (int j = 0; j < 8; j++) {
-        const float d = dh2_of(ra + j, c, wr, wc);
-        s.dh2[(size_t)(r0 + ra + j) * MLP_NH + c] = d;
-        t[j] = to_bf16(d);
-        dh2[(ra + j) * HS + c] = t[j];
-      }
-      __builtin_memcpy(&dh2T[c * TS + ra], t, 16);
-    }
-    __syncthreads();
-    // dh1 = dh2 W2 * [h1 > 0]: 8 tiles, two per wave
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-      const int u = wave * 16 + lm;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kt = 0; kt < 2; kt++)
-        acc = mfma(load8(dh2 + (j * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2T + u * MLP_NH + kt * 32 + lk), acc);
-#pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int r = j * 16 + lq + i;
-        const float d = from_bf16(h1[r * HS + u]) > 0.f ? acc[i] : 0.f;
-        dh1[r * (MLP_NH + 1) + u] = d;
-        dh1T[u * TS + r] = to_bf16(d);
-      }
-    }
-    __syncthreads();
-    // the transposed operands and the rows' values to memory, 16 bytes a thread
-    auto put = [&](uint16_t* to, const uint16_t* from) { __builtin_memcpy(to, from, 16); };
-    for (int i = tid; i < MLP_NIN * TR / 8; i += 256)
-      put(s.xT + (size_t)(i >> 2) * B + r0 + 8 * (i & 3), xT + (i >> 2) * TS + 8 * (i & 3));
-    const int u = tid >> 2, q = 8 * (tid & 3);
-    put(s.h1T + (size_t)u * B + r0 + q, h1T + u * TS + q);
-    put(s.dh2T + (size_t)u * B + r0 + q, dh2T + u * TS + q);
-    put(s.dh1T + (size_t)u * B + r0 + q, dh1T + u * TS + q);
-    put(s.h2 + (size_t)(r0 + (tid >> 3)) * MLP_NH + 8 * (tid & 7), h2 + (tid >> 3) * HS + 8 * (tid & 7));
-    for (int i = tid; i < TR * MLP_NH; i += 256)
-      s.dh1[(size_t)r0 * MLP_NH + i] = dh1[(i >> 6) * (MLP_NH + 1) + (i & 63)];
   }
+  __syncthreads();
+  // layer 2
+#pragma unroll
+  for (int q = 0; q < 2; q++) {
+    const int u = (2 * np + q) * 16 + lm;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 2; kt++)
+      acc = mfma(load8(h1 + (rt * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2 + u * MLP_NH + kt * 32 + lk), acc);
+    const float bias = w[MLP_B2 + u];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const float a = acc[i] + bias;
+      h2[(rt * 16 + lq + i) * HS + u] = to_bf16(a > 0.f ? a : 0.f);
+    }
+  }
+  __syncthreads();
+  // logits, in unit order
+  if (tid < TR * MLP_NOUT) {
+    const int o = tid >> 5, r = tid & 31;
+    float z = 0.f;
+    for (int k = 0; k < MLP_NH; k++) z = z + from_bf16(h2[r * HS + k]) * from_bf16(wb[MLP_WB_W3 + o * MLP_NH + k]);
+    zs[r][o] = z + w[MLP_B3 + o];
+  }
+  __syncthreads();
+  // logit gradients and loss per row.  The label is Loehner's class (+1
+  // refine, -1 coarsen, 0 keep): target 1 of the refine output for +1, of
+  // the coarsen output for -1; each output's class-weighted binary
+  // cross-entropy, summed
+  if (tid < TR) {
+    float d[MLP_NOUT] = {0.f, 0.f}, lr = 0.f;
+    if (r0 + tid < nvalid) {
+      const float lab = Y[order[b0 + r0 + tid]];
+#pragma unroll
+      for (int o = 0; o < MLP_NOUT; o++) {
+        const float z = zs[tid][o];
+        const float y = o == 0 ? (lab > 0.5f ? 1.f : 0.f) : (lab < -0.5f ? 1.f : 0.f);
+        const float pw = o == 0 ? hp.pos_weight : hp.pos_weight_c;
+        const float sg = 1.f / (1.f + expf(-z));
+        d[o] = ((1.f - y) * sg - pw * y * (1.f - sg)) / Bv;
+        // -(pw y log s + (1-y) log(1-s)) with log s = -softplus(-z)
+        const float sp_neg = fmaxf(-z, 0.f) + log1pf(expf(-fabsf(z)));
+        const float sp_pos = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));
+        lr = lr + (pw * y * sp_neg + (1.f - y) * sp_pos);
+      }
+    }
+    dz[tid][0] = d[0];
+    dz[tid][1] = d[1];
+    s.dz[(size_t)(r0 + tid) * MLP_NOUT] = d[0];
+    s.dz[(size_t)(r0 + tid) * MLP_NOUT + 1] = d[1];
+    s.loss[r0 + tid] = lr;
+  }
+  __syncthreads();
+  // dh2 = (dz_r w3_r + dz_c w3_c) * [h2 > 0] (binary32, then bfloat16)
+  auto dh2_of = [&](int r, int c, float wr, float wc) -> float {
+    return from_bf16(h2[r * HS + c]) > 0.f ? dz[r][0] * wr + dz[r][1] * wc : 0.f;
+  };
+  {
+    const int c = tid & 63, ra = 8 * wave;
+    const float wr = from_bf16(wb[MLP_WB_W3 + c]), wc = from_bf16(wb[MLP_WB_W3 + MLP_NH + c]);
+    uint16_t t[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+      const float d = dh2_of(ra + j, c, wr, wc);
+      s.dh2[(size_t)(r0 + ra + j) * MLP_NH + c] = d;
+      t[j] = to_bf16(d);
+      dh2[(ra + j) * HS + c] = t[j];
+    }
+    __builtin_memcpy(&dh2T[c * TS + ra], t, 16);
+  }
+  __syncthreads();
+  // dh1 = dh2 W2 * [h1 > 0]: 8 tiles, two per wave
+#pragma unroll
+  for (int j = 0; j < 2; j++) {
+    const int u = wave * 16 + lm;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kt = 0; kt < 2; kt++)
+      acc = mfma(load8(dh2 + (j * 16 + lm) * HS + kt * 32 + lk), load8(wb + MLP_WB_W2T + u * MLP_NH + kt * 32 + lk), acc);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int r = j * 16 + lq + i;
+      const float d = from_bf16(h1[r * HS + u]) > 0.f ? acc[i] : 0.f;
+      dh1[r * (MLP_NH + 1) + u] = d;
+      dh1T[u * TS + r] = to_bf16(d);
+    }
+  }
+  __syncthreads();
+  // the transposed operands and the rows' values to memory, 16 bytes a thread
+  auto put = [&](uint16_t* to, const uint16_t* from) { __builtin_memcpy(to, from, 16); };
+  for (int i = tid; i < MLP_NIN * TR / 8; i += 256)
+    put(s.xT + (size_t)(i >> 2) * B + r0 + 8 * (i & 3), xT + (i >> 2) * TS + 8 * (i & 3));
+  const int u = tid >> 2, q = 8 * (tid & 3);
+  put(s.h1T + (size_t)u * B + r0 + q, h1T + u * TS + q);
+  put(s.dh2T + (size_t)u * B + r0 + q, dh2T + u * TS + q);
+  put(s.dh1T + (size_t)u * B + r0 + q, dh1T + u * TS + q);
+  put(s.h2 + (size_t)(r0 + (tid >> 3)) * MLP_NH + 8 * (tid & 7), h2 + (tid >> 3) * HS + 8 * (tid & 7));
+  for (int i = tid; i < TR * MLP_NH; i += 256)
+    s.dh1[(size_t)r0 * MLP_NH + i] = dh1[(i >> 6) * (MLP_NH + 1) + (i & 63)];
 }
 
 // Workgroups 0..11: the 32 + 16 tiles of dW1 = dh1^T X and dW2 = dh2^T h1, one

@@ -5,9 +5,14 @@
 //
 // Layout in the caller's workspace (every array 256-byte aligned):
 //   phi[field][level], f[field][level]   n_l^d doubles each, n_l = n >> l,
-//                                         x fastest; level 0 is the grid
+//                                         level 0 is the grid; x fastest, or in
+//                                         3D above the tail (constant
+//                                         coefficient) in split order
+//                                         (mg_internal.hpp)
 //   tmp[4]                                n^d doubles (reaction-diffusion
-//                                         temporaries)
+//                                         temporaries; between explicit steps
+//                                         tmp[2 + field] holds the coarse
+//                                         matrix, k_mg_coarse_matrix)
 //   par                                   lambda per field, 1/diagonal per
 //                                         field and level, 1/h^2 per level
 // plus pinned host memory for the per-block residual maxima, folded on the
@@ -18,8 +23,10 @@
 // averages it into the coarse right-hand side and zeroes the coarse
 // correction (in 2D both in one tiled launch, k_mg_down2d); the coarse
 // levels of at most 4,096 cells are solved by one workgroup per field with
-// every level resident in LDS (the whole descent, the exact solve on the
-// 2-per-side grid and the ascent in one launch); back up, a launch adds the
+// every level resident in LDS (k_mg_tail: the whole descent and ascent in one
+// launch, with the levels of at most 64 cells, down to the exact solve on the
+// 2-per-side grid, as one product with the coarse matrix; with a cell
+// coefficient k_mg_tail_var, level by level); back up, a launch adds the
 // bi/trilinear interpolation of the coarse correction, then `post` sweeps
 // (again one tiled launch in 2D, the finest one also folding the residual
 // norms).  Fields (u and v of the reaction-diffusion steps) are solved by the

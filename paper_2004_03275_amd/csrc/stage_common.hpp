@@ -1,5 +1,5 @@
 // stage_common.hpp -- device helpers shared by the stage-update kernels
-// (kernels.hip, stage3d.hip): state indexing, ghost cells of a leaf from its
+// (kernels.hip and the units that include it): state indexing, ghost cells of a leaf from its
 // neighbours or the coarse-fine slabs, coarse-fine face fluxes, the Courant
 // fold, the persistent work queues, the SSP combination and the fused
 // restriction of a 3D leaf's result.
