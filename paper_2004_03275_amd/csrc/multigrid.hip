@@ -883,6 +883,7 @@ __device__ void wave_cycle(double* P, int lg0, int lev0, const MgDev& g, int f, 
       sync();
     }
   };
+  sync();  // the lanes' phi and f
   for (int lg = lg0, lev = lev0; lg > 1; lg--, lev++) {
     double* p = level(P, lg);
     double* r = p + (1 << (ND * lg));
