@@ -834,7 +834,7 @@ __global__ void __launch_bounds__(WGS, (Sys<ND, PH>::NV > 5) ? 1 : (SPLIT ? (lim
 // which leaves 168 registers per thread (no spills) and LDS enough for any
 // system; forests of more leaves than CUs walk them, each XCD its own eighth.
 // One stage, 256 threads per leaf and workgroups per leaf -> this: Orszag-Tang
-// 1,024 leaves 44.1 -> 28.3 us (4 leaves per CU; VALU issue alone 2.8 us a
+// 1,024 leaves 44.1 -> 28.3 us (4 leaves per CU; VALU issue alone 2.6 us a
 // leaf), Kelvin-Helmholtz 256 leaves 8.8 -> 7.2 us, 1,024 leaves 17.6 us, dam
 // break 84 leaves 9.2 -> 6.6 us (a launch that touches memory once: 3 us).
 constexpr int WGS2 = 576;

@@ -203,7 +203,7 @@ inline unsigned __float_as_uint(float v) { return bits_as<unsigned>(v); }
 #define __builtin_amdgcn_wave_barrier() emu::wait(emu::AT_WAVE)
 
 typedef struct Stream* hipStream_t;
-enum hipError_t { hipSuccess, hipErrorUnknown };
+enum hipError_t { hipSuccess, hipErrorInvalidValue, hipErrorUnknown };
 inline hipError_t hipGetLastError() { return hipSuccess; }
 #define hipLaunchKernelGGL(...) ((void)0)
 
