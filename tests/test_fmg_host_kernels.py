@@ -17,7 +17,7 @@ HOST = os.path.join(ROOT, "tests", "host")
 
 
 @pytest.fixture(scope="module")
-def checker(tmp_path_factory):
+def program(tmp_path_factory):
     if not shutil.which("g++"):
         pytest.skip("g++ not available")
     exe = str(tmp_path_factory.mktemp("fmgkern") / "fmg_kernels")
@@ -40,7 +40,7 @@ CASES = [
 
 @pytest.mark.parametrize("bc", [0, 1])
 @pytest.mark.parametrize("nd,base,max_level,centre,radius", CASES)
-def test_kernels_equal_the_per_cell_functions(checker, tmp_path, bc, nd, base, max_level, centre, radius):
+def test_kernels_equal_the_per_cell_functions(program, tmp_path, bc, nd, base, max_level, centre, radius):
     f = W.fmg_forest(W.fmg_scheme(base=base, max_level=max_level, bc=bc, ndim=nd), centre=centre, radius=radius)
     assert f.n >= 1
     s = f.scheme
@@ -49,7 +49,7 @@ def test_kernels_equal_the_per_cell_functions(checker, tmp_path, bc, nd, base, m
         fh.write(f"{f.n} {s.base_blocks[0]} {s.max_level} {bc} {nd}\n")
         for k in range(f.n):
             fh.write(f"{f.level[k]} {f.ijk[k, 0]} {f.ijk[k, 1]} {f.ijk[k, 2]}\n")
-    out = subprocess.run([checker, str(path)], capture_output=True, text=True, timeout=300)
+    out = subprocess.run([program, str(path)], capture_output=True, text=True, timeout=300)
     print(f.level_counts(), out.stdout.strip())
     assert out.returncode == 0, (out.stdout[-2000:], out.stderr[-3000:])
     assert "mismatches 0" in out.stdout
