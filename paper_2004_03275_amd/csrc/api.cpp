@@ -53,9 +53,18 @@ constexpr size_t ALIGN = 256;
 // launch (Sod 18.8 us a step in calls of 20, 16 of them replayed).
 constexpr int DGRAPH_STEPS = 8, DGRAPH_AFTER = 64;
 
+// The small blocks that a forest is created with, uploaded in one copy (with the
+// counters in a copy of their own a forest of one block took 57 us to create, so
+// 30 us)
+struct Params {
+  alignas(ALIGN) double pp[PP_COUNT];
+  alignas(ALIGN) double lp[LP_COUNT];
+  alignas(ALIGN) unsigned cnt[CNT_COUNT];
+};
+
 struct Layout {
   size_t off_U[3], off_G, off_FF, off_lvl, off_ijk, off_nbr, off_slot, off_kind, off_fslot, off_sleaf, off_sface,
-      off_rlist, off_plist, off_pp, off_lp, off_red, off_cnt, off_emax, off_flags, off_mw, off_mwb, off_mx, off_mz,
+      off_rlist, off_plist, off_params, off_red, off_emax, off_flags, off_mw, off_mwb, off_mx, off_mz,
       off_munc, off_xfer, off_zd, total;
 };
 
@@ -87,10 +96,8 @@ Layout plan(const amrv_config& c, const Tables& t) {
   L.off_sface = take(sizeof(int32_t) * std::max(1, t.nslot));
   L.off_rlist = take(sizeof(int32_t) * std::max<size_t>(1, t.rlist.size()));
   L.off_plist = take(sizeof(int32_t) * std::max<size_t>(1, t.plist.size()));
-  L.off_pp = take(sizeof(double) * PP_COUNT);
-  L.off_lp = take(sizeof(double) * LP_COUNT);
+  L.off_params = take(sizeof(Params));
   L.off_red = take(sizeof(unsigned long long) * RED_WORDS);
-  L.off_cnt = take(sizeof(unsigned) * CNT_COUNT);
   L.off_emax = take(sizeof(double) * t.n);
   L.off_flags = take(sizeof(int8_t) * t.n);
   L.off_mw = take(sizeof(float) * MLP_NPARAM);
@@ -505,10 +512,11 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
   const Tables& t = f->tab;
   const Layout& L = f->lay;
   for (int i = 0; i < 3; i++) f->U[i] = (double*)(f->ws + L.off_U[i]);
-  f->pp = (double*)(f->ws + L.off_pp);
-  f->lp = (double*)(f->ws + L.off_lp);
+  Params* dev_params = (Params*)(f->ws + L.off_params);
+  f->pp = dev_params->pp;
+  f->lp = dev_params->lp;
+  f->cnt = dev_params->cnt;
   f->red = (unsigned long long*)(f->ws + L.off_red);
-  f->cnt = (unsigned*)(f->ws + L.off_cnt);
   f->emax = (double*)(f->ws + L.off_emax);
   f->flags = (int8_t*)(f->ws + L.off_flags);
   f->rlist = (int32_t*)(f->ws + L.off_rlist);
@@ -563,7 +571,8 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
     return hipMemcpyAsync(f->ws + off, src, bytes, hipMemcpyHostToDevice, f->st);
   };
   const size_t nsl = (size_t)t.nslot;
-  double pp[PP_COUNT] = {0};
+  Params params{};
+  double *pp = params.pp, *lp = params.lp;
   pp[PP_GAMMA] = cfg->gamma;
   pp[PP_GM1] = cfg->gamma - 1.0;
   pp[PP_IGM1] = 1.0 / (cfg->gamma - 1.0);
@@ -576,8 +585,6 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
         const double rd = cfg->cada_radius * ((cfg->xmax[d] - cfg->xmin[d]) / cells);
         pp[PP_CTHR + 3 * l + d] = rd * rd;
       }
-  const unsigned cnt0[CNT_COUNT] = {0};
-  double lp[LP_COUNT] = {0};
   lp[LP_EPS] = cfg->lohner_eps;
   lp[LP_WRHO] = cfg->lohner_w_rho;
   lp[LP_WP] = cfg->lohner_w_p;
@@ -593,9 +600,7 @@ int amrv_forest_create(const amrv_config* cfg, int64_t n, const int32_t* lev, co
                      up(L.off_sface, t.sface.data(), 4 * nsl),
                      up(L.off_rlist, t.rlist.data(), 4 * t.rlist.size()),
                      up(L.off_plist, t.plist.data(), 4 * t.plist.size()),
-                     up(L.off_pp, pp, sizeof pp),
-                     up(L.off_lp, lp, sizeof lp),
-                     up(L.off_cnt, cnt0, sizeof cnt0),
+                     up(L.off_params, &params, sizeof params),
                      hipStreamSynchronize(f->st)};
   for (hipError_t x : es)
     if (x != hipSuccess) {
