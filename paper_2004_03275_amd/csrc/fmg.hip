@@ -438,6 +438,29 @@ __global__ void __launch_bounds__(ND == 3 ? WG : WG / 2) k_fmg_smooth(FmgDev g, 
   }
 }
 
+// bit per face of block b with a refined neighbour
+template <int ND>
+__host__ __device__ inline unsigned refined_faces(const FmgDev& g, int b) {
+  unsigned refined = 0;
+#pragma unroll
+  for (int face = 0; face < 2 * ND; face++) {
+    const int nb = g.nbr[FS * b + face];
+    if (nb >= 0 && g.chi[CS * nb] >= 0) refined |= 1u << face;
+  }
+  return refined;
+}
+
+// cell c lies along one of them
+template <int ND>
+__host__ __device__ inline bool along(unsigned refined, const int* c) {
+  bool r = false;
+  if (refined)
+#pragma unroll
+    for (int face = 0; face < 2 * ND; face++)
+      r = r || ((refined >> face & 1) && c[face >> 1] == ((face & 1) ? NB - 1 : 0));
+  return r;
+}
+
 // lap(u) - lambda u at K cells of block b (u their values): apply_cell's
 // arithmetic with the loads batched as in stencil_k
 template <int ND, int K, bool GHOSTS = false>
@@ -697,12 +720,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resmax(FmgDev g, const int* leafblk,
   const int b = leafblk[ND == 3 ? xcd_block(blockIdx.x, gridDim.x) : (int)blockIdx.x];
   constexpr int NCB = ncb<ND>(), K = ND == 3 ? 4 : 1, NF = nface<ND>();
   const double ih2 = g.ih2[g.lvl[b]];
-  unsigned refined = 0;  // faces with a refined neighbour
-#pragma unroll
-  for (int face = 0; face < 2 * ND; face++) {
-    const int nb = g.nbr[FS * b + face];
-    if (nb >= 0 && g.chi[CS * nb] >= 0) refined |= 1u << face;
-  }
+  const unsigned refined = refined_faces<ND>(g, b);
   double mr = 0.0, mf = 0.0;
   const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
   const int span = ND == 3 ? NB / gridDim.y : 1;
@@ -722,12 +740,7 @@ __global__ void __launch_bounds__(WG) k_fmg_resmax(FmgDev g, const int* leafblk,
 #pragma unroll
     for (int k = 0; k < K; k++) {
       const double r = fv[k] - (ih2 * (sc[k] + sw[k] * uv[k] - (2.0 * ND) * uv[k]) - g.lam * uv[k]);
-      bool skip = false;
-      if (refined)
-#pragma unroll
-        for (int face = 0; face < 2 * ND; face++)
-          skip = skip || ((refined >> face & 1) && c[k][face >> 1] == ((face & 1) ? NB - 1 : 0));
-      mr = fmax(mr, skip ? 0.0 : (isnan(r) ? INFINITY : fabs(r)));
+      mr = fmax(mr, along<ND>(refined, c[k]) ? 0.0 : (isnan(r) ? INFINITY : fabs(r)));
       mf = fmax(mf, isnan(fv[k]) ? INFINITY : fabs(fv[k]));
     }
   }
@@ -914,23 +927,68 @@ __device__ __forceinline__ void react(const RdF& p, double u, double v, double& 
   }
 }
 
-// a leaf field into the state of the leaf blocks
+// a leaf field into the state of the leaf blocks, a pair of cells (2 xh, 2 xh + 1:
+// one of each colour at the same place of its half) per thread, so that both
+// sides move whole lines
 template <int ND>
 __global__ void __launch_bounds__(WG) k_fmg_load(FmgDev g, const int* leafblk, const double* w) {
-  constexpr int NCB = ncb<ND>();
-  for (int t = threadIdx.x; t < NCB; t += WG) {
-    int c[3];
-    ncell(t, c);
-    g.u[(size_t)leafblk[blockIdx.x] * NCB + cidx(c)] = w[(size_t)blockIdx.x * NCB + t];
+  constexpr int NCB = ncb<ND>(), HP = NB * NB / 2;  // pairs of a plane
+  const double* src = w + (size_t)blockIdx.x * NCB;
+  double* dst = g.u + (size_t)leafblk[blockIdx.x] * NCB;
+#pragma unroll
+  for (int k = 0; k < (NCB / 2 + WG - 1) / WG; k++) {
+    const int t = threadIdx.x + k * WG;
+    if (t >= NCB / 2) break;
+    const int z = t / HP, p = t % HP;
+    const double a = src[2 * t], b = src[2 * t + 1];
+    const bool odd = ((p >> 3) + z) & 1;  // the left cell's colour
+    double* q = dst + NB * NB * z + p;
+    q[0] = odd ? b : a;
+    q[HP] = odd ? a : b;
   }
 }
 
-// D lap(w) at the leaf cells of the loaded field (the problem's rules; g.lam = 0)
+// D lap(w) at the leaf cells of the loaded field (the problem's rules; g.lam = 0).
+// 3D: with the loaded field's coarse-fine ghosts (k_fmg_ghosts), four planes at a
+// time under the plain stencil, the cells along a refined neighbour after them
+// (4,453 leaves: cell by cell 210 us, so 156 and 16 for the ghosts; in the natural
+// order, cell by cell, 179)
 template <int ND>
 __global__ void __launch_bounds__(WG) k_fmg_lap(FmgDev g, const int* leafblk, double D, double* out) {
-  FMG_PLANES(ND) {
-    const int c[3] = {tx, ty, tz};
-    out[(size_t)blockIdx.x * ncb<ND>() + nidx(c)] = D * apply_cell<ND>(g, leafblk[blockIdx.x], true, c);
+  const int tx = threadIdx.x & (NB - 1), ty = threadIdx.x >> 4;
+  if constexpr (ND == 2) {
+    const int c[3] = {tx, ty, 0};
+    out[(size_t)blockIdx.x * ncb<2>() + nidx(c)] = D * apply_cell<2>(g, leafblk[blockIdx.x], true, c);
+  } else {
+    constexpr int K = 4;
+    const int k0 = xcd_block(blockIdx.x, gridDim.x), b = leafblk[k0];
+    const double* u = g.u + (size_t)b * ncb<3>();
+    double* o = out + (size_t)k0 * ncb<3>();
+    const unsigned refined = refined_faces<3>(g, b);
+    for (int z0 = 0; z0 < NB; z0 += K) {
+      int c[K][3];
+      double uv[K], a[K];
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        c[k][0] = tx;
+        c[k][1] = ty;
+        c[k][2] = z0 + k;
+        uv[k] = u[cidx(c[k])];
+      }
+      apply_k<3, K, true>(g, b, false, c, uv, a);
+#pragma unroll
+      for (int k = 0; k < K; k++)
+        if (!along<3>(refined, c[k])) o[nidx(c[k])] = D * a[k];
+    }
+    for (int face = 0; face < 6; face++) {
+      if (!(refined >> face & 1)) continue;
+      int c[1][3];
+      face_coord<3>(face, threadIdx.x, c[0]);
+      const double uv = u[cidx(c[0])];
+      double a;
+      apply_k<3, 1, true>(g, b, true, c, &uv, &a);
+      o[nidx(c[0])] = D * a;
+    }
   }
 }
 
@@ -1479,8 +1537,10 @@ int amrv_fmg_rd_step(amrv_fmg* m, const amrv_rd_params* p, int32_t scheme, doubl
   g0.lam = 0.0;
   double* const* T = m->tmp;
   // D lap of a leaf field into out
+  const bool ghosts = m->nd == 3 && std::find(m->T.nbr.begin(), m->T.nbr.end(), NBR_NONE) != m->T.nbr.end();
   auto lap = [&](const double* w, double D, double* out) {
     FMG_LAUNCH(k_fmg_load, nl, WG, g0, m->leafblk, w);
+    if (ghosts) FMG_LAUNCH(k_fmg_ghosts, dim3(nl, 2), WG, g0, m->leafblk);
     FMG_LAUNCH(k_fmg_lap, nl, WG, g0, m->leafblk, D, out);
   };
   int total = 0;

@@ -226,8 +226,36 @@ struct Check {
     same(mf, host[1], "max |f|", -1);
   }
 
+  // a leaf field loaded (from 8 bytes past a 16-byte boundary), its Laplacian
+  void field() {
+    const int n = (int)T.leafblk.size();
+    const size_t off = (reinterpret_cast<uintptr_t>(fu.data()) & 15) ? 0 : 1;
+    std::vector<double> w((size_t)n * NCB + 1), out((size_t)n * NCB, NAN), keep = u;
+    for (size_t i = 0; i < w.size(); i++) w[i] = std::sin(0.37 * (double)i);
+    FmgDev h = g;
+    h.lam = 0.0;
+    launch(dim3((unsigned)n), WG, [&] { k_fmg_load<ND>(h, T.leafblk.data(), w.data() + off); });
+    std::vector<double> want = keep;
+    for (int k = 0; k < n; k++)
+      for (int t = 0; t < NCB; t++) {
+        int x[3];
+        ncell(t, x);
+        want[(size_t)T.leafblk[k] * NCB + cidx(x)] = w[off + (size_t)k * NCB + t];
+      }
+    for (size_t i = 0; i < u.size(); i++) same(want[i], u[i], "loaded field", (int)(i / NCB));
+    if (ND == 3) launch(dim3((unsigned)n, 2), WG, [&] { k_fmg_ghosts<ND>(h, T.leafblk.data()); });
+    launch(dim3((unsigned)n), WG, [&] { k_fmg_lap<ND>(h, T.leafblk.data(), 0.7, out.data()); });
+    for (int k = 0; k < n; k++)
+      cells([&](const int* x) {
+        same(0.7 * apply_cell<ND>(h, T.leafblk[k], true, x), out[(size_t)k * NCB + nidx(x)], "Laplacian", T.leafblk[k]);
+      });
+    u = keep;
+    g.u = u.data();
+  }
+
   void run() {
     const int L = T.nlev;
+    field();
     launch(dim3((unsigned)T.leafblk.size(), ND == 3 ? 2 : 1), WG, [&] { k_fmg_ghosts<ND>(g, T.leafblk.data()); });
     ghosts(0, "ghosts");
     norms(ND == 3 ? 2 : 1);
